@@ -225,8 +225,13 @@ qed_status qed_set_step(qed_workspace* ws, int64_t step, qed_stream stream);
 qed_status qed_step(const qed_tables* tables, qed_workspace* ws, const qed_step_params* params,
                     qed_stream stream);
 
-/* n_steps steps; steps are replayed from a HIP graph of graph_steps steps (captured once per
- * workspace and launch shape; 0 = plain launches).  Async. */
+/* n_steps steps: the same results as n_steps calls of qed_step.  In the fields whose particles are
+ * independent (all but the grid kinds) and from 4 steps on, each particle is advanced by many
+ * steps at once (up to 256 per set of launches) and graph_steps has no effect; otherwise steps are
+ * replayed from a HIP graph of graph_steps steps (captured once per workspace and launch shape;
+ * 0 = plain launches).  With kernel timing on (qed_profile), single steps.  When a species buffer
+ * fills up during a run, which children are dropped depends on the order in which particles were
+ * advanced; they are counted and booked alike.  Never allocates device memory; async. */
 qed_status qed_run(const qed_tables* tables, qed_workspace* ws, const qed_step_params* params,
                    int64_t n_steps, int32_t graph_steps, qed_stream stream);
 

@@ -103,6 +103,7 @@ struct qed_tables {
 };
 
 constexpr int64_t kDefaultEventQueue = int64_t(1) << 20;
+constexpr int64_t kMultiMin = 4, kMultiMax = 256;  // steps of a multi-step run
 
 struct qed_workspace {
   int device = 0;
@@ -142,6 +143,11 @@ struct qed_workspace {
   // (field kind, particles per thread, block, precision, table rows)
   int fit[2] = {0, 0};
   int fit_key[2][5] = {{-1, -1, -1, -1, -1}, {-1, -1, -1, -1, -1}};
+  int32_t* d_born = nullptr;      // per lepton slot: first step of a lepton made in a multi-step run
+  size_t born_len = 0;
+  MultiCtl* d_multi = nullptr;
+  int multi_fit[2] = {0, 0};      // blocks per CU of the multi-step lepton and photon kernels
+  int multi_fit_key[4] = {-1, -1, -1, -1};
   int emit_fit = 0;                         // emission-pass blocks per CU (occupancy query)
   int emit_fit_key[3] = {-1, -1, -1};       // field kind, precision, lepton-sweep waves
   size_t win_len = 0;
@@ -468,6 +474,47 @@ qed_status enqueue_step(const qed_tables* tb, qed_workspace* ws, const qed_step_
   return QED_OK;
 }
 
+// k steps of every particle, each particle at once (qed_multi.hip); fields without a grid only
+qed_status enqueue_multi(const qed_tables* tb, qed_workspace* ws, const qed_step_params* p, int k, hipStream_t s) {
+  const bool mixed = ws->prec == QED_FP32_MIXED;
+  MultiArgs m;
+  m.s.inst = ws->d_inst;
+  m.s.acc = ws->d_acc;
+  m.s.glob = ws->d_glob;
+  m.s.base = nullptr;
+  m.s.n_base = 0;
+  m.s.ppt = 1;
+  m.s.tb = device_tabs(tb);
+  m.s.sc = step_const(p);
+  m.s.q.ctl = ws->d_evc;
+  m.s.q.ent = ws->d_evq;
+  m.s.q.cap = ws->evq_cap;
+  m.s.qe = EmitQueue{};
+  m.s.win = ws->d_win;
+  m.s.rec = ws->d_rec;
+  m.s.lmask = ws->d_lmask;
+  m.mc = ws->d_multi;
+  m.evc = ws->d_evc;
+  m.glob = ws->d_glob;
+  m.lep_born = ws->d_born;
+  m.base_lep = ws->d_base;
+  m.base_ph = ws->d_base + 2 * ws->max_inst;
+  m.n_inst = ws->n_inst;
+  m.k = k;
+  m.round = 0;
+  const int key[4] = {ws->field_kind, (int)mixed, m.s.tb.n_eta, m.s.tb.n_cp};
+  if (std::memcmp(key, ws->multi_fit_key, sizeof(key)) != 0) {
+    for (int w = 0; w < 2; ++w)
+      ws->multi_fit[w] = multi_blocks_per_cu(ws->field_kind, w, m.s.tb.n_eta, m.s.tb.n_cp, mixed);
+    std::memcpy(ws->multi_fit_key, key, sizeof(key));
+  }
+  m.lep_grid = ws->cus * ws->multi_fit[0];
+  m.ph_grid = ws->cus * ws->multi_fit[1];
+  launch_multi(ws->field_kind, m, mixed, s);
+  HIP_TRY(hipGetLastError());
+  return QED_OK;
+}
+
 // (Re)computes the photons' pair windows when the step constants or tables differ from those
 // they were made with.  Enqueued on `s` outside any graph capture.
 qed_status ensure_windows(const qed_tables* tb, qed_workspace* ws, const qed_step_params* p, hipStream_t s) {
@@ -653,7 +700,10 @@ qed_status qed_workspace_create(int32_t max_inst, qed_workspace** out) {
   if (e == hipSuccess) e = hipMemset(ws->d_wave_cnt, 0, (size_t)cus * 32 * sizeof(int32_t));
   if (e == hipSuccess) e = hipMemset(ws->d_glob, 0, sizeof(Glob));
   if (e == hipSuccess) e = hipMemset(ws->d_acc, 0, max_inst * sizeof(InstAcc));
+  if (e == hipSuccess) e = hipMalloc((void**)&ws->d_multi, sizeof(MultiCtl));
+  if (e == hipSuccess) e = hipMemset(ws->d_multi, 0, sizeof(MultiCtl));
   if (e == hipSuccess) e = init_crmath();
+  if (e == hipSuccess) e = init_crmath_multi();
   if (e != hipSuccess) {
     qed_workspace_destroy(ws);
     return fail(QED_ERR_HIP, "workspace allocation: %s", hipGetErrorString(e));
@@ -683,6 +733,8 @@ void qed_workspace_destroy(qed_workspace* ws) {
   hipFree(ws->d_win);
   hipFree(ws->d_rec);
   hipFree(ws->d_lmask);
+  hipFree(ws->d_born);
+  hipFree(ws->d_multi);
   delete ws;
 }
 
@@ -788,13 +840,24 @@ qed_status qed_bind(qed_workspace* ws, const qed_instance* inst, int32_t n_inst,
   // compaction scratch: one mover index per photon slot
   std::vector<InstAcc> acc0(n_inst);
   std::memset(acc0.data(), 0, n_inst * sizeof(InstAcc));
-  size_t off = 0, goff = 0;
+  size_t off = 0, goff = 0, loff = 0;
   for (int i = 0; i < n_inst; ++i) {
     acc0[i].n_pair_compacted = ~0ull;  // the first compaction after a bind always runs
     acc0[i].mover_off = (int64_t)off;
     acc0[i].lmask_off = (int64_t)goff;  // the masks are made with the windows
     off += (size_t)inst[i].s[2].capacity;
     goff += ((size_t)inst[i].s[2].capacity + kWinGroup - 1) / kWinGroup;
+    for (int s = 0; s < 2; ++s) {
+      acc0[i].lep_off[s] = (int64_t)loff;
+      loff += (size_t)inst[i].s[s].capacity;
+    }
+  }
+  if (multi_kind(ws->field_kind) && (loff > ws->born_len || !ws->d_born)) {
+    hipFree(ws->d_born);
+    ws->d_born = nullptr;
+    ws->born_len = 0;
+    HIP_TRY(hipMalloc((void**)&ws->d_born, (loff ? loff : 1) * sizeof(int32_t)));
+    ws->born_len = loff ? loff : 1;
   }
   if (goff > ws->lmask_len || !ws->d_lmask) {
     hipFree(ws->d_lmask);
@@ -888,6 +951,13 @@ qed_status qed_run(const qed_tables* tables, qed_workspace* ws, const qed_step_p
   if (graph_steps > 0 && ws->profiling) return fail(QED_ERR_STATE, "kernel timing is on; graph replay cannot record it");
   if ((st = ensure_windows(tables, ws, params, s))) return st;
   int64_t done = 0;
+  if (multi_kind(ws->field_kind) && !ws->profiling && n_steps >= kMultiMin) {
+    // particles are independent: each takes many steps at once.  (Kernel timing reports the
+    // classes of single steps, so it keeps them.)
+    for (; done < n_steps; done += kMultiMax)
+      if ((st = enqueue_multi(tables, ws, params, (int)std::min<int64_t>(kMultiMax, n_steps - done), s))) return st;
+    return QED_OK;
+  }
   if (graph_steps > 0 && n_steps >= graph_steps) {
     char key[256];
     snprintf(key, sizeof(key), "%p|%a|%a|%a|%u|%d|%d|%d|%d", (const void*)tables, params->t0, params->dt,

@@ -62,8 +62,8 @@ __device__ __forceinline__ dd dd_mul_d(dd a, double b) {
   return dd_fast_two_sum(p.hi, p.lo);
 }
 
-// 1/n!, n = 0..29, as double-double; filled by the host (init_crmath in qed_step.hip, the
-// translation unit whose kernels use it)
+// 1/n!, n = 0..29, as double-double; filled by the host (qed_crinit.h) in every source file whose
+// kernels use it
 static __constant__ dd c_inv_fact[30];
 
 constexpr double kLn2A = 0x1.62e42fefa3800p-1;   // ln 2 = A + B + C, A with 42 significant bits

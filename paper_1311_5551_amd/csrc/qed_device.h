@@ -156,6 +156,9 @@ struct InstAcc {
   int64_t lmask_off;           // offset of this instance's live masks (one per kWinGroup photon slots)
   int64_t n_front;             // photons [0, n_front) have no pair rate in any later step (their window
                                // is over; set by the partition at compaction)
+  int64_t lep_off[2];          // offset of the electron and positron slots in the workspace's per-lepton arrays
+  int64_t lep_lo[2], lep_hi[2];  // multi-step run: lepton slots of the current round
+  int64_t ph_lo, ph_hi;        // multi-step run: photon slots of the current round
   int64_t ph_first;            // first photon slot of the photon sweep's chunk list (n_front rounded
                                // down to a chunk)
   unsigned long long hole_ctr, mover_ctr;
@@ -222,6 +225,24 @@ struct Glob {
   int64_t step_cur, step_next;   // device clock: index of the running / next step
   int64_t n_chunks[2];           // chunk-list lengths: 0 leptons, 1 photons
 };
+
+// State of one multi-step run (qed_multi.hip) between its kernels.
+struct MultiCtl {
+  int64_t s0;                    // its first step
+  int64_t n_lep, n_ph;           // chunk-list lengths of the round
+  int32_t lep_chunk, ph_chunk;   // slots per chunk
+  unsigned long long ph_ticket;  // next photon chunk to take
+};
+
+// largest idx with base[idx] <= c (lands on a non-empty entry; see the chunk-list layout)
+__device__ __forceinline__ int find_entry(const int64_t* __restrict__ base, int n, int64_t c) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (base[mid] <= c) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
 
 // Pair-event queue of one step: the photon sweep appends (instance << 40 | slot) of every photon
 // whose optical depth reached zero; the event pass converts them.  When more events occur than

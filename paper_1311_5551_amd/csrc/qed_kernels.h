@@ -24,6 +24,21 @@ struct StepArgs {
   uint64_t* lmask;            // live masks of the photon slot groups; instance i's from acc[i].lmask_off
 };
 
+// a multi-step run: each particle advanced by k steps (qed_multi.hip)
+struct MultiArgs {
+  StepArgs s;
+  MultiCtl* mc;
+  EvCtl* evc;            // the pair-event queue's control words
+  Glob* glob;
+  int32_t* lep_born;     // per lepton slot (acc.lep_off): the step a lepton made in the run is first stepped
+  int64_t* base_lep;     // chunk-list prefixes: (instance, species) of the leptons, instances of the photons
+  int64_t* base_ph;
+  int n_inst;
+  int k;                 // steps
+  int round;             // 0: all particles; later: those made in the round before
+  int lep_grid, ph_grid; // blocks of the lepton and photon kernels
+};
+
 // retirement of photons at compaction (pair window over): the photon spectrum they are counted in
 struct RetireSpec {
   int on = 0;
@@ -72,6 +87,13 @@ int lepton_blocks_per_cu(int fk, int ppt, int block, int n_eta, bool mixed);
 void launch_photon(int fk, const StepArgs& a, int grid, int block, bool mixed, hipStream_t s);
 void launch_pair_events(int fk, const StepArgs& a, int grid, int block, bool mixed, hipStream_t s);
 void launch_emit_events(int fk, const StepArgs& a, int grid, int block, bool mixed, hipStream_t s);
+// field kinds whose particles are independent, so that each can be advanced by many steps at once
+inline bool multi_kind(int fk) {
+  return fk == QED_FIELD_UNIFORM || fk == QED_FIELD_LP_PULSE || fk == QED_FIELD_CP_WAVE || fk == QED_FIELD_CP_STANDING;
+}
+hipError_t init_crmath_multi();
+int multi_blocks_per_cu(int fk, int which, int n_eta, int n_cp, bool mixed);  // which: 0 leptons, 1 photons
+void launch_multi(int fk, MultiArgs m, bool mixed, hipStream_t s);
 void launch_init_tau(const qed_instance* inst, int n_inst, hipStream_t s);
 void launch_ledger(const qed_instance* inst, int n_inst, InstAcc* acc, bool mixed, hipStream_t s);
 void launch_compact(int fk, const qed_instance* inst, int n_inst, InstAcc* acc, const Glob* glob, int64_t* movers,

@@ -20,9 +20,11 @@
 #include <cmath>
 #include <type_traits>
 
+#include "qed_crinit.h"
 #include "qed_device.h"
 #include "qed_kernels.h"
 #include "qed_mixed.h"
+#include "qed_particle.h"
 
 namespace qedk {
 
@@ -120,16 +122,6 @@ __global__ void k_front_clear(InstAcc* acc, int n_inst) {
   for (int i = threadIdx.x; i < n_inst; i += blockDim.x) acc[i].n_front = 0;
 }
 
-// largest idx with base[idx] <= c (lands on a non-empty entry; see the chunk-list layout)
-__device__ __forceinline__ int find_entry(const int64_t* __restrict__ base, int n, int64_t c) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (base[mid] <= c) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 // ---------------------------------------------------------------------------
 // analytic refresh of the grid: the standing wave at t^n, in FP64, stored as FP32
 // ---------------------------------------------------------------------------
@@ -224,18 +216,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
   const int64_t step = uni64(a.glob->step_cur);
   const double t = a.sc.t0 + (double)step * a.sc.dt;
   const double dt = a.sc.dt;
-  const float dtf = (float)dt;
   const int64_t nch = uni64(a.glob->n_chunks[0]);
   const int B = blockDim.x;
   const int64_t CH = (int64_t)B * PPT;
   const bool emit = (a.sc.flags & QED_EMIT) != 0;
-  const double agdt = a.sc.a_gamma * dt;
 
   int cur = -1;  // chunk-list entry (2 instance + species) the context belongs to
   int64_t cb = 0, ce = 0, n = 0;
   LepPtr<MIXED> P{};
   bool d3 = false;
-  double hq = 0.0;
+  LepEnv env{dt, 0.0, (float)dt, emit, rr, rr_q, false, sh, sh32, sLog};
   double qch = 0.0;  // charge of the species (-1 electrons, +1 positrons)
   float tpf0 = 0.0f, psif_max = 0.0f;
   FieldK fK{0.0};
@@ -294,7 +284,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
       n = uni64(a.acc[ii].n_start[sp]);
       d3 = uni32(I.dims) == 3;
       qch = sp == 0 ? -1.0 : 1.0;
-      hq = 0.5 * qch * a.sc.kappa * dt;
+      env.hq = 0.5 * qch * a.sc.kappa * dt;
+      env.d3 = d3;
       __syncthreads();
       const uint64_t* src = (const uint64_t*)&I.field;
       for (int w = threadIdx.x; w < (int)(sizeof(qed_field) / 8); w += B) ((uint64_t*)&sF)[w] = src[w];
@@ -379,13 +370,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
       }
     }
 
-    // position and momentum of one lepton (slots past the chunk's live ones read as zero)
-    struct LepState {
-      Real x, y, z, ux, uy, uz;
-      float xl, yl, zl, uxl, uyl, uzl;  // FP32-mixed low words
-    };
-    auto load_state = [&](unsigned off) -> LepState {
-      LepState st;
+    // state of one lepton (slots past the chunk's live ones read as zero)
+    auto load_state = [&](unsigned off) -> LepState<MIXED> {
+      LepState<MIXED> st;
       st.x = buf_ld<Real>(C.x, off * SR);
       st.y = buf_ld<Real>(C.y, off * SR);
       st.z = d3 ? buf_ld<Real>(C.z, off * SR) : Real(0);
@@ -404,189 +391,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
       }
       return st;
     };
-    // field-free drift of one lepton (outside the plane-wave pulse the Boris step reduces
-    // exactly to x += dt u / gamma, with u and tau unchanged)
-    auto drift = [&](unsigned off, const LepState& st) {
-      if (!MIXED) {
-        const double g1 = sqrt(1.0 + (st.ux * st.ux + st.uy * st.uy + st.uz * st.uz));
-        buf_st(C.x, off * SR, (Real)(st.x + dt * st.ux / g1));
-        buf_st(C.y, off * SR, (Real)(st.y + dt * st.uy / g1));
-        if (d3) buf_st(C.z, off * SR, (Real)(st.z + dt * st.uz / g1));
-        if (!isfinite(g1)) ++uacc[2];
-      } else {
-        const float g1 = sqrtf(1.0f + ((float)st.ux * (float)st.ux + (float)st.uy * (float)st.uy +
-                                       (float)st.uz * (float)st.uz));
-        float xh = (float)st.x, xlo = st.xl, yh = (float)st.y, ylo = st.yl;
-        comp_add(xh, xlo, dtf * (float)st.ux / g1);
-        comp_add(yh, ylo, dtf * (float)st.uy / g1);
-        buf_st(C.x, off * SR, (Real)xh);
-        buf_st(C.xl, off * 4u, xlo);
-        buf_st(C.y, off * SR, (Real)yh);
-        buf_st(C.yl, off * 4u, ylo);
-        if (d3) {
-          float zh = (float)st.z, zlo = st.zl;
-          comp_add(zh, zlo, dtf * (float)st.uz / g1);
-          buf_st(C.z, off * SR, (Real)zh);
-          buf_st(C.zl, off * 4u, zlo);
-        }
-        if (!isfinite(g1)) ++uacc[2];
+    auto store_position = [&](unsigned off, const LepState<MIXED>& st) {
+      buf_st(C.x, off * SR, st.x);
+      if (MIXED) buf_st(C.xl, off * 4u, st.xl);
+      buf_st(C.y, off * SR, st.y);
+      if (MIXED) buf_st(C.yl, off * 4u, st.yl);
+      if (d3) {
+        buf_st(C.z, off * SR, st.z);
+        if (MIXED) buf_st(C.zl, off * 4u, st.zl);
       }
     };
     // full step of one lepton; returns true (and its eta) when its optical depth reached zero
-    auto full = [&](unsigned off, const LepState& st, double* eta_out, double* wk, double* rd) -> bool {
-      bool pend = false;
-      if (!MIXED) {
-        double x = st.x, y = st.y, z = st.z;
-        const double ux = st.ux, uy = st.uy, uz = st.uz;
-        double tau = buf_ld<double>(C.tau, off * 8u);
-        double E[3], Bf[3];
-        field_at<FK>(sF, x, y, t, E, Bf);
-        const double g0 = sqrt(1.0 + (ux * ux + uy * uy + uz * uz));
-        const double umx = ux + hq * E[0], umy = uy + hq * E[1], umz = uz + hq * E[2];
-        const double gm = sqrt(1.0 + (umx * umx + umy * umy + umz * umz));
-        const double tx = hq / gm * Bf[0], ty = hq / gm * Bf[1], tz = hq / gm * Bf[2];
-        const double sf = 2.0 / (1.0 + (tx * tx + ty * ty + tz * tz));
-        const double sx = sf * tx, sy = sf * ty, sz = sf * tz;
-        const double upx = umx + (umy * tz - umz * ty), upy = umy + (umz * tx - umx * tz),
-                     upz = umz + (umx * ty - umy * tx);
-        const double ulx = umx + (upy * sz - upz * sy), uly = umy + (upz * sx - upx * sz),
-                     ulz = umz + (upx * sy - upy * sx);
-        const double u1x = ulx + hq * E[0], u1y = uly + hq * E[1], u1z = ulz + hq * E[2];
-        const double g1 = sqrt(1.0 + (u1x * u1x + u1y * u1y + u1z * u1z));
-        *wk = 2.0 * hq * (E[0] * (ulx + umx) + E[1] * (uly + umy) + E[2] * (ulz + umz)) / (g1 + g0);
-        x += dt * u1x / g1;
-        y += dt * u1y / g1;
-        if (d3) z += dt * u1z / g1;
+    auto full = [&](unsigned off, LepState<MIXED>& st, double* eta_out, double* wk, double* rd) -> bool {
+      st.tau = buf_ld<double>(C.tau, off * 8u);
+      const bool pend = lepton_full<FK, MIXED>(st, sF, fK, t, a.sc, a.tb, env, eta_out, wk, rd, uacc[1], uacc[2],
+                                               [&](double x0, double y0, double x1, double y1, double vz) {
         // field feedback: the current of this move onto the solver's grid (or the chunk's LDS box)
-        if constexpr (DEP) deposit_current(sF, qch * sF.p[0], dt, st.x, st.y, x, y, u1z / g1, sink);
-        double wx = u1x, wy = u1y, wz = u1z;  // stored momentum
-        if (rr) {
-          // continuous reaction (eqs. 8, 9): gamma -> max(gamma - (2/3) alpha kappa eta^2 g dt, 1)
-          // along u; the energy removed is what the stored momentum lost
-          const double ax = g1 * E[0] + (u1y * Bf[2] - u1z * Bf[1]);
-          const double ay = g1 * E[1] + (u1z * Bf[0] - u1x * Bf[2]);
-          const double az = g1 * E[2] + (u1x * Bf[1] - u1y * Bf[0]);
-          const double ue = u1x * E[0] + u1y * E[1] + u1z * E[2];
-          const double r2 = (ax * ax + ay * ay + az * az) - ue * ue;
-          const double eta = sqrt(r2 > 0.0 ? r2 : 0.0);
-          if (eta > 0.0) {
-            const double gq = rr_q ? lookup_g(sh, a.tb, eta, uacc[1]) : 1.0;
-            const double gn = fmax(g1 - a.sc.a_rr * eta * eta * gq * dt, 1.0);
-            const double um = sqrt(u1x * u1x + u1y * u1y + u1z * u1z);
-            const double sc = um > 0.0 ? sqrt((gn - 1.0) * (gn + 1.0)) / um : 0.0;
-            wx = sc * u1x;
-            wy = sc * u1y;
-            wz = sc * u1z;
-            *rd = g1 - sqrt(1.0 + (wx * wx + wy * wy + wz * wz));
-          }
-        }
-        if (emit) {
-          const double ax = g1 * E[0] + (u1y * Bf[2] - u1z * Bf[1]);
-          const double ay = g1 * E[1] + (u1z * Bf[0] - u1x * Bf[2]);
-          const double az = g1 * E[2] + (u1x * Bf[1] - u1y * Bf[0]);
-          const double ue = u1x * E[0] + u1y * E[1] + u1z * E[2];
-          const double r2 = (ax * ax + ay * ay + az * az) - ue * ue;
-          const double eta = sqrt(r2 > 0.0 ? r2 : 0.0);
-          if (eta > 0.0) {
-            const double h = lookup_h(sh, sLog, a.tb, eta, uacc[1]);
-            tau -= a.sc.a_gamma * (eta / g1) * h * dt;
-            if (tau <= 0.0) {
-              pend = true;
-              *eta_out = eta;
-            }
-          }
-        }
-        if (!isfinite(tau) || !isfinite(wx) || !isfinite(wy) || !isfinite(wz)) ++uacc[2];
-        buf_st(C.x, off * SR, (Real)(x));
-        buf_st(C.y, off * SR, (Real)(y));
-        if (d3) buf_st(C.z, off * SR, (Real)(z));
-        buf_st(C.ux, off * SR, (Real)(wx));
-        buf_st(C.uy, off * SR, (Real)(wy));
-        buf_st(C.uz, off * SR, (Real)(wz));
-        buf_st(C.tau, off * 8u, (double)(tau));
-      } else {
-        float xh = st.x, xl = st.xl, yh = st.y, yl = st.yl, zh = st.z, zl = st.zl;
-        float uxh = st.ux, uxl = st.uxl, uyh = st.uy, uyl = st.uyl, uzh = st.uz, uzl = st.uzl;
-        double tau = buf_ld<double>(C.tau, off * 8u);
-        const double ux0 = (double)uxh + uxl, uy0 = (double)uyh + uyl, uz0 = (double)uzh + uzl;
-        const double g0d = sqrt(1.0 + (ux0 * ux0 + uy0 * uy0 + uz0 * uz0));
-        float E[3], Bf[3];
-        field_at32<FK>(sF, fK, (double)xh + xl, (double)yh + yl, t, E, Bf);
-        const float hqf = (float)hq;
-        const float umx = uxh + hqf * E[0], umy = uyh + hqf * E[1], umz = uzh + hqf * E[2];
-        const float gm = sqrtf(1.0f + (umx * umx + umy * umy + umz * umz));
-        const float tx = hqf / gm * Bf[0], ty = hqf / gm * Bf[1], tz = hqf / gm * Bf[2];
-        const float sf = 2.0f / (1.0f + (tx * tx + ty * ty + tz * tz));
-        const float sx = sf * tx, sy = sf * ty, sz = sf * tz;
-        const float upx = umx + (umy * tz - umz * ty), upy = umy + (umz * tx - umx * tz),
-                    upz = umz + (umx * ty - umy * tx);
-        // rotation increment (u+ - u-) formed directly, without cancellation
-        const float rx = upy * sz - upz * sy, ry = upz * sx - upx * sz, rz = upx * sy - upy * sx;
-        comp_add(uxh, uxl, 2.0f * hqf * E[0] + rx);
-        comp_add(uyh, uyl, 2.0f * hqf * E[1] + ry);
-        comp_add(uzh, uzl, 2.0f * hqf * E[2] + rz);
-        const float g1 = sqrtf(1.0f + (uxh * uxh + uyh * uyh + uzh * uzh));
-        comp_add(xh, xl, dtf * uxh / g1);
-        comp_add(yh, yl, dtf * uyh / g1);
-        if (d3) comp_add(zh, zl, dtf * uzh / g1);
-        // field work from the stored states (FP64), so the ledger closes on what is stored
-        const double ux1 = (double)uxh + uxl, uy1 = (double)uyh + uyl, uz1 = (double)uzh + uzl;
-        const double g1d = sqrt(1.0 + (ux1 * ux1 + uy1 * uy1 + uz1 * uz1));
-        *wk = g1d - g0d;
-        if (rr) {
-          // continuous reaction with eta in FP32 (as for emission) and the energy update in
-          // FP64 on the stored momentum; the energy removed is what the stored pairs lost
-          const float ax = g1 * E[0] + (uyh * Bf[2] - uzh * Bf[1]);
-          const float ay = g1 * E[1] + (uzh * Bf[0] - uxh * Bf[2]);
-          const float az = g1 * E[2] + (uxh * Bf[1] - uyh * Bf[0]);
-          const float ue = uxh * E[0] + uyh * E[1] + uzh * E[2];
-          const float r2 = (ax * ax + ay * ay + az * az) - ue * ue;
-          const double eta = (double)sqrtf(r2 > 0.0f ? r2 : 0.0f);
-          if (eta > 0.0) {
-            const double gq = rr_q ? lookup_g(sh, a.tb, eta, uacc[1]) : 1.0;
-            const double gn = fmax(g1d - a.sc.a_rr * eta * eta * gq * dt, 1.0);
-            const double um = sqrt(ux1 * ux1 + uy1 * uy1 + uz1 * uz1);
-            const double sc = um > 0.0 ? sqrt((gn - 1.0) * (gn + 1.0)) / um : 0.0;
-            split_double(sc * ux1, uxh, uxl);
-            split_double(sc * uy1, uyh, uyl);
-            split_double(sc * uz1, uzh, uzl);
-            const double vx = (double)uxh + uxl, vy = (double)uyh + uyl, vz = (double)uzh + uzl;
-            *rd = g1d - sqrt(1.0 + (vx * vx + vy * vy + vz * vz));
-          }
-        }
-        if (emit) {
-          const float ax = g1 * E[0] + (uyh * Bf[2] - uzh * Bf[1]);
-          const float ay = g1 * E[1] + (uzh * Bf[0] - uxh * Bf[2]);
-          const float az = g1 * E[2] + (uxh * Bf[1] - uyh * Bf[0]);
-          const float ue = uxh * E[0] + uyh * E[1] + uzh * E[2];
-          const float r2 = (ax * ax + ay * ay + az * az) - ue * ue;
-          const float eta = sqrtf(r2 > 0.0f ? r2 : 0.0f);
-          if (eta > 0.0f) {
-            const float h = lookup32(sh32, a.tb.n_eta, a.tb.le0, a.tb.idle, eta, uacc[1], false);
-            tau -= agdt * ((double)eta / (double)g1) * (double)h;  // FP32 look-up, FP64 decrement
-            if (tau <= 0.0) {
-              pend = true;
-              *eta_out = (double)eta;
-            }
-          }
-        }
-        if (!isfinite(tau) || !isfinite(uxh) || !isfinite(uyh) || !isfinite(uzh)) ++uacc[2];
-        buf_st(C.x, off * SR, (Real)(xh));
-        buf_st(C.xl, off * 4u, (float)(xl));
-        buf_st(C.y, off * SR, (Real)(yh));
-        buf_st(C.yl, off * 4u, (float)(yl));
-        if (d3) {
-          buf_st(C.z, off * SR, (Real)(zh));
-          buf_st(C.zl, off * 4u, (float)(zl));
-        }
-        buf_st(C.ux, off * SR, (Real)(uxh));
-        buf_st(C.uxl, off * 4u, (float)(uxl));
-        buf_st(C.uy, off * SR, (Real)(uyh));
-        buf_st(C.uyl, off * 4u, (float)(uyl));
-        buf_st(C.uz, off * SR, (Real)(uzh));
-        buf_st(C.uzl, off * 4u, (float)(uzl));
-        buf_st(C.tau, off * 8u, (double)(tau));
-      }
+        if constexpr (DEP) deposit_current(sF, qch * sF.p[0], dt, x0, y0, x1, y1, vz, sink);
+      });
+      store_position(off, st);
+      buf_st(C.ux, off * SR, st.ux);
+      if (MIXED) buf_st(C.uxl, off * 4u, st.uxl);
+      buf_st(C.uy, off * SR, st.uy);
+      if (MIXED) buf_st(C.uyl, off * 4u, st.uyl);
+      buf_st(C.uz, off * SR, st.uz);
+      if (MIXED) buf_st(C.uzl, off * 4u, st.uzl);
+      buf_st(C.tau, off * 8u, st.tau);
       return pend;
     };
     auto enqueue = [&](unsigned off, bool pend, double eta) {
@@ -607,26 +437,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
     };
 
     if (FK == QED_FIELD_LP_PULSE) {
-      // outside the pulse (an FP32 test of the phase with a margin far above its rounding error)
-      // the drift, inside it the full step
-      const float tpf = (float)t - tpf0;
-      const float mt = fabsf((float)t) + fabsf(tpf0);
+      // outside the pulse the drift, inside it the full step
 #pragma unroll 1
       for (int j = 0; j < PPT; ++j) {
         const unsigned off = threadIdx.x + j * B;
         bool pend = false, in = false;
         double eta = 0.0, wk = 0.0, rd = 0.0;
         if ((int64_t)off < rem) {
-          const LepState st = load_state(off);
-          const float xf = (float)st.x;
-          const float psif = tpf - xf;
-          const float m = 1e-5f * (mt + fabsf(xf)) + 1e-30f;
-          in = psif >= -m && psif <= psif_max + m;
+          LepState<MIXED> st = load_state(off);
+          in = near_pulse(t, tpf0, psif_max, (float)st.x);
           if (in) {
             ++uacc[0];
             pend = full(off, st, &eta, &wk, &rd);
           } else {
-            drift(off, st);
+            const DriftMove<MIXED> mv = drift_move(st, env);
+            drift_apply(st, mv, d3);
+            store_position(off, st);
+            if (mv.bad) ++uacc[2];
           }
         }
         if (__ballot(in)) {  // wave-uniform: the energy sums of the wave's group of 64 slots
@@ -644,7 +471,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
         const bool in = (int64_t)off < rem;
         if (in) {
           ++uacc[0];
-          pend = full(off, load_state(off), &eta, &wk, &rd);
+          LepState<MIXED> st = load_state(off);
+          pend = full(off, st, &eta, &wk, &rd);
         }
         if (__ballot(in)) {
           fix_group_add(wk, fx_work);
@@ -771,67 +599,46 @@ __global__ __launch_bounds__(256) void k_emit_events(StepArgs a) {
     const bool d3 = I.dims == 3;
     const int64_t moff = a.acc[ii].mover_off, lmoff = a.acc[ii].lmask_off;
     int64_t* const bcount = a.inst[bkey].s[2].count_dev;
-    bool child = false;
-    double defect = 0.0, cx = 0, cy = 0, cz = 0, ckx = 0, cky = 0, ckz = 0, ctau = 0;
-    uint64_t cuid = 0;
+    Emission em;
+    em.child = false;
+    em.kx = em.ky = em.kz = em.defect = 0.0;
+    double cx = 0.0, cy = 0.0, cz = 0.0;
     unsigned n_null = 0;
     if (want) {
       const uint64_t uid = S.uid_dev[k];
       gptr<Real> UX = as_global((Real*)S.ux_dev), UY = as_global((Real*)S.uy_dev), UZ = as_global((Real*)S.uz_dev);
-      double ux1, uy1, uz1;
+      LepState<MIXED> st{};
+      st.ux = UX[k];
+      st.uy = UY[k];
+      st.uz = UZ[k];
       if (MIXED) {
-        ux1 = (double)UX[k] + S.ux_lo_dev[k];
-        uy1 = (double)UY[k] + S.uy_lo_dev[k];
-        uz1 = (double)UZ[k] + S.uz_lo_dev[k];
+        st.uxl = S.ux_lo_dev[k];
+        st.uyl = S.uy_lo_dev[k];
+        st.uzl = S.uz_lo_dev[k];
         cx = (double)((const float*)S.x_dev)[k] + S.x_lo_dev[k];
         cy = (double)((const float*)S.y_dev)[k] + S.y_lo_dev[k];
         cz = d3 ? (double)((const float*)S.z_dev)[k] + S.z_lo_dev[k] : 0.0;
       } else {
-        ux1 = UX[k];
-        uy1 = UY[k];
-        uz1 = UZ[k];
         cx = ((const double*)S.x_dev)[k];
         cy = ((const double*)S.y_dev)[k];
         cz = d3 ? ((const double*)S.z_dev)[k] : 0.0;
       }
-      uint64_t r[4];
-      philox4x64_10(uid, (uint64_t)step, KIND_EMIT, 0, seed, key_inst, r);
-      const double g1 = sqrt(1.0 + (ux1 * ux1 + uy1 * uy1 + uz1 * uz1));
-      double chi;
-      if (sample_chi(a.tb, ev.eta, unit_open(r[0]), &chi)) {
-        const double xi = 2.0 * chi / ev.eta;
-        double ux, uy, uz;
+      em = emit_photon<MIXED>(a.tb, st, ev.eta, uid, (uint64_t)step, seed, key_inst);
+      if (em.child) {
+        UX[k] = st.ux;
+        UY[k] = st.uy;
+        UZ[k] = st.uz;
         if (MIXED) {
-          // the emitter loses exactly the stored (FP32) photon momentum
-          ckx = (float)(xi * ux1);
-          cky = (float)(xi * uy1);
-          ckz = (float)(xi * uz1);
-          float h, l;
-          split_double(ux1 - ckx, h, l); UX[k] = h; S.ux_lo_dev[k] = l; ux = (double)h + l;
-          split_double(uy1 - cky, h, l); UY[k] = h; S.uy_lo_dev[k] = l; uy = (double)h + l;
-          split_double(uz1 - ckz, h, l); UZ[k] = h; S.uz_lo_dev[k] = l; uz = (double)h + l;
-        } else {
-          ckx = xi * ux1;
-          cky = xi * uy1;
-          ckz = xi * uz1;
-          ux = ux1 - ckx;
-          uy = uy1 - cky;
-          uz = uz1 - ckz;
-          UX[k] = ux;
-          UY[k] = uy;
-          UZ[k] = uz;
+          S.ux_lo_dev[k] = st.uxl;
+          S.uy_lo_dev[k] = st.uyl;
+          S.uz_lo_dev[k] = st.uzl;
         }
-        const double g2 = sqrt(1.0 + (ux * ux + uy * uy + uz * uz));
-        const double eps = sqrt(ckx * ckx + cky * cky + ckz * ckz);
-        defect = g2 + eps - g1;
-        child = true;
-        ctau = optical_depth(r[3]);
-        cuid = r[2];
       } else {
         n_null = 1;
       }
-      S.tau_dev[k] = optical_depth(r[1]);
+      S.tau_dev[k] = st.tau;
     }
+    const bool child = em.child;
     const long long slot = uni ? block_reserve(child, bcount, s_wave, &s_base)
                                : wave_reserve_grouped(child, ii, G.count_dev);
     double dropped_e = 0.0;
@@ -839,39 +646,12 @@ __global__ __launch_bounds__(256) void k_emit_events(StepArgs a) {
     uint64_t* lword = nullptr;  // the live mask word of a new photon that can still create a pair
     if (child) {
       if (slot < G.capacity) {
-        if (MIXED) {
-          ((float*)G.x_dev)[slot] = (float)cx;
-          ((float*)G.y_dev)[slot] = (float)cy;
-          if (d3) ((float*)G.z_dev)[slot] = (float)cz;
-          ((float*)G.ux_dev)[slot] = (float)ckx;
-          ((float*)G.uy_dev)[slot] = (float)cky;
-          ((float*)G.uz_dev)[slot] = (float)ckz;
-        } else {
-          ((double*)G.x_dev)[slot] = cx;
-          ((double*)G.y_dev)[slot] = cy;
-          if (d3) ((double*)G.z_dev)[slot] = cz;
-          ((double*)G.ux_dev)[slot] = ckx;
-          ((double*)G.uy_dev)[slot] = cky;
-          ((double*)G.uz_dev)[slot] = ckz;
-        }
-        G.tau_dev[slot] = ctau;
-        G.uid_dev[slot] = cuid;
-        G.birth_step_dev[slot] = (int32_t)(step + 1);
-        // the steps in which the new photon can create a pair, from its stored state
-        const double sx = MIXED ? (double)(float)cx : cx;
-        const double skx = MIXED ? (double)(float)ckx : ckx, sky = MIXED ? (double)(float)cky : cky,
-                     skz = MIXED ? (double)(float)ckz : ckz;
-        const double sy = MIXED ? (double)(float)cy : cy;
-        const int64_t pk = moff + slot;
-        const uint32_t wn = pack_window(photon_window(F, pair_eps_min(F, a.tb.cp_min), a.tb.cp_min, a.sc.t0, a.sc.dt,
-                                                      skx, sky, skz, sx, (int32_t)(step + 1)));
-        a.win[pk] = wn;
+        const uint32_t wn = store_photon<FK, MIXED>(G, slot, moff + slot, d3, cx, cy, cz, em, (int32_t)(step + 1), F,
+                                                    a.tb.cp_min, a.sc, a.win, a.rec);
         if (!window_over(wn, step + 1)) lword = a.lmask + lmoff + slot / kWinGroup;
-        make_photon_rec<MIXED, FK>(((PhotonRecT<MIXED, FK>*)a.rec)[pk], F, a.sc.t0, a.sc.dt, skx, sky, skz, sx, sy,
-                                   (int32_t)(step + 1));
       } else {
         n_drop = 1;
-        dropped_e = sqrt(ckx * ckx + cky * cky + ckz * ckz);
+        dropped_e = sqrt(em.kx * em.kx + em.ky * em.ky + em.kz * em.kz);
       }
     }
     // the new photons' live bits (the words' other bits belong to other slots, some of them set
@@ -883,11 +663,11 @@ __global__ __launch_bounds__(256) void k_emit_events(StepArgs a) {
         bst.inst = bkey;
       }
       long long ld[4], le[4];
-      fix_split(defect, ld);
+      fix_split(em.defect, ld);
       fix_split(dropped_e, le);
       bst.add(ld, le, child ? 1u : 0u, n_null, n_drop, s_ll, s_u);
     } else {
-      add_event_stats(0, want, ii, a.acc, defect, dropped_e, child ? 1u : 0u, n_null, n_drop);
+      add_event_stats(0, want, ii, a.acc, em.defect, dropped_e, child ? 1u : 0u, n_null, n_drop);
     }
   }
   if (threadIdx.x == 0) bst.flush(0, a.acc);
@@ -1009,12 +789,12 @@ __global__ __launch_bounds__(256) void k_photon(StepArgs a) {
     const bufres rtau = make_buf(TAU + k0, nlive * 8u), rwin = make_buf(WIN + k0, nlive * 4u);
     const bufres rrec = make_buf(REC + k0, nlive * (uint32_t)sizeof(Rec));
     // the optical-depth step of a photon with pair rate T > 0; true when its depth reached zero
-    auto decrement = [&](unsigned off, double T, double dtau, double tau) -> bool {
+    auto decrement = [&](unsigned off, const PairRate& r, double tau) -> bool {
       bool pend = false;
-      if (T > 0.0) {
+      if (r.T > 0.0) {
         if (!(tau < 0.0)) {  // tau < 0: converted in an earlier step
           ++uacc[0];
-          tau -= dtau;
+          tau -= r.dtau;
           if (tau <= 0.0) {
             pend = true;
             tau = fmax(tau, kTauPendingMin);
@@ -1024,63 +804,6 @@ __global__ __launch_bounds__(256) void k_photon(StepArgs a) {
         }
       }
       return pend;
-    };
-    // in-field part for one photon; true when its optical depth reached zero
-    auto infield = [&](unsigned off, Real kx, Real ky, Real kz, Real xb, Real yb, int32_t bs, double tau) -> bool {
-      const Real eps = sqrt(kx * kx + ky * ky + kz * kz);
-      const Real inv = (Real)1 / eps;
-      const Real nx = kx * inv, ny = ky * inv, nz = kz * inv;
-      double x = 0.0, y = 0.0;
-      if (NEED_X) {
-        const double age = (double)(step - (int64_t)bs) * dt;
-        x = (double)xb + age * nx;
-        if (NEED_Y) y = (double)yb + age * ny;
-      }
-      double chi, T;
-      if (MIXED) {
-        float E[3], Bf[3];
-        field_at32<FK>(sF, fK, x, y, t, E, Bf);
-        const float ax = E[0] + (ny * Bf[2] - nz * Bf[1]);
-        const float ay = E[1] + (nz * Bf[0] - nx * Bf[2]);
-        const float az = E[2] + (nx * Bf[1] - ny * Bf[0]);
-        const float ne = nx * E[0] + ny * E[1] + nz * E[2];
-        const float r2 = (ax * ax + ay * ay + az * az) - ne * ne;
-        const float chif = 0.5f * (float)eps * sqrtf(r2 > 0.0f ? r2 : 0.0f);
-        chi = chif;
-        T = lookup32(sT32, a.tb.n_cp, a.tb.lc0, a.tb.idlc, chif, uacc[1], true);
-      } else {
-        double E[3], Bf[3];
-        field_at<FK, false>(sF, x, y, t, E, Bf, &fK);
-        const double ax = E[0] + (ny * Bf[2] - nz * Bf[1]);
-        const double ay = E[1] + (nz * Bf[0] - nx * Bf[2]);
-        const double az = E[2] + (nx * Bf[1] - ny * Bf[0]);
-        const double ne = nx * E[0] + ny * E[1] + nz * E[2];
-        const double r2 = (ax * ax + ay * ay + az * az) - ne * ne;
-        chi = 0.5 * (double)eps * sqrt(r2 > 0.0 ? r2 : 0.0);
-        T = lookup_T(sT, sLog, a.tb, chi, uacc[1]);
-      }
-      return decrement(off, T, rate * chi * T * (double)inv, tau);  // FP64 (chi, T, 1/eps FP32 if mixed)
-    };
-    // the plane-wave pulse from the photon's record: psi(n) = A + n S, chi = c |e(psi)|, and the
-    // decrement a_pair |e| T(chi) S / 2 (PhotonRecPW)
-    auto infield_pw = [&](unsigned off, double A, double S, double cr, double tau) -> bool {
-      const double psi = A + (double)step * S;
-      double T = 0.0, ae = 0.0;
-      if (psi >= 0.0 && psi <= sF.p[1]) {
-        if (MIXED) {
-          float sn, cs, d;
-          fast_sincosf((float)(psi * fK.pi_over_len), &sn, &d);
-          fast_sincosf(reduce_phase(psi + sF.p[3]), &d, &cs);
-          const float e = fabsf((float)sF.p[0] * sn * sn * cs);
-          ae = e;
-          T = lookup32(sT32, a.tb.n_cp, a.tb.lc0, a.tb.idlc, (float)cr * e, uacc[1], true);
-        } else {
-          const double sn = fast_sin(psi * fK.pi_over_len), cs = fast_cos(psi + sF.p[3]);
-          ae = fabs(sF.p[0] * sn * sn * cs);
-          T = lookup_T(sT, sLog, a.tb, cr * ae, uacc[1]);
-        }
-      }
-      return decrement(off, T, 0.5 * a.sc.a_pair * ae * T * S, tau);
     };
     auto enqueue = [&](unsigned off, bool pend) {
       const long long slot = wave_reserve(pend, &a.q.ctl->count);
@@ -1157,17 +880,24 @@ __global__ __launch_bounds__(256) void k_photon(StepArgs a) {
       // one photon inside its window, from the dwords of its record and its optical depth
       auto eval = [&](unsigned off, const uint32_t* w, double tau) -> bool {
         auto dbl = [&](int i) { return __hiloint2double((int)w[i + 1], (int)w[i]); };
+        PairRate r;
         if constexpr (FK == QED_FIELD_LP_PULSE) {
-          if (MIXED) return infield_pw(off, dbl(0), (double)__uint_as_float(w[2]), (double)__uint_as_float(w[3]), tau);
-          else return infield_pw(off, dbl(0), dbl(2), dbl(4), tau);
+          if (MIXED)
+            r = pair_rate_pw<MIXED>(sF, fK, a.tb, sT, sT32, sLog, a.sc.a_pair, step, dbl(0),
+                                    (double)__uint_as_float(w[2]), (double)__uint_as_float(w[3]), uacc[1]);
+          else
+            r = pair_rate_pw<MIXED>(sF, fK, a.tb, sT, sT32, sLog, a.sc.a_pair, step, dbl(0), dbl(2), dbl(4), uacc[1]);
         } else if (MIXED) {
-          return infield(off, (Real)__uint_as_float(w[0]), (Real)__uint_as_float(w[1]), (Real)__uint_as_float(w[2]),
-                         NEED_X ? (Real)__uint_as_float(w[3]) : Real(0), NEED_Y ? (Real)__uint_as_float(w[4]) : Real(0),
-                         NEED_X ? (int32_t)w[5] : 0, tau);
+          r = pair_rate<FK, MIXED>(sF, fK, a.tb, sT, sT32, sLog, rate, step, t, dt, (Real)__uint_as_float(w[0]),
+                                   (Real)__uint_as_float(w[1]), (Real)__uint_as_float(w[2]),
+                                   NEED_X ? (Real)__uint_as_float(w[3]) : Real(0),
+                                   NEED_Y ? (Real)__uint_as_float(w[4]) : Real(0), NEED_X ? (int32_t)w[5] : 0, uacc[1]);
         } else {
-          return infield(off, (Real)dbl(0), (Real)dbl(2), (Real)dbl(4), NEED_X ? (Real)dbl(6) : Real(0),
-                         NEED_Y ? (Real)dbl(8) : Real(0), NEED_X ? (int32_t)w[10] : 0, tau);
+          r = pair_rate<FK, MIXED>(sF, fK, a.tb, sT, sT32, sLog, rate, step, t, dt, (Real)dbl(0), (Real)dbl(2),
+                                   (Real)dbl(4), NEED_X ? (Real)dbl(6) : Real(0), NEED_Y ? (Real)dbl(8) : Real(0),
+                                   NEED_X ? (int32_t)w[10] : 0, uacc[1]);
         }
+        return decrement(off, r, tau);
       };
       // phase 2: the photons inside their windows, in place
 #pragma unroll
@@ -1180,130 +910,6 @@ __global__ __launch_bounds__(256) void k_photon(StepArgs a) {
     }
   }
   if (cur >= 0) flush(cur);
-}
-
-template <bool MIXED>
-__device__ __forceinline__ void write_lepton(const qed_species& S, long long slot, double x, double y, double z,
-                                             double ux, double uy, double uz, double tau, uint64_t uid, bool d3) {
-  if (MIXED) {
-    float h, l;
-    split_double(x, h, l); ((float*)S.x_dev)[slot] = h; S.x_lo_dev[slot] = l;
-    split_double(y, h, l); ((float*)S.y_dev)[slot] = h; S.y_lo_dev[slot] = l;
-    if (d3) { split_double(z, h, l); ((float*)S.z_dev)[slot] = h; S.z_lo_dev[slot] = l; }
-    split_double(ux, h, l); ((float*)S.ux_dev)[slot] = h; S.ux_lo_dev[slot] = l;
-    split_double(uy, h, l); ((float*)S.uy_dev)[slot] = h; S.uy_lo_dev[slot] = l;
-    split_double(uz, h, l); ((float*)S.uz_dev)[slot] = h; S.uz_lo_dev[slot] = l;
-  } else {
-    ((double*)S.x_dev)[slot] = x;
-    ((double*)S.y_dev)[slot] = y;
-    if (d3) ((double*)S.z_dev)[slot] = z;
-    ((double*)S.ux_dev)[slot] = ux;
-    ((double*)S.uy_dev)[slot] = uy;
-    ((double*)S.uz_dev)[slot] = uz;
-  }
-  S.tau_dev[slot] = tau;
-  S.uid_dev[slot] = uid;
-}
-
-// Pair creation by photon k of instance ii (when `want`): chi at the photon's position (FP64
-// form: correctly rounded field), energy split f from the P_f table, electron with (1 - f) k
-// and positron with f k at the position after the step, fresh optical depths, photon removed.
-// Every lane of the wave calls this (the appends are wave-aggregated).
-template <int FK, bool MIXED>
-__device__ __forceinline__ void pair_event(const StepArgs& a, int ii, int64_t k, bool want, int64_t step, double t) {
-  using Real = typename std::conditional<MIXED, float, double>::type;
-  const double dt = a.sc.dt;
-  const qed_instance& I = a.inst[ii];
-  const qed_species& S = I.s[2];
-  const bool d3 = I.dims == 3;
-  // the children's species and the photon's record offset, read before the first store (which the
-  // compiler cannot tell apart from them), so that the loads share a memory round trip
-  const qed_species Se = I.s[0], Sp = I.s[1];
-  const int64_t moff = a.acc[ii].mover_off;
-  double px = 0, py = 0, pz = 0, etau = 0, ptau = 0, ex = 0, ey = 0, ez = 0, pkx = 0, pky = 0, pkz = 0;
-  double defect = 0.0, dropped_e = 0.0;
-  unsigned n_drop = 0;
-  uint64_t euid = 0, puid = 0;
-  if (want) {
-    const Real kxr = ((const Real*)S.ux_dev)[k], kyr = ((const Real*)S.uy_dev)[k], kzr = ((const Real*)S.uz_dev)[k];
-    const Real xbr = ((const Real*)S.x_dev)[k], ybr = ((const Real*)S.y_dev)[k];
-    const int32_t bs = S.birth_step_dev[k];
-    const uint64_t uid = S.uid_dev[k];
-    const Real eps = sqrt(kxr * kxr + kyr * kyr + kzr * kzr);
-    const Real nx = kxr / eps, ny = kyr / eps, nz = kzr / eps;
-    const double age = (double)(step - (int64_t)bs) * dt;
-    const double x = (double)xbr + age * nx;
-    const double y = (double)ybr + age * ny;
-    double chi;
-    if (MIXED) {
-      float E[3], Bf[3];
-      field_at32<FK>(I.field, field_k(I.field), x, y, t, E, Bf);
-      const float ax = E[0] + (ny * Bf[2] - nz * Bf[1]);
-      const float ay = E[1] + (nz * Bf[0] - nx * Bf[2]);
-      const float az = E[2] + (nx * Bf[1] - ny * Bf[0]);
-      const float ne = nx * E[0] + ny * E[1] + nz * E[2];
-      const float r2 = (ax * ax + ay * ay + az * az) - ne * ne;
-      chi = 0.5f * (float)eps * sqrtf(r2 > 0.0f ? r2 : 0.0f);
-    } else {
-      double E[3], Bf[3];
-      field_at<FK, true>(I.field, x, y, t, E, Bf);
-      const double ax = E[0] + (ny * Bf[2] - nz * Bf[1]);
-      const double ay = E[1] + (nz * Bf[0] - nx * Bf[2]);
-      const double az = E[2] + (nx * Bf[1] - ny * Bf[0]);
-      const double ne = nx * E[0] + ny * E[1] + nz * E[2];
-      const double r2 = (ax * ax + ay * ay + az * az) - ne * ne;
-      chi = 0.5 * (double)eps * sqrt(r2 > 0.0 ? r2 : 0.0);
-    }
-    uint64_t r0[4], r1[4];
-    philox4x64_10(uid, (uint64_t)step, KIND_PAIR, 0, I.seed, I.key_instance, r0);
-    philox4x64_10(uid, (uint64_t)step, KIND_PAIR, 1, I.seed, I.key_instance, r1);
-    const double f = sample_f(a.tb, chi, unit_open(r0[0]));
-    const double kxd = kxr, kyd = kyr, kzd = kzr;
-    pkx = f * kxd;
-    pky = f * kyd;
-    pkz = f * kzd;
-    if (MIXED) {
-      ex = kxd - pkx;
-      ey = kyd - pky;
-      ez = kzd - pkz;
-    } else {
-      ex = (1.0 - f) * kxd;
-      ey = (1.0 - f) * kyd;
-      ez = (1.0 - f) * kzd;
-    }
-    const double gp = sqrt(1.0 + (pkx * pkx + pky * pky + pkz * pkz));
-    const double ge = sqrt(1.0 + (ex * ex + ey * ey + ez * ez));
-    const double epsd = MIXED ? sqrt(kxd * kxd + kyd * kyd + kzd * kzd) : (double)eps;
-    const double age1 = age + dt;
-    px = (double)xbr + age1 * nx;
-    py = (double)ybr + age1 * ny;
-    pz = d3 ? (double)((const Real*)S.z_dev)[k] + age1 * nz : 0.0;
-    euid = r0[1];
-    puid = r0[2];
-    etau = optical_depth(r0[3]);
-    ptau = optical_depth(r1[0]);
-    S.tau_dev[k] = kTauGone;
-    a.win[moff + k] = kWinEmpty;
-    defect = gp + ge - epsd;
-  }
-  // append electron and positron, one atomic per wave, instance and species
-  long long se, spo;
-  wave_reserve2_grouped(want, ii, Se.count_dev, Sp.count_dev, &se, &spo);
-  if (want) {
-    if (se < Se.capacity) {
-      write_lepton<MIXED>(Se, se, px, py, pz, ex, ey, ez, etau, euid, d3);
-    } else {
-      ++n_drop;
-      dropped_e += sqrt(1.0 + (ex * ex + ey * ey + ez * ez));
-    }
-    if (spo < Sp.capacity) {
-      write_lepton<MIXED>(Sp, spo, px, py, pz, pkx, pky, pkz, ptau, puid, d3);
-    } else {
-      ++n_drop;
-      dropped_e += sqrt(1.0 + (pkx * pkx + pky * pky + pkz * pkz));
-    }
-  }
-  add_event_stats(1, want, ii, a.acc, defect, dropped_e, want ? 1u : 0u, 0u, n_drop);
 }
 
 // Event pass: the queued photons, or, when the queue overflowed, every photon whose optical
@@ -1833,35 +1439,9 @@ __global__ __launch_bounds__(256) void k_photon_windows(const qed_instance* __re
 // host launchers
 // ---------------------------------------------------------------------------
 
-// Reciprocal factorials 1/n! as double-doubles (Dekker splits; dd / integer division with one
-// exact remainder), uploaded once per device for the correctly rounded device math.
 hipError_t init_crmath() {
   static unsigned long long done = 0;  // one bit per device
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 64 && (done >> dev) & 1ull) return hipSuccess;
-  dd f[30];
-  f[0] = {1.0, 0.0};
-  for (int n = 1; n < 30; ++n) {
-    const double q1 = f[n - 1].hi / n;
-    const double p = q1 * n, pe = std::fma(q1, (double)n, -p);
-    const double rem = ((f[n - 1].hi - p) - pe) + f[n - 1].lo;
-    const double q2 = rem / n;
-    const double s = q1 + q2;
-    f[n] = {s, q2 - (s - q1)};
-  }
-  e = hipMemcpyToSymbol(HIP_SYMBOL(c_inv_fact), f, sizeof(f));
-  // log table of fast_log: c_j = 1 / (centre of the j-th sub-interval of [1/2, 1)), L_j = -log c_j
-  double lt[2 * kLogTab];
-  for (int j = 0; j < kLogTab; ++j) {
-    const double c = 1.0 / (0.5 + (j + 0.5) / (2.0 * kLogTab));
-    lt[2 * j] = c;
-    lt[2 * j + 1] = -std::log(c);
-  }
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_logtab), lt, sizeof(lt));
-  if (e == hipSuccess && dev < 64) done |= 1ull << dev;
-  return e;
+  return upload_crmath(&done);
 }
 template <int FK>
 static void launch_lepton_fk(const StepArgs& a, dim3 grid, dim3 block, size_t shm, hipStream_t s, bool mixed) {

@@ -201,9 +201,12 @@ class Run:
         capi.qed_set_event_queue(self.ws, capacity)
 
     def step(self, n: int = 1):
-        for _ in range(n):
+        """n steps: one by qed_step, more by qed_run (the same results)."""
+        if n == 1:
             capi.qed_step(self.tables.handle, self.ws, self.params, self._s())
-        self.step_index += n
+        elif n > 1:
+            capi.qed_run(self.tables.handle, self.ws, self.params, n, 0, self._s())
+        self.step_index += max(n, 0)
 
     def run(self, n: int, graph_steps: int = 0):
         capi.qed_run(self.tables.handle, self.ws, self.params, n, graph_steps, self._s())

@@ -34,6 +34,36 @@ static hipError_t upload_crmath(unsigned long long* done) {
     lt[2 * j + 1] = -std::log(c);
   }
   if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_logtab), lt, sizeof(lt));
+  // sine table of the correctly rounded sin and cos: j pi/256, its sine and cosine as double-doubles
+  // (relative error below 2^-100) by Taylor series in the same arithmetic
+  auto two_sum = [](double a, double b) -> dd {
+    const double s = a + b, bb = s - a;
+    return {s, (a - (s - bb)) + (b - bb)};
+  };
+  auto fast = [](double a, double b) -> dd { return {a + b, b - ((a + b) - a)}; };
+  auto add = [&](dd a, dd b) {
+    const dd s = two_sum(a.hi, b.hi), t = two_sum(a.lo, b.lo);
+    const dd u = fast(s.hi, s.lo + t.hi);
+    return fast(u.hi, u.lo + t.lo);
+  };
+  auto mul = [&](dd a, dd b) {
+    const double p = a.hi * b.hi;
+    return fast(p, std::fma(a.hi, b.hi, -p) + (a.hi * b.lo + a.lo * b.hi));
+  };
+  double sc[kSinCosTab * kSinCosWords];
+  const dd unit = {0x1.921fb54442d18p-7, 0x1.1a62633145c07p-61};  // pi / 256
+  for (int j = 0; j < kSinCosTab; ++j) {
+    const dd x = mul(unit, dd{(double)j, 0.0}), z = mul(x, x), m = {-z.hi, -z.lo};
+    dd ps = f[29], pc = f[28];
+    for (int n = 13; n >= 0; --n) {
+      ps = add(mul(ps, m), f[2 * n + 1]);
+      pc = add(mul(pc, m), f[2 * n]);
+    }
+    ps = mul(ps, x);
+    const double row[kSinCosWords] = {x.hi, x.lo, ps.hi, ps.lo, pc.hi, pc.lo};
+    for (int q = 0; q < kSinCosWords; ++q) sc[kSinCosWords * j + q] = row[q];
+  }
+  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_sctab), sc, sizeof(sc));
   if (e == hipSuccess && dev < 64) *done |= 1ull << dev;
   return e;
 }

@@ -63,7 +63,7 @@ __device__ __forceinline__ dd dd_mul_d(dd a, double b) {
 }
 
 // 1/n!, n = 0..29, as double-double; filled by the host (qed_crinit.h) in every source file whose
-// kernels use it
+// kernels use it, as is the sine table below
 static __constant__ dd c_inv_fact[30];
 
 constexpr double kLn2A = 0x1.62e42fefa3800p-1;   // ln 2 = A + B + C, A with 42 significant bits
@@ -166,14 +166,10 @@ __device__ __noinline__ double cr_sinq_dd(double x, int qs) {
 }
 
 // ---------------------------------------------------------------------------
-// Fast path of the same correctly rounded sin and cos (Ziv's rounding test).  The reduced
-// argument r = rh + rl is a double-double as above; sin rh and cos rh come from their Taylor
-// series with the terms up to r^7 (sin) and r^6 (cos) in double-double and the rest, a tail
-// below 3e-6 of the result, in double, truncated past r^19 and r^20 (remainders below 2^-72).
-// rl enters through rl cos rh and -rl sin rh (second order below 2^-100).  The unrounded
-// result is thus within 2^-68 of the exact value (relative).  It is returned when every value
-// within kZivEps of it rounds to the same double, i.e. when that double is the correctly rounded
-// result; otherwise (probability ~2^-12 per call) the full double-double series above decides.
+// Fast path of the same correctly rounded sin and cos (Ziv's rounding test): an unrounded result
+// well within kZivEps of the exact value (relative) is returned when every value within kZivEps of it
+// rounds to the same double, i.e. when that double is the correctly rounded result; otherwise
+// (probability ~2^-12 per call) the full double-double series above decides.
 // ---------------------------------------------------------------------------
 constexpr double kZivEps = 0x1p-66;
 
@@ -181,75 +177,10 @@ constexpr double kZivEps = 0x1p-66;
 namespace crc {
 constexpr double i8 = 1.0 / 40320.0, i9 = 1.0 / 362880.0, i10 = 1.0 / 3628800.0, i11 = 1.0 / 39916800.0,
                  i12 = 1.0 / 479001600.0, i13 = 1.0 / 6227020800.0, i14 = 1.0 / 87178291200.0,
-                 i15 = 1.0 / 1307674368000.0, i16 = 1.0 / 20922789888000.0, i17 = 1.0 / 355687428096000.0,
-                 i18 = 1.0 / 6402373705728000.0, i19 = 1.0 / 121645100408832000.0,
-                 i20 = 1.0 / 2432902008176640000.0;
+                 i15 = 1.0 / 1307674368000.0, i16 = 1.0 / 20922789888000.0, i17 = 1.0 / 355687428096000.0;
 }  // namespace crc
 
 __device__ __forceinline__ dd dd_neg(dd a) { return {-a.hi, -a.lo}; }
-
-// sin rh as a double-double (z = rh^2 exact)
-__device__ __forceinline__ dd sin_series_dd(double rh, dd z) {
-  using namespace crc;
-  const double zh = z.hi;
-  double t = -i19;
-  t = t * zh + i17;
-  t = t * zh - i15;
-  t = t * zh + i13;
-  t = t * zh - i11;
-  t = t * zh + i9;                                          // r^9 on: 1/9! - z/11! + ...
-  dd m = dd_add(dd_neg(c_inv_fact[7]), dd_two_prod(zh, t));  // -1/7! + z T
-  m = dd_add(dd_mul(z, m), c_inv_fact[5]);
-  m = dd_add(dd_mul(z, m), dd_neg(c_inv_fact[3]));          // S(z) = -1/3! + z/5! - ...
-  const dd q = dd_mul(z, m);                                // sin rh = rh (1 + z S)
-  return dd_add(dd{rh, 0.0}, dd_mul_d(q, rh));
-}
-
-// cos rh as a double-double
-__device__ __forceinline__ dd cos_series_dd(dd z) {
-  using namespace crc;
-  const double zh = z.hi;
-  double u = i20;
-  u = u * zh - i18;
-  u = u * zh + i16;
-  u = u * zh - i14;
-  u = u * zh + i12;
-  u = u * zh - i10;
-  u = u * zh + i8;                                          // r^8 on: 1/8! - z/10! + ...
-  dd m = dd_add(dd_neg(c_inv_fact[6]), dd_two_prod(zh, u));  // -1/6! + z U
-  m = dd_add(dd_mul(z, m), c_inv_fact[4]);
-  m = dd_add(dd_mul(z, m), dd{-0.5, 0.0});
-  return dd_add(dd{1.0, 0.0}, dd_mul(z, m));               // 1 - z/2 + z^2/4! - ...
-}
-
-// sin rh and cos rh in double only (for the rl terms)
-__device__ __forceinline__ double sin_series_d(double rh, double zh) {
-  using namespace crc;
-  double t = -i19;
-  t = t * zh + i17;
-  t = t * zh - i15;
-  t = t * zh + i13;
-  t = t * zh - i11;
-  t = t * zh + i9;
-  t = t * zh - 1.0 / 5040.0;
-  t = t * zh + 1.0 / 120.0;
-  t = t * zh - 1.0 / 6.0;
-  return rh + rh * (zh * t);
-}
-__device__ __forceinline__ double cos_series_d(double zh) {
-  using namespace crc;
-  double u = i20;
-  u = u * zh - i18;
-  u = u * zh + i16;
-  u = u * zh - i14;
-  u = u * zh + i12;
-  u = u * zh - i10;
-  u = u * zh + i8;
-  u = u * zh - 1.0 / 720.0;
-  u = u * zh + 1.0 / 24.0;
-  u = u * zh - 0.5;
-  return 1.0 + zh * u;
-}
 
 // x = k pi/2 + r with r as a double-double (the reduction of cr_sincos_dd)
 __device__ __forceinline__ dd reduce_pio2(double x, double* k) {
@@ -266,16 +197,68 @@ __device__ __forceinline__ bool ziv_round(dd v, double* out) {
   return a == b;
 }
 
-__device__ inline void cr_sincos(double x, double* sn, double* cs) {
+// The unrounded result comes from a table: with r = x - k pi/2 as above, j = rint(|r| 256/pi) <= 64 and
+// r' = |r| - j pi/256 (a double-double, |r'| <= pi/512),
+//   sin|r| = S_j cos r' + C_j sin r',  cos r = C_j cos r' - S_j sin r',
+// S_j = sin(j pi/256) and C_j as double-doubles.  cos r' - 1 = -z/2 + z^2/24 - ... (z = r'^2 a
+// double-double in its first term) is below 2^-15.7 and sin r' - r' below 2^-17.3 of r', so their
+// double parts err by less than 2^-69 of the result; the products with S_j and C_j are exact in
+// their leading terms.  The error stays below 2^-67 of the result (S_j and sin r' are at most the
+// result for j >= 1, and j = 0 leaves r' (1 - r'^2/6 + ...) alone; the largest of 3e6 arguments,
+// against 113 bits: 2^-67.9), so the rounding test decides.  One evaluation serves every quadrant (the roles of S and C are selected), where the
+// series for sin and cos were both run by waves whose lanes lie in different quadrants: about 90
+// instructions instead of 300.
+constexpr int kSinCosTab = 65;   // entries j pi/256, j = 0..64
+constexpr int kSinCosWords = 6;  // angle, sine and cosine, high and low words
+constexpr double k256OverPi = 0x1.45f306dc9c883p+6;
+static __constant__ __attribute__((aligned(16))) double c_sctab[kSinCosTab * kSinCosWords];
+// LDS copy of the table for a block (every thread calls this, then a barrier follows)
+__device__ __forceinline__ void stage_sctab(double* dst) {
+  for (int i = threadIdx.x; i < kSinCosTab * kSinCosWords; i += blockDim.x) dst[i] = c_sctab[i];
+}
+
+// r' and the table entry of |r|; z = r'^2
+struct ScArg {
+  dd S, C, r;   // table sine and cosine, r'
+  double s3;    // sin r' - r'
+  dd c1;        // cos r' - 1
+};
+__device__ __forceinline__ ScArg sc_arg(dd r, const double* tab) {
+  ScArg a;
+  const bool neg = r.hi < 0.0;
+  const double ah = neg ? -r.hi : r.hi, al = neg ? -r.lo : r.lo;
+  const double2* T = (const double2*)tab + 3 * (int)rint(ah * k256OverPi);
+  const double2 t = T[0], s = T[1], c = T[2];
+  a.S = {s.x, s.y};
+  a.C = {c.x, c.y};
+  a.r = dd_two_sum(ah - t.x, al - t.y);  // ah - t.x is exact
+  const double rh = a.r.hi;
+  const dd z = dd_two_prod(rh, rh);
+  const double zl = fma(2.0 * rh, a.r.lo, z.lo);
+  const double p = fma(z.hi, fma(z.hi, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0);
+  const double q = fma(z.hi, fma(z.hi, 1.0 / 40320.0, -1.0 / 720.0), 1.0 / 24.0);
+  a.s3 = rh * (z.hi * p);
+  a.c1 = {-0.5 * z.hi, fma(z.hi * z.hi, q, -0.5 * zl)};
+  return a;
+}
+// P (1 + c1) + Q (r' + s3) as an unevaluated sum
+__device__ __forceinline__ dd sc_combine(dd P, dd Q, const ScArg& a) {
+  const dd u = dd_two_prod(P.hi, a.c1.hi), v = dd_two_prod(Q.hi, a.r.hi);
+  double lo = fma(P.hi, a.c1.lo, fma(Q.hi, a.s3, fma(Q.hi, a.r.lo, fma(Q.lo, a.r.hi, fma(P.lo, a.c1.hi, P.lo)))));
+  lo += u.lo + v.lo;
+  const dd w = dd_two_sum(u.hi, v.hi), s = dd_two_sum(P.hi, w.hi);
+  return dd_fast_two_sum(s.hi, s.lo + (w.lo + lo));
+}
+
+__device__ inline void cr_sincos(double x, double* sn, double* cs, const double* tab = c_sctab) {
   if (fabs(x) < 1048576.0) {
     double k;
     const dd r = reduce_pio2(x, &k);
-    const dd z = dd_two_prod(r.hi, r.hi);
-    const dd s0 = sin_series_dd(r.hi, z), c0 = cos_series_dd(z);
-    const dd s = dd_add(s0, dd{r.lo * c0.hi, 0.0});
-    const dd c = dd_add(c0, dd{-r.lo * s0.hi, 0.0});
+    const ScArg a = sc_arg(r, tab);
+    const dd s = sc_combine(a.S, a.C, a), c = sc_combine(a.C, dd_neg(a.S), a);
     double sv, cv;
     if (ziv_round(s, &sv) && ziv_round(c, &cv)) {
+      if (r.hi < 0.0) sv = -sv;
       const int q = (int)k & 3;
       *sn = q == 0 ? sv : q == 1 ? cv : q == 2 ? -sv : -cv;
       *cs = q == 0 ? cv : q == 1 ? -sv : q == 2 ? -cv : sv;
@@ -286,23 +269,22 @@ __device__ inline void cr_sincos(double x, double* sn, double* cs) {
 }
 
 // sin(x + qs pi/2): qs = 0 sin, qs = 1 cos
-__device__ inline double cr_sinq(double x, int qs) {
+__device__ inline double cr_sinq(double x, int qs, const double* tab) {
   if (fabs(x) < 1048576.0) {
     double k;
     const dd r = reduce_pio2(x, &k);
-    const dd z = dd_two_prod(r.hi, r.hi);
+    const ScArg a = sc_arg(r, tab);
     const int q = ((int)k + qs) & 3;
-    dd v;
-    if (q & 1) v = dd_add(cos_series_dd(z), dd{-r.lo * sin_series_d(r.hi, z.hi), 0.0});  // +-cos r
-    else v = dd_add(sin_series_dd(r.hi, z), dd{r.lo * cos_series_d(z.hi), 0.0});        // +-sin r
+    const bool co = (q & 1) != 0;  // cos r, else sin r
+    const dd P = co ? a.C : a.S, Q = co ? dd_neg(a.S) : a.C;
     double out;
-    if (ziv_round(v, &out)) return (q & 2) ? -out : out;
+    if (ziv_round(sc_combine(P, Q, a), &out)) return ((q & 2) != 0) != (!co && r.hi < 0.0) ? -out : out;
   }
   return cr_sinq_dd(x, qs);
 }
 
-__device__ inline double cr_sin(double x) { return cr_sinq(x, 0); }
-__device__ inline double cr_cos(double x) { return cr_sinq(x, 1); }
+__device__ inline double cr_sin(double x, const double* tab = c_sctab) { return cr_sinq(x, 0, tab); }
+__device__ inline double cr_cos(double x, const double* tab = c_sctab) { return cr_sinq(x, 1, tab); }
 
 // Fast paths of the correctly rounded exp and log (the same Ziv test).
 //   exp: x = k ln2 + r (double-double, |r| <= 0.347); e^r by its Taylor series with the terms up

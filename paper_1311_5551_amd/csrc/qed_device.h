@@ -720,7 +720,8 @@ __device__ __forceinline__ void deposit_current(const qed_field& F, double Q, do
 
 template <int FK, bool EXACT = true>
 __device__ __forceinline__ void field_at(const qed_field& F, double x, double y, double t, double E[3],
-                                         double B[3], const FieldK* K = nullptr) {
+                                         double B[3], const FieldK* K = nullptr,
+                                         const double* sct = c_sctab) {
   E[0] = E[1] = E[2] = B[0] = B[1] = B[2] = 0.0;
   if (FK == QED_FIELD_UNIFORM) {
     E[0] = F.p[0];
@@ -734,8 +735,8 @@ __device__ __forceinline__ void field_at(const qed_field& F, double x, double y,
     if (psi >= 0.0 && psi <= F.p[1]) {
       double s, c, d;
       if (EXACT) {
-        s = cr_sin(kPi * psi / F.p[1]);
-        c = cr_cos(psi + F.p[3]);
+        s = cr_sin(kPi * psi / F.p[1], sct);
+        c = cr_cos(psi + F.p[3], sct);
       } else {  // K: pi / Psi precomputed
         s = fast_sin(psi * K->pi_over_len);
         c = fast_cos(psi + F.p[3]);
@@ -748,7 +749,7 @@ __device__ __forceinline__ void field_at(const qed_field& F, double x, double y,
   } else if (FK == QED_FIELD_CP_WAVE) {
     const double psi = t - x + F.p[1];
     double sn, cs;
-    if (EXACT) cr_sincos(psi, &sn, &cs);
+    if (EXACT) cr_sincos(psi, &sn, &cs, sct);
     else fast_sincos(psi, &sn, &cs);
     const double ey = F.p[0] * cs, ez = F.p[0] * sn;
     E[1] = ey;
@@ -758,8 +759,8 @@ __device__ __forceinline__ void field_at(const qed_field& F, double x, double y,
   } else if (FK == QED_FIELD_CP_STANDING) {
     double st, ct, sx, cx;
     if (EXACT) {
-      cr_sincos(t, &st, &ct);
-      cr_sincos(x, &sx, &cx);
+      cr_sincos(t, &st, &ct, sct);
+      cr_sincos(x, &sx, &cx, sct);
     } else {
       fast_sincos(t, &st, &ct);
       fast_sincos(x, &sx, &cx);

@@ -49,6 +49,7 @@ enum { MC_FIELD, MC_RANGE, MC_BAD, MC_EMIT, MC_NULL, MC_DROP, MC_LSTEPS, MC_PSTE
 struct MultiShared {
   qed_field F;
   double log[2 * kLogTab];
+  __attribute__((aligned(16))) double sct[kSinCosTab * kSinCosWords];
   int64_t scan[kMultiBlock];
   long long fx[3][4];                   // field work, radiated energy, emission defect
   unsigned long long cnt[MC_COUNT];
@@ -241,10 +242,11 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
     else tab[i] = a.tb.h[i];
   }
   if (!MIXED) stage_logtab(sh.log);
+  if (!MIXED && ZeroField<FK>::pw) stage_sctab(sh.sct);
   zero_shared(sh);
   const int64_t s0 = uni64(m.mc->s0), chunk = uni32(m.mc->lep_chunk);
   const double dt = a.sc.dt;
-  LepEnv env{dt, 0.0, (float)dt, emit, rr, rr_q, false, tab, (const float*)tab, sh.log};
+  LepEnv env{dt, 0.0, (float)dt, emit, rr, rr_q, false, tab, (const float*)tab, sh.log, sh.sct};
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
   for (int64_t c = bid; c < n_ch; c += nblk) {
@@ -299,6 +301,7 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
           }
           st.tau = as_global(S.tau_dev)[k];
           uid = as_global(S.uid_dev)[k];
+          lepton_gamma(st);
           wh = wl = rh = rl = 0.0;
           pend = moving = false;
           busy = n < m.k;

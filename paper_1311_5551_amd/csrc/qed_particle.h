@@ -17,7 +17,72 @@ struct LepState {
   Real x, y, z, ux, uy, uz;
   float xl, yl, zl, uxl, uyl, uzl;  // FP32-mixed low words
   double tau;
+  double g;  // gamma = sqrt(1 + u^2) of the momentum held (FP32-mixed: of hi + lo)
 };
+template <bool MIXED>
+__device__ __forceinline__ void lepton_gamma(LepState<MIXED>& st) {
+  double ux = st.ux, uy = st.uy, uz = st.uz;
+  if (MIXED) {
+    ux += st.uxl;
+    uy += st.uyl;
+    uz += st.uzl;
+  }
+  st.g = sqrt(1.0 + (ux * ux + uy * uy + uz * uz));
+}
+
+// Field components that are zero everywhere for a field kind.  The push leaves their terms out
+// (a product with zero added to a finite value is that value), which in the linearly polarised
+// pulse is half of its arithmetic.
+template <int FK>
+struct ZeroField {
+  static constexpr bool pw = FK == QED_FIELD_LP_PULSE || FK == QED_FIELD_CP_WAVE || FK == QED_FIELD_CP_STANDING;
+  static constexpr bool ex = pw, bx = pw, ey = false, bz = false;
+  static constexpr bool ez = FK == QED_FIELD_LP_PULSE, by = FK == QED_FIELD_LP_PULSE;
+};
+// c + (p q - r s), p q or r s left out where known to be zero
+template <bool ZP, bool ZR, class T>
+__device__ __forceinline__ T add_cross(T c, T p, T q, T r, T s) {
+  if constexpr (ZP && ZR) return c;
+  else if constexpr (ZP) return c - r * s;
+  else if constexpr (ZR) return c + p * q;
+  else return c + (p * q - r * s);
+}
+template <bool ZP, bool ZR, class T>
+__device__ __forceinline__ T cross2(T p, T q, T r, T s) {
+  if constexpr (ZP && ZR) return T(0);
+  else if constexpr (ZP) return -(r * s);
+  else if constexpr (ZR) return p * q;
+  else return p * q - r * s;
+}
+template <bool Z, class T>
+__device__ __forceinline__ T add_mul(T c, T p, T q) {
+  if constexpr (Z) return c;
+  else return c + p * q;
+}
+// g e + c, with e known to be zero: c
+template <bool Z, class T>
+__device__ __forceinline__ T mul_add(T g, T e, T c) {
+  if constexpr (Z) return c;
+  else return g * e + c;
+}
+// p0 q0 + p1 q1 + p2 q2 in this order
+template <bool Z0, bool Z1, bool Z2, class T>
+__device__ __forceinline__ T dot3(T p0, T q0, T p1, T q1, T p2, T q2) {
+  if constexpr (Z0 && Z1) return Z2 ? T(0) : p2 * q2;
+  else if constexpr (Z0) return add_mul<Z2>(p1 * q1, p2, q2);
+  else return add_mul<Z2>(add_mul<Z1>(p0 * q0, p1, q1), p2, q2);
+}
+// eta = |gamma E + u x B|^2 - (u . E)^2, as a square root
+template <int FK, class T>
+__device__ __forceinline__ T eta_of(T g, T ux, T uy, T uz, const T E[3], const T B[3]) {
+  using Z = ZeroField<FK>;
+  const T ax = mul_add<Z::ex>(g, E[0], cross2<Z::bz, Z::by>(uy, B[2], uz, B[1]));
+  const T ay = mul_add<Z::ey>(g, E[1], cross2<Z::bx, Z::bz>(uz, B[0], ux, B[2]));
+  const T az = mul_add<Z::ez>(g, E[2], cross2<Z::by, Z::bx>(ux, B[1], uy, B[0]));
+  const T ue = dot3<Z::ex, Z::ey, Z::ez>(ux, E[0], uy, E[1], uz, E[2]);
+  const T r2 = dot3<Z::ex && Z::by && Z::bz, false, Z::ez && Z::bx && Z::by>(ax, ax, ay, ay, az, az) - ue * ue;
+  return sqrt(r2 > T(0) ? r2 : T(0));
+}
 
 // what a lepton's step needs besides its state, uniform over a wave
 struct LepEnv {
@@ -27,6 +92,7 @@ struct LepEnv {
   const double* sh;   // LDS: h (FP64), g with QED_RR_QUANTUM; the FP32 copy of h in sh32
   const float* sh32;
   const double* slog; // LDS: log table
+  const double* sct;  // LDS: sine table of the correctly rounded sin and cos
 };
 
 // One full step of a lepton: field at the start-of-step position, Boris push, deterministic
@@ -38,6 +104,7 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
                                             const StepConst& sc, const Tabs& tb, const LepEnv& e, double* eta_out,
                                             double* wk, double* rd, unsigned& n_range, unsigned& n_bad,
                                             AfterPush after_push) {
+  using Z = ZeroField<FK>;
   bool pend = false;
   const double dt = e.dt, hq = e.hq;
   if constexpr (!MIXED) {
@@ -45,34 +112,34 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
     const double ux = st.ux, uy = st.uy, uz = st.uz;
     double tau = st.tau;
     double E[3], Bf[3];
-    field_at<FK>(sF, x, y, t, E, Bf);
-    const double g0 = sqrt(1.0 + (ux * ux + uy * uy + uz * uz));
-    const double umx = ux + hq * E[0], umy = uy + hq * E[1], umz = uz + hq * E[2];
+    field_at<FK>(sF, x, y, t, E, Bf, nullptr, e.sct);
+    const double umx = add_mul<Z::ex>(ux, hq, E[0]), umy = add_mul<Z::ey>(uy, hq, E[1]),
+                 umz = add_mul<Z::ez>(uz, hq, E[2]);
     const double gm = sqrt(1.0 + (umx * umx + umy * umy + umz * umz));
-    const double tx = hq / gm * Bf[0], ty = hq / gm * Bf[1], tz = hq / gm * Bf[2];
-    const double sf = 2.0 / (1.0 + (tx * tx + ty * ty + tz * tz));
+    const double hg = hq / gm;
+    const double tx = hg * Bf[0], ty = hg * Bf[1], tz = hg * Bf[2];
+    const double sf = 2.0 / (1.0 + dot3<Z::bx, Z::by, Z::bz>(tx, tx, ty, ty, tz, tz));
     const double sx = sf * tx, sy = sf * ty, sz = sf * tz;
-    const double upx = umx + (umy * tz - umz * ty), upy = umy + (umz * tx - umx * tz),
-                 upz = umz + (umx * ty - umy * tx);
-    const double ulx = umx + (upy * sz - upz * sy), uly = umy + (upz * sx - upx * sz),
-                 ulz = umz + (upx * sy - upy * sx);
-    const double u1x = ulx + hq * E[0], u1y = uly + hq * E[1], u1z = ulz + hq * E[2];
+    const double upx = add_cross<Z::bz, Z::by>(umx, umy, tz, umz, ty),
+                 upy = add_cross<Z::bx, Z::bz>(umy, umz, tx, umx, tz),
+                 upz = add_cross<Z::by, Z::bx>(umz, umx, ty, umy, tx);
+    const double ulx = add_cross<Z::bz, Z::by>(umx, upy, sz, upz, sy),
+                 uly = add_cross<Z::bx, Z::bz>(umy, upz, sx, upx, sz),
+                 ulz = add_cross<Z::by, Z::bx>(umz, upx, sy, upy, sx);
+    const double u1x = add_mul<Z::ex>(ulx, hq, E[0]), u1y = add_mul<Z::ey>(uly, hq, E[1]),
+                 u1z = add_mul<Z::ez>(ulz, hq, E[2]);
     const double g1 = sqrt(1.0 + (u1x * u1x + u1y * u1y + u1z * u1z));
-    *wk = 2.0 * hq * (E[0] * (ulx + umx) + E[1] * (uly + umy) + E[2] * (ulz + umz)) / (g1 + g0);
+    *wk = 2.0 * hq * dot3<Z::ex, Z::ey, Z::ez>(E[0], ulx + umx, E[1], uly + umy, E[2], ulz + umz) / (g1 + st.g);
     x += dt * u1x / g1;
     y += dt * u1y / g1;
     if (e.d3) z += dt * u1z / g1;
     after_push(st.x, st.y, x, y, u1z / g1);
     double wx = u1x, wy = u1y, wz = u1z;  // stored momentum
+    st.g = g1;
     if (e.rr) {
       // continuous reaction (eqs. 8, 9): gamma -> max(gamma - (2/3) alpha kappa eta^2 g dt, 1)
       // along u; the energy removed is what the stored momentum lost
-      const double ax = g1 * E[0] + (u1y * Bf[2] - u1z * Bf[1]);
-      const double ay = g1 * E[1] + (u1z * Bf[0] - u1x * Bf[2]);
-      const double az = g1 * E[2] + (u1x * Bf[1] - u1y * Bf[0]);
-      const double ue = u1x * E[0] + u1y * E[1] + u1z * E[2];
-      const double r2 = (ax * ax + ay * ay + az * az) - ue * ue;
-      const double eta = sqrt(r2 > 0.0 ? r2 : 0.0);
+      const double eta = eta_of<FK>(g1, u1x, u1y, u1z, E, Bf);
       if (eta > 0.0) {
         const double gq = e.rr_q ? lookup_g(e.sh, tb, eta, n_range) : 1.0;
         const double gn = fmax(g1 - sc.a_rr * eta * eta * gq * dt, 1.0);
@@ -81,16 +148,12 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
         wx = s * u1x;
         wy = s * u1y;
         wz = s * u1z;
-        *rd = g1 - sqrt(1.0 + (wx * wx + wy * wy + wz * wz));
+        st.g = sqrt(1.0 + (wx * wx + wy * wy + wz * wz));
+        *rd = g1 - st.g;
       }
     }
     if (e.emit) {
-      const double ax = g1 * E[0] + (u1y * Bf[2] - u1z * Bf[1]);
-      const double ay = g1 * E[1] + (u1z * Bf[0] - u1x * Bf[2]);
-      const double az = g1 * E[2] + (u1x * Bf[1] - u1y * Bf[0]);
-      const double ue = u1x * E[0] + u1y * E[1] + u1z * E[2];
-      const double r2 = (ax * ax + ay * ay + az * az) - ue * ue;
-      const double eta = sqrt(r2 > 0.0 ? r2 : 0.0);
+      const double eta = eta_of<FK>(g1, u1x, u1y, u1z, E, Bf);
       if (eta > 0.0) {
         const double h = lookup_h(e.sh, e.slog, tb, eta, n_range);
         tau -= sc.a_gamma * (eta / g1) * h * dt;
@@ -113,23 +176,26 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
     float uxh = st.ux, uxl = st.uxl, uyh = st.uy, uyl = st.uyl, uzh = st.uz, uzl = st.uzl;
     double tau = st.tau;
     const float dtf = e.dtf;
-    const double ux0 = (double)uxh + uxl, uy0 = (double)uyh + uyl, uz0 = (double)uzh + uzl;
-    const double g0d = sqrt(1.0 + (ux0 * ux0 + uy0 * uy0 + uz0 * uz0));
+    const double g0d = st.g;
     float E[3], Bf[3];
     field_at32<FK>(sF, fK, (double)xh + xl, (double)yh + yl, t, E, Bf);
     const float hqf = (float)hq;
-    const float umx = uxh + hqf * E[0], umy = uyh + hqf * E[1], umz = uzh + hqf * E[2];
+    const float umx = add_mul<Z::ex>(uxh, hqf, E[0]), umy = add_mul<Z::ey>(uyh, hqf, E[1]),
+                umz = add_mul<Z::ez>(uzh, hqf, E[2]);
     const float gm = sqrtf(1.0f + (umx * umx + umy * umy + umz * umz));
-    const float tx = hqf / gm * Bf[0], ty = hqf / gm * Bf[1], tz = hqf / gm * Bf[2];
-    const float sf = 2.0f / (1.0f + (tx * tx + ty * ty + tz * tz));
+    const float hg = hqf / gm;
+    const float tx = hg * Bf[0], ty = hg * Bf[1], tz = hg * Bf[2];
+    const float sf = 2.0f / (1.0f + dot3<Z::bx, Z::by, Z::bz>(tx, tx, ty, ty, tz, tz));
     const float sx = sf * tx, sy = sf * ty, sz = sf * tz;
-    const float upx = umx + (umy * tz - umz * ty), upy = umy + (umz * tx - umx * tz),
-                upz = umz + (umx * ty - umy * tx);
+    const float upx = add_cross<Z::bz, Z::by>(umx, umy, tz, umz, ty),
+                upy = add_cross<Z::bx, Z::bz>(umy, umz, tx, umx, tz),
+                upz = add_cross<Z::by, Z::bx>(umz, umx, ty, umy, tx);
     // rotation increment (u+ - u-) formed directly, without cancellation
-    const float rx = upy * sz - upz * sy, ry = upz * sx - upx * sz, rz = upx * sy - upy * sx;
-    comp_add(uxh, uxl, 2.0f * hqf * E[0] + rx);
-    comp_add(uyh, uyl, 2.0f * hqf * E[1] + ry);
-    comp_add(uzh, uzl, 2.0f * hqf * E[2] + rz);
+    const float rx = cross2<Z::bz, Z::by>(upy, sz, upz, sy), ry = cross2<Z::bx, Z::bz>(upz, sx, upx, sz),
+                rz = cross2<Z::by, Z::bx>(upx, sy, upy, sx);
+    comp_add(uxh, uxl, mul_add<Z::ex>(2.0f * hqf, E[0], rx));
+    comp_add(uyh, uyl, mul_add<Z::ey>(2.0f * hqf, E[1], ry));
+    comp_add(uzh, uzl, mul_add<Z::ez>(2.0f * hqf, E[2], rz));
     const float g1 = sqrtf(1.0f + (uxh * uxh + uyh * uyh + uzh * uzh));
     comp_add(xh, xl, dtf * uxh / g1);
     comp_add(yh, yl, dtf * uyh / g1);
@@ -138,15 +204,11 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
     const double ux1 = (double)uxh + uxl, uy1 = (double)uyh + uyl, uz1 = (double)uzh + uzl;
     const double g1d = sqrt(1.0 + (ux1 * ux1 + uy1 * uy1 + uz1 * uz1));
     *wk = g1d - g0d;
+    st.g = g1d;
     if (e.rr) {
       // continuous reaction with eta in FP32 (as for emission) and the energy update in
       // FP64 on the stored momentum; the energy removed is what the stored pairs lost
-      const float ax = g1 * E[0] + (uyh * Bf[2] - uzh * Bf[1]);
-      const float ay = g1 * E[1] + (uzh * Bf[0] - uxh * Bf[2]);
-      const float az = g1 * E[2] + (uxh * Bf[1] - uyh * Bf[0]);
-      const float ue = uxh * E[0] + uyh * E[1] + uzh * E[2];
-      const float r2 = (ax * ax + ay * ay + az * az) - ue * ue;
-      const double eta = (double)sqrtf(r2 > 0.0f ? r2 : 0.0f);
+      const double eta = (double)eta_of<FK>(g1, uxh, uyh, uzh, E, Bf);
       if (eta > 0.0) {
         const double gq = e.rr_q ? lookup_g(e.sh, tb, eta, n_range) : 1.0;
         const double gn = fmax(g1d - sc.a_rr * eta * eta * gq * dt, 1.0);
@@ -156,16 +218,12 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
         split_double(s * uy1, uyh, uyl);
         split_double(s * uz1, uzh, uzl);
         const double vx = (double)uxh + uxl, vy = (double)uyh + uyl, vz = (double)uzh + uzl;
-        *rd = g1d - sqrt(1.0 + (vx * vx + vy * vy + vz * vz));
+        st.g = sqrt(1.0 + (vx * vx + vy * vy + vz * vz));
+        *rd = g1d - st.g;
       }
     }
     if (e.emit) {
-      const float ax = g1 * E[0] + (uyh * Bf[2] - uzh * Bf[1]);
-      const float ay = g1 * E[1] + (uzh * Bf[0] - uxh * Bf[2]);
-      const float az = g1 * E[2] + (uxh * Bf[1] - uyh * Bf[0]);
-      const float ue = uxh * E[0] + uyh * E[1] + uzh * E[2];
-      const float r2 = (ax * ax + ay * ay + az * az) - ue * ue;
-      const float eta = sqrtf(r2 > 0.0f ? r2 : 0.0f);
+      const float eta = eta_of<FK>(g1, uxh, uyh, uzh, E, Bf);
       if (eta > 0.0f) {
         const float h = lookup32(e.sh32, tb.n_eta, tb.le0, tb.idle, eta, n_range, false);
         tau -= sc.a_gamma * dt * ((double)eta / (double)g1) * (double)h;  // FP32 look-up, FP64 decrement
@@ -204,7 +262,7 @@ template <bool MIXED>
 __device__ __forceinline__ DriftMove<MIXED> drift_move(const LepState<MIXED>& st, const LepEnv& e) {
   DriftMove<MIXED> m;
   if constexpr (!MIXED) {
-    const double g1 = sqrt(1.0 + (st.ux * st.ux + st.uy * st.uy + st.uz * st.uz));
+    const double g1 = st.g;
     m.dx = e.dt * st.ux / g1;
     m.dy = e.dt * st.uy / g1;
     m.dz = e.dt * st.uz / g1;
@@ -263,7 +321,7 @@ __device__ __forceinline__ Emission emit_photon(const Tabs& tb, LepState<MIXED>&
     uy1 = (double)st.uy + st.uyl;
     uz1 = (double)st.uz + st.uzl;
   }
-  const double g1 = sqrt(1.0 + (ux1 * ux1 + uy1 * uy1 + uz1 * uz1));
+  const double g1 = st.g;
   double chi;
   if (sample_chi(tb, eta, unit_open(r[0]), &chi)) {
     const double xi = 2.0 * chi / eta;
@@ -293,6 +351,7 @@ __device__ __forceinline__ Emission emit_photon(const Tabs& tb, LepState<MIXED>&
     const double g2 = sqrt(1.0 + (ux * ux + uy * uy + uz * uz));
     const double eps = sqrt(m.kx * m.kx + m.ky * m.ky + m.kz * m.kz);
     m.defect = g2 + eps - g1;
+    st.g = g2;
     m.child = true;
     m.tau = optical_depth(r[3]);
     m.uid = r[2];

@@ -194,6 +194,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
   extern __shared__ double smem[];
   __shared__ qed_field sF;
   __shared__ double sLog[2 * kLogTab];
+  constexpr bool TRIG = !MIXED && ZeroField<FK>::pw;  // the push evaluates correctly rounded sin and cos
+  __shared__ __attribute__((aligned(16))) double sSc[TRIG ? kSinCosTab * kSinCosWords : 1];
   double* sh = smem;
   float* sh32 = (float*)smem;
   long long* s_ll = (long long*)(smem + a.tb.n_eta);  // 16 waves x 2 sums x 4 words
@@ -212,6 +214,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
   }
   for (int i = threadIdx.x; i < 16 * 2 * 4; i += blockDim.x) s_ll[i] = 0;
   if (!MIXED) stage_logtab(sLog);
+  if (TRIG) stage_sctab(sSc);
 
   const int64_t step = uni64(a.glob->step_cur);
   const double t = a.sc.t0 + (double)step * a.sc.dt;
@@ -225,7 +228,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
   int64_t cb = 0, ce = 0, n = 0;
   LepPtr<MIXED> P{};
   bool d3 = false;
-  LepEnv env{dt, 0.0, (float)dt, emit, rr, rr_q, false, sh, sh32, sLog};
+  LepEnv env{dt, 0.0, (float)dt, emit, rr, rr_q, false, sh, sh32, sLog, sSc};
   double qch = 0.0;  // charge of the species (-1 electrons, +1 positrons)
   float tpf0 = 0.0f, psif_max = 0.0f;
   FieldK fK{0.0};
@@ -389,6 +392,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
       } else {
         st.xl = st.yl = st.zl = st.uxl = st.uyl = st.uzl = 0.0f;
       }
+      lepton_gamma(st);
       return st;
     };
     auto store_position = [&](unsigned off, const LepState<MIXED>& st) {
@@ -623,6 +627,7 @@ __global__ __launch_bounds__(256) void k_emit_events(StepArgs a) {
         cy = ((const double*)S.y_dev)[k];
         cz = d3 ? ((const double*)S.z_dev)[k] : 0.0;
       }
+      lepton_gamma(st);
       em = emit_photon<MIXED>(a.tb, st, ev.eta, uid, (uint64_t)step, seed, key_inst);
       if (em.child) {
         UX[k] = st.ux;

@@ -42,6 +42,7 @@ constexpr int kLepChunkMin = 16; // fewest leptons a block takes
 constexpr int kRefillLep = 8, kRefillPh = 8;  // idle lanes at which a wave takes new particles
 constexpr int kPhInner = 4;      // photon steps between two looks at the idle lanes
 constexpr int kRing = 128;       // per-wave ring of photon slots waiting for a lane
+constexpr int kPool = 128, kPoolWords = 13;   // per-wave pool of leptons waiting for a lane
 
 enum { MC_FIELD, MC_RANGE, MC_BAD, MC_EMIT, MC_NULL, MC_DROP, MC_LSTEPS, MC_PSTEPS, MC_ACTIVE, MC_READS, MC_GROUPS,
        MC_COUNT };
@@ -221,14 +222,85 @@ __device__ __forceinline__ void zero_shared(MultiShared& sh) {
 // ---------------------------------------------------------------------------
 // Leptons.  A block takes a chunk of one species of one instance, each wave a contiguous share of
 // it.  A lane takes a lepton, steps it to the end of the run and takes the next, so the lanes of
-// a wave are at different steps and stay busy.  A lepton whose optical depth ran out waits until
-// half as many lanes wait as still step; then the wave does their emissions together.  The
-// emission is ten times a push (Philox, two look-ups through L2, four logarithms), and at the
-// collision peak one lane in seventeen emits per step: at each step it would run for three lanes.
+// a wave are at different steps and stay busy.  A lepton whose optical depth ran out leaves its
+// lane for the wave's pool in LDS, and the lane goes on with another; when 64 wait, the wave's
+// running leptons change places with them and all lanes emit together.  An emission is three
+// pushes' work (Philox, two look-ups through L2, four logarithms) and at the collision peak one
+// lane in seventeen emits per step: done at once it would run for three lanes of 64.  At the end
+// of its share, when nothing is left to put into a lane, leptons that wait stay in their lanes
+// and emit once half as many wait as still step.
+//
+// The pool holds a lepton's 13 words in columns of 128: those waiting to emit from its bottom,
+// those that gave up their lane from its top.  A wave has at most 127 leptons in hand (63 waiting
+// and 64 in lanes before a step), so the two never meet.
 // ---------------------------------------------------------------------------
+template <bool MIXED>
+struct LeptonPool {
+  double* w;  // the wave's columns
+
+  __device__ static double pack(float h, float l) { return __hiloint2double(__float_as_int(h), __float_as_int(l)); }
+  __device__ static void unpack(double v, float& h, float& l) {
+    h = __int_as_float(__double2hiint(v));
+    l = __int_as_float(__double2loint(v));
+  }
+  __device__ void put(int e, const LepState<MIXED>& st, double wh, double wl, double eta, uint64_t uid, int n,
+                      int slot) const {
+    double* q = w + e;
+    if constexpr (MIXED) {
+      q[0 * kPool] = pack(st.x, st.xl);
+      q[1 * kPool] = pack(st.y, st.yl);
+      q[2 * kPool] = pack(st.z, st.zl);
+      q[3 * kPool] = pack(st.ux, st.uxl);
+      q[4 * kPool] = pack(st.uy, st.uyl);
+      q[5 * kPool] = pack(st.uz, st.uzl);
+    } else {
+      q[0 * kPool] = st.x;
+      q[1 * kPool] = st.y;
+      q[2 * kPool] = st.z;
+      q[3 * kPool] = st.ux;
+      q[4 * kPool] = st.uy;
+      q[5 * kPool] = st.uz;
+    }
+    q[6 * kPool] = st.tau;
+    q[7 * kPool] = st.g;
+    q[8 * kPool] = wh;
+    q[9 * kPool] = wl;
+    q[10 * kPool] = eta;
+    q[11 * kPool] = __longlong_as_double((long long)uid);
+    q[12 * kPool] = __hiloint2double(n, slot);
+  }
+  __device__ void get(int e, LepState<MIXED>& st, double& wh, double& wl, double& eta, uint64_t& uid, int& n,
+                      int& slot) const {
+    const double* q = w + e;
+    if constexpr (MIXED) {
+      unpack(q[0 * kPool], st.x, st.xl);
+      unpack(q[1 * kPool], st.y, st.yl);
+      unpack(q[2 * kPool], st.z, st.zl);
+      unpack(q[3 * kPool], st.ux, st.uxl);
+      unpack(q[4 * kPool], st.uy, st.uyl);
+      unpack(q[5 * kPool], st.uz, st.uzl);
+    } else {
+      st.x = q[0 * kPool];
+      st.y = q[1 * kPool];
+      st.z = q[2 * kPool];
+      st.ux = q[3 * kPool];
+      st.uy = q[4 * kPool];
+      st.uz = q[5 * kPool];
+    }
+    st.tau = q[6 * kPool];
+    st.g = q[7 * kPool];
+    wh = q[8 * kPool];
+    wl = q[9 * kPool];
+    eta = q[10 * kPool];
+    uid = (uint64_t)__double_as_longlong(q[11 * kPool]);
+    n = __double2hiint(q[12 * kPool]);
+    slot = __double2loint(q[12 * kPool]);
+  }
+};
+
 template <int FK, bool MIXED>
-__device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, MultiShared& sh, double* tab, int bid,
-                                             int nblk) {
+__device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, MultiShared& sh, double* tab,
+                                             double* pools, int bid, int nblk) {
   using Real = typename std::conditional<MIXED, float, double>::type;
   const StepArgs& a = m.s;
   const int64_t n_ch = uni64(m.mc->n_lep);
@@ -248,6 +320,8 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
   const double dt = a.sc.dt;
   LepEnv env{dt, 0.0, (float)dt, emit, rr, rr_q, false, tab, (const float*)tab, sh.log, sh.sct};
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  const LeptonPool<MIXED> pool{pools + wave * kPool * kPoolWords};
 
   for (int64_t c = bid; c < n_ch; c += nblk) {
     const int idx = uni32(find_entry(m.base_lep, 2 * m.n_inst, c));
@@ -273,17 +347,28 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
     bool busy = false, pend = false, moving = false;
     LepState<MIXED> st{};
     DriftMove<MIXED> mv{};
-    int64_t slot = 0;
+    int slot = 0;    // relative to lo
     uint64_t uid = 0;
-    int32_t n = 0;  // steps done since s0
+    int n = 0;       // steps done since s0
+    int n_wait = 0, n_ready = 0;  // leptons in the pool: waiting to emit, ready to go on
     double eta = 0.0, wh = 0.0, wl = 0.0, rh = 0.0, rl = 0.0;
     unsigned n_field = 0, n_range = 0, n_bad = 0, n_emit = 0, n_null = 0, n_drop = 0, lsteps = 0, psteps = 0;
     for (;;) {
-      const unsigned long long idle = __ballot(!busy);
-      if (next < w1 && (__popcll(idle) >= kRefillLep)) {
-        const int64_t k = next + __popcll(idle & ((1ull << lane) - 1ull));
+      unsigned long long idle = __ballot(!busy);
+      if (n_ready && idle) {
+        const int r = __popcll(idle & below);
+        if (!busy && r < n_ready) {
+          pool.get(kPool - n_ready + r, st, wh, wl, eta, uid, n, slot);
+          busy = true;
+          moving = false;
+        }
+        n_ready -= min(n_ready, __popcll(idle));
+        idle = __ballot(!busy);
+      }
+      if (next < w1 && __popcll(idle) >= kRefillLep) {
+        const int64_t k = next + __popcll(idle & below);
         if (!busy && k < w1) {
-          slot = k;
+          slot = (int)(k - lo);
           n = round ? max(0, m.lep_born[loff + k] - (int32_t)s0) : 0;
           st.x = as_global((const Real*)S.x_dev)[k];
           st.y = as_global((const Real*)S.y_dev)[k];
@@ -309,12 +394,12 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
         }
         next = min(w1, next + __popcll(idle));
       }
-      if (__ballot(busy) == 0ull) {
-        if (next >= w1) break;
+      if (__ballot(busy) == 0ull && n_wait == 0) {
+        if (next >= w1 && n_ready == 0) break;
         continue;
       }
       // one step of every lane that does not wait for its emission
-      if (busy && !pend) {
+      if (busy && !pend && n < m.k) {
         const double t = a.sc.t0 + (double)(s0 + n) * dt;
         const bool in = FK != QED_FIELD_LP_PULSE || near_pulse(t, tpf0, psif_max, (float)st.x);
         if (in) {
@@ -333,9 +418,59 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
         }
         ++n;
       }
+      if (busy && !pend && n >= m.k) {  // done: back to memory
+        as_global((Real*)S.x_dev)[lo + slot] = st.x;
+        as_global((Real*)S.y_dev)[lo + slot] = st.y;
+        if (env.d3) as_global((Real*)S.z_dev)[lo + slot] = st.z;
+        as_global((Real*)S.ux_dev)[lo + slot] = st.ux;
+        as_global((Real*)S.uy_dev)[lo + slot] = st.uy;
+        as_global((Real*)S.uz_dev)[lo + slot] = st.uz;
+        if (MIXED) {
+          as_global(S.x_lo_dev)[lo + slot] = st.xl;
+          as_global(S.y_lo_dev)[lo + slot] = st.yl;
+          if (env.d3) as_global(S.z_lo_dev)[lo + slot] = st.zl;
+          as_global(S.ux_lo_dev)[lo + slot] = st.uxl;
+          as_global(S.uy_lo_dev)[lo + slot] = st.uyl;
+          as_global(S.uz_lo_dev)[lo + slot] = st.uzl;
+        }
+        as_global(S.tau_dev)[lo + slot] = st.tau;
+        fix_lds_add(sh.fx[0], wh);
+        fix_lds_add(sh.fx[0], wl);
+        if (rr) {
+          fix_lds_add(sh.fx[1], rh);
+          fix_lds_add(sh.fx[1], rl);
+        }
+        busy = false;
+      }
       if (emit) {
-        const int n_pend = __popcll(__ballot(pend)), n_run = __popcll(__ballot(busy && !pend && n < m.k));
-        if (n_pend && 2 * n_pend >= n_run) {
+        const bool more = next < w1 || n_ready > 0;  // a lane given up can be filled again
+        if (more) {
+          const unsigned long long out = __ballot(pend);
+          if (pend) {
+            pool.put(n_wait + __popcll(out & below), st, wh, wl, eta, uid, n, slot);
+            busy = pend = false;
+          }
+          n_wait += __popcll(out);
+        }
+        const int n_pend = n_wait + __popcll(__ballot(pend)), n_run = __popcll(__ballot(busy && !pend));
+        if (n_wait >= 64 || (!more && n_pend && 2 * n_pend >= n_run)) {
+          if (n_wait) {
+            // those in lanes to the top of the pool, those waiting into the lanes
+            const unsigned long long out = __ballot(busy && !pend);
+            n_ready += __popcll(out);
+            if (busy && !pend) {
+              pool.put(kPool - n_ready + __popcll(out & below), st, wh, wl, eta, uid, n, slot);
+              busy = false;
+            }
+            __builtin_amdgcn_wave_barrier();  // (a wave's LDS accesses are carried out in order)
+            const unsigned long long in = __ballot(!busy);
+            const int take = min(n_wait, __popcll(in)), r = __popcll(in & below);
+            if (!busy && r < take) {
+              pool.get(n_wait - take + r, st, wh, wl, eta, uid, n, slot);
+              busy = pend = true;
+            }
+            n_wait -= take;
+          }
           Emission em;
           em.child = false;
           double cx = 0.0, cy = 0.0, cz = 0.0;
@@ -377,30 +512,6 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
           }
           if (!pairs) wave_or_bit(lword, (int)(ps % kWinGroup));
         }
-      }
-      if (busy && !pend && n >= m.k) {  // done: back to memory
-        as_global((Real*)S.x_dev)[slot] = st.x;
-        as_global((Real*)S.y_dev)[slot] = st.y;
-        if (env.d3) as_global((Real*)S.z_dev)[slot] = st.z;
-        as_global((Real*)S.ux_dev)[slot] = st.ux;
-        as_global((Real*)S.uy_dev)[slot] = st.uy;
-        as_global((Real*)S.uz_dev)[slot] = st.uz;
-        if (MIXED) {
-          as_global(S.x_lo_dev)[slot] = st.xl;
-          as_global(S.y_lo_dev)[slot] = st.yl;
-          if (env.d3) as_global(S.z_lo_dev)[slot] = st.zl;
-          as_global(S.ux_lo_dev)[slot] = st.uxl;
-          as_global(S.uy_lo_dev)[slot] = st.uyl;
-          as_global(S.uz_lo_dev)[slot] = st.uzl;
-        }
-        as_global(S.tau_dev)[slot] = st.tau;
-        fix_lds_add(sh.fx[0], wh);
-        fix_lds_add(sh.fx[0], wl);
-        if (rr) {
-          fix_lds_add(sh.fx[1], rh);
-          fix_lds_add(sh.fx[1], rl);
-        }
-        busy = false;
       }
     }
     count_wave(sh, MC_FIELD, n_field);
@@ -633,7 +744,7 @@ template <int FK, bool MIXED>
 __global__ __launch_bounds__(kMultiBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_multi_lepton(MultiArgs m) {
   extern __shared__ double tab[];
   __shared__ MultiShared sh;
-  multi_lepton<FK, MIXED>(m, m.round, sh, tab, blockIdx.x, gridDim.x);
+  multi_lepton<FK, MIXED>(m, m.round, sh, tab, tab + m.n_tab, blockIdx.x, gridDim.x);
 }
 template <int FK, bool MIXED>
 __global__ __launch_bounds__(kMultiBlock) void k_multi_photon(MultiArgs m) {
@@ -658,7 +769,7 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi_finish(MultiArgs m) {
   for (int g = 0; g <= m.k; ++g) {
     if (multi_begin(m, kRounds, sh, 1) == 0) break;  // block-uniform
     sync();
-    multi_lepton<FK, MIXED>(m, kRounds, sh, tab, 0, 1);
+    multi_lepton<FK, MIXED>(m, kRounds, sh, tab, tab + m.n_tab, 0, 1);
     sync();
     multi_mid(m, sh, 1);
     sync();
@@ -674,20 +785,25 @@ hipError_t init_crmath_multi() {
   return upload_crmath(&done);
 }
 
-static size_t multi_shm(int n_eta, int n_cp) { return (size_t)std::max(n_eta, n_cp) * sizeof(double); }
+// dynamic LDS: the rate table, and the lepton kernels' pools
+static int multi_tab(int n_eta, int n_cp) { return (std::max(n_eta, n_cp) + 1) / 2 * 2; }
+static size_t multi_shm(int n_tab, bool leptons) {
+  return sizeof(double) * ((size_t)n_tab + (leptons ? (size_t)kMultiWaves * kPool * kPoolWords : 0));
+}
 
 template <int FK, bool MIXED>
-static int multi_fit(int which, size_t shm) {
+static int multi_fit(int which, int n_tab) {
   int n = 0;
+  const size_t shm = multi_shm(n_tab, which == 0);
   const hipError_t e =
       which ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_multi_photon<FK, MIXED>, kMultiBlock, shm)
             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_multi_lepton<FK, MIXED>, kMultiBlock, shm);
   return e == hipSuccess && n > 0 ? n : 1;
 }
 int multi_blocks_per_cu(int fk, int which, int n_eta, int n_cp, bool mixed) {
-  const size_t shm = multi_shm(n_eta, n_cp);
+  const int n_tab = multi_tab(n_eta, n_cp);
 #define QED_FIT(K) \
-  if (fk == K) return mixed ? multi_fit<K, true>(which, shm) : multi_fit<K, false>(which, shm);
+  if (fk == K) return mixed ? multi_fit<K, true>(which, n_tab) : multi_fit<K, false>(which, n_tab);
   QED_FIT(QED_FIELD_UNIFORM)
   QED_FIT(QED_FIELD_LP_PULSE)
   QED_FIT(QED_FIELD_CP_WAVE)
@@ -698,18 +814,19 @@ int multi_blocks_per_cu(int fk, int which, int n_eta, int n_cp, bool mixed) {
 
 template <int FK, bool MIXED>
 static void launch_multi_fk(MultiArgs m, hipStream_t s) {
-  const size_t shm = multi_shm(m.s.tb.n_eta, m.s.tb.n_cp);
+  m.n_tab = multi_tab(m.s.tb.n_eta, m.s.tb.n_cp);
+  const size_t shl = multi_shm(m.n_tab, true), shp = multi_shm(m.n_tab, false);
   const dim3 b(kMultiBlock);
   const bool pairs = (m.s.sc.flags & QED_PAIRS) != 0;
   for (m.round = 0; m.round < (pairs ? kRounds : 1); ++m.round) {
     hipLaunchKernelGGL(k_multi_begin, dim3(1), b, 0, s, m);
-    hipLaunchKernelGGL((k_multi_lepton<FK, MIXED>), dim3(m.lep_grid), b, shm, s, m);
+    hipLaunchKernelGGL((k_multi_lepton<FK, MIXED>), dim3(m.lep_grid), b, shl, s, m);
     if (!pairs) return;
     hipLaunchKernelGGL(k_multi_mid, dim3(1), b, 0, s, m);
-    hipLaunchKernelGGL((k_multi_photon<FK, MIXED>), dim3(m.ph_grid), b, shm, s, m);
+    hipLaunchKernelGGL((k_multi_photon<FK, MIXED>), dim3(m.ph_grid), b, shp, s, m);
     hipLaunchKernelGGL((k_multi_pairs<FK, MIXED>), dim3(256), b, 0, s, m);
   }
-  hipLaunchKernelGGL((k_multi_finish<FK, MIXED>), dim3(1), b, shm, s, m);
+  hipLaunchKernelGGL((k_multi_finish<FK, MIXED>), dim3(1), b, shl, s, m);
 }
 void launch_multi(int fk, MultiArgs m, bool mixed, hipStream_t s) {
 #define QED_MULTI(K)                               \

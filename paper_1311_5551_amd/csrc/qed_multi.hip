@@ -89,7 +89,7 @@ __device__ inline int64_t multi_begin(const MultiArgs& m, int round, MultiShared
   const int per = (m.n_inst + kMultiBlock - 1) / kMultiBlock;
   const int b = min(m.n_inst, (int)threadIdx.x * per), e = min(m.n_inst, b + per);
   const bool pairs = (m.s.sc.flags & QED_PAIRS) != 0;
-  int64_t tot = 0;
+  int64_t tot = 0, used = 0;
   for (int i = b; i < e; ++i) {
     InstAcc& A = acc[i];
     for (int s = 0; s < 2; ++s) {
@@ -98,6 +98,7 @@ __device__ inline int64_t multi_begin(const MultiArgs& m, int round, MultiShared
       A.lep_lo[s] = lo;
       A.lep_hi[s] = c;
       tot += c - lo;
+      used += c > lo;
     }
     if (round == 0) {
       const int64_t c = clamp_count(inst[i].s[2]);
@@ -109,9 +110,13 @@ __device__ inline int64_t multi_begin(const MultiArgs& m, int round, MultiShared
       if (pairs) A.particle_steps[2] += (unsigned long long)(c * m.k);
     }
   }
-  int64_t total, n_ch;
+  int64_t total, n_used, n_ch;
   block_scan(tot, sh.scan, &total);
-  const int64_t chunk = max((int64_t)kLepChunkMin, (total + grid - 1) / grid);
+  block_scan(used, sh.scan, &n_used);
+  // one chunk per block, with the last, partial chunk of each species counted (a second round of
+  // chunks would take as long as the first)
+  const int64_t room = max((int64_t)grid - n_used, (int64_t)(grid + 1) / 2);
+  const int64_t chunk = max((int64_t)kLepChunkMin, (total + room - 1) / room);
   int64_t mine = 0;
   for (int i = b; i < e; ++i)
     for (int s = 0; s < 2; ++s) mine += (acc[i].lep_hi[s] - acc[i].lep_lo[s] + chunk - 1) / chunk;
@@ -228,7 +233,10 @@ __device__ __forceinline__ void zero_shared(MultiShared& sh) {
 // pushes' work (Philox, two look-ups through L2, four logarithms) and at the collision peak one
 // lane in seventeen emits per step: done at once it would run for three lanes of 64.  At the end
 // of its share, when nothing is left to put into a lane, leptons that wait stay in their lanes
-// and emit once half as many wait as still step.
+// and emit once half as many wait as still step.  A wave whose share fits its lanes (small runs)
+// has no use for the pool; its memory then collects the new photons, which go out 64 at a time.
+// (With one reservation per emission pass the 2000 waves' atomics on the photon count, about 10 ns
+// each, took longer than all the rest.)
 //
 // The pool holds a lepton's 13 words in columns of 128: those waiting to emit from its bottom,
 // those that gave up their lane from its top.  A wave has at most 127 leptons in hand (63 waiting
@@ -298,6 +306,35 @@ struct LeptonPool {
   }
 };
 
+// New photons of a wave waiting to be appended: 9 words each, in columns of kPool in the pool's memory
+struct PhotonStage {
+  double* w;
+  __device__ void put(int e, double x, double y, double z, const Emission& m, int n) const {
+    double* q = w + e;
+    q[0 * kPool] = x;
+    q[1 * kPool] = y;
+    q[2 * kPool] = z;
+    q[3 * kPool] = m.kx;
+    q[4 * kPool] = m.ky;
+    q[5 * kPool] = m.kz;
+    q[6 * kPool] = m.tau;
+    q[7 * kPool] = __longlong_as_double((long long)m.uid);
+    q[8 * kPool] = __hiloint2double(0, n);
+  }
+  __device__ void get(int e, double& x, double& y, double& z, Emission& m, int& n) const {
+    const double* q = w + e;
+    x = q[0 * kPool];
+    y = q[1 * kPool];
+    z = q[2 * kPool];
+    m.kx = q[3 * kPool];
+    m.ky = q[4 * kPool];
+    m.kz = q[5 * kPool];
+    m.tau = q[6 * kPool];
+    m.uid = (uint64_t)__double_as_longlong(q[7 * kPool]);
+    n = __double2loint(q[8 * kPool]);
+  }
+};
+
 template <int FK, bool MIXED>
 __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, MultiShared& sh, double* tab,
                                              double* pools, int bid, int nblk) {
@@ -344,6 +381,9 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
     const int64_t per = (hi - lo + kMultiWaves - 1) / kMultiWaves;
     int64_t next = lo + wave * per;
     const int64_t w1 = min(hi, next + per);
+    const bool stage = per <= 64;  // no use for the pool: it collects new photons
+    const PhotonStage staged{pool.w};
+    int n_staged = 0;
     bool busy = false, pend = false, moving = false;
     LepState<MIXED> st{};
     DriftMove<MIXED> mv{};
@@ -353,6 +393,27 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
     int n_wait = 0, n_ready = 0;  // leptons in the pool: waiting to emit, ready to go on
     double eta = 0.0, wh = 0.0, wl = 0.0, rh = 0.0, rl = 0.0;
     unsigned n_field = 0, n_range = 0, n_bad = 0, n_emit = 0, n_null = 0, n_drop = 0, lsteps = 0, psteps = 0;
+    // the wave's new photons (lanes with `child`) into the photon arrays, first stepped in step s0 + nb
+    auto append = [&](bool child, double cx, double cy, double cz, const Emission& em, int nb) {
+      const qed_species& G = I.s[2];
+      const long long ps = wave_reserve(child, G.count_dev);
+      uint64_t* lword = nullptr;
+      if (child) {
+        if (ps < G.capacity) {
+          const uint32_t wn = store_photon<FK, MIXED>(G, ps, moff + ps, env.d3, cx, cy, cz, em, (int32_t)(s0 + nb),
+                                                      sh.F, a.tb.cp_min, a.sc, a.win, a.rec);
+          psteps += m.k - nb;
+          // the photon kernel writes the live masks; without it they are set here
+          if (!pairs && !window_over(wn, s0 + nb)) lword = a.lmask + A.lmask_off + ps / kWinGroup;
+        } else {
+          ++n_drop;
+          long long l[4];
+          fix_split(sqrt(em.kx * em.kx + em.ky * em.ky + em.kz * em.kz), l);
+          fix_atomic_add(a.acc[ii].fx[FX_DROPPED], l);
+        }
+      }
+      if (!pairs) wave_or_bit(lword, (int)(ps % kWinGroup));
+    };
     for (;;) {
       unsigned long long idle = __ballot(!busy);
       if (n_ready && idle) {
@@ -486,33 +547,39 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
               cz += st.zl;
             }
           }
-          const qed_species& G = I.s[2];
-          const long long ps = wave_reserve(em.child, G.count_dev);
-          uint64_t* lword = nullptr;
           if (pend) {
             if (em.child) {
               ++n_emit;
               fix_lds_add(sh.fx[2], em.defect);
-              if (ps < G.capacity) {
-                const uint32_t wn = store_photon<FK, MIXED>(G, ps, moff + ps, env.d3, cx, cy, cz, em, (int32_t)(s0 + n),
-                                                            sh.F, a.tb.cp_min, a.sc, a.win, a.rec);
-                psteps += m.k - n;
-                // the photon kernel writes the live masks; without it they are set here
-                if (!pairs && !window_over(wn, s0 + n)) lword = a.lmask + A.lmask_off + ps / kWinGroup;
-              } else {
-                ++n_drop;
-                long long l[4];
-                fix_split(sqrt(em.kx * em.kx + em.ky * em.ky + em.kz * em.kz), l);
-                fix_atomic_add(a.acc[ii].fx[FX_DROPPED], l);
-              }
             } else {
               ++n_null;
             }
             pend = false;
           }
-          if (!pairs) wave_or_bit(lword, (int)(ps % kWinGroup));
+          if (stage) {
+            const unsigned long long out = __ballot(em.child);
+            if (em.child) staged.put(n_staged + __popcll(out & below), cx, cy, cz, em, n);
+            n_staged += __popcll(out);
+          } else {
+            append(em.child, cx, cy, cz, em, n);
+          }
         }
       }
+      if (n_staged >= 64) {
+        n_staged -= 64;
+        Emission em;
+        double cx, cy, cz;
+        int nb;
+        staged.get(n_staged + lane, cx, cy, cz, em, nb);
+        append(true, cx, cy, cz, em, nb);
+      }
+    }
+    if (n_staged) {
+      Emission em{};
+      double cx = 0.0, cy = 0.0, cz = 0.0;
+      int nb = 0;
+      if (lane < n_staged) staged.get(lane, cx, cy, cz, em, nb);
+      append(lane < n_staged, cx, cy, cz, em, nb);
     }
     count_wave(sh, MC_FIELD, n_field);
     count_wave(sh, MC_RANGE, n_range);

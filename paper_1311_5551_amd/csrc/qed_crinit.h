@@ -64,6 +64,37 @@ static hipError_t upload_crmath(unsigned long long* done) {
     for (int q = 0; q < kSinCosWords; ++q) sc[kSinCosWords * j + q] = row[q];
   }
   if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_sctab), sc, sizeof(sc));
+  // tables of the correctly rounded log and exp: c_j and -log c_j for the 128 sub-intervals of the
+  // mantissa (log c = 2 atanh t, t = (c - 1)/(c + 1), in double-double), and 2^(j/64) by the
+  // exponential's Taylor series
+  auto div = [&](dd a, dd b) {  // long division, three digits
+    const double q1 = a.hi / b.hi;
+    dd r = add(a, mul(b, dd{-q1, 0.0}));
+    const double q2 = r.hi / b.hi;
+    r = add(r, mul(b, dd{-q2, 0.0}));
+    return add(fast(q1, q2), dd{r.hi / b.hi, 0.0});
+  };
+  double mt[kMathTab];
+  for (int j = 0; j < kLogCrTab; ++j) {
+    const double mid = 0.5 + j / 256.0 + 1.0 / 512.0;                         // of [1/2 + j/256, + 1/256)
+    double cj = std::rint((mid < 0.75 ? 0.5 : 1.0) / mid * 512.0) / 512.0;  // 1/m, m in [3/4, 3/2)
+    if (j == 0 || j == kLogCrTab - 1) cj = 1.0;
+    const dd t = div(dd{cj - 1.0, 0.0}, dd{cj + 1.0, 0.0}), t2 = mul(t, t);
+    dd p = {0.0, 0.0};
+    for (int n = 61; n >= 1; n -= 2) p = add(mul(p, t2), div(dd{1.0, 0.0}, dd{(double)n, 0.0}));
+    const dd l = mul(mul(p, t), dd{-2.0, 0.0});
+    mt[3 * j] = cj;
+    mt[3 * j + 1] = l.hi;
+    mt[3 * j + 2] = l.lo;
+  }
+  for (int j = 0; j < kExpTab; ++j) {
+    const dd x = mul(dd{kLn2Hi, kLn2Lo}, dd{j / 64.0, 0.0});
+    dd p = f[29];
+    for (int n = 28; n >= 0; --n) p = add(mul(p, x), f[n]);
+    mt[3 * kLogCrTab + 2 * j] = p.hi;
+    mt[3 * kLogCrTab + 2 * j + 1] = p.lo;
+  }
+  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_mathtab), mt, sizeof(mt));
   if (e == hipSuccess && dev < 64) *done |= 1ull << dev;
   return e;
 }

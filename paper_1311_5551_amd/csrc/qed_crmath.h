@@ -173,13 +173,6 @@ __device__ __noinline__ double cr_sinq_dd(double x, int qs) {
 // ---------------------------------------------------------------------------
 constexpr double kZivEps = 0x1p-66;
 
-// 1/n! rounded to double, for the double tails
-namespace crc {
-constexpr double i8 = 1.0 / 40320.0, i9 = 1.0 / 362880.0, i10 = 1.0 / 3628800.0, i11 = 1.0 / 39916800.0,
-                 i12 = 1.0 / 479001600.0, i13 = 1.0 / 6227020800.0, i14 = 1.0 / 87178291200.0,
-                 i15 = 1.0 / 1307674368000.0, i16 = 1.0 / 20922789888000.0, i17 = 1.0 / 355687428096000.0;
-}  // namespace crc
-
 __device__ __forceinline__ dd dd_neg(dd a) { return {-a.hi, -a.lo}; }
 
 // x = k pi/2 + r with r as a double-double (the reduction of cr_sincos_dd)
@@ -286,86 +279,82 @@ __device__ inline double cr_sinq(double x, int qs, const double* tab) {
 __device__ inline double cr_sin(double x, const double* tab = c_sctab) { return cr_sinq(x, 0, tab); }
 __device__ inline double cr_cos(double x, const double* tab = c_sctab) { return cr_sinq(x, 1, tab); }
 
-// Fast paths of the correctly rounded exp and log (the same Ziv test).
-//   exp: x = k ln2 + r (double-double, |r| <= 0.347); e^r by its Taylor series with the terms up
-//        to r^5 in double-double and r^6 .. r^17 in double (tail below 1.7e-3 of the result,
-//        truncation below 1e-24): the unrounded e^r is within 2^-68 of the exact value; times 2^k.
-//   log: x = m 2^e, m in [1/sqrt2, sqrt2); log m = 2 atanh(s), s = (m - 1)/(m + 1) as a
-//        double-double (|s| <= 0.172), the series 2 (s + s^3/3 + s^5/5) in double-double and
-//        s^7/7 .. s^27/27 in double (tail below 4e-6 of the result, truncation below 1e-21);
-//        plus e ln2.  Relative error below 2^-68 of the result.
-constexpr double kThirdHi = 0x1.5555555555555p-2, kThirdLo = 0x1.5555555555555p-56;  // 1/3
-constexpr double kFifthHi = 0x1.999999999999ap-3, kFifthLo = -0x1.999999999999ap-57;  // 1/5
+// Fast paths of the correctly rounded exp and log (the same rounding test), both from tables:
+//   exp: x = k ln2/64 + r (double-double, |r| <= 0.00542), e^x = 2^(k/64) (1 + r + r^2/2 + ...).
+//        T_j = 2^(j/64) is a double-double; r^2/2 and the terms up to r^7/7! are below 2^-16 of the
+//        result, so their double sum errs by less than 2^-69 of it.
+//   log: x = m 2^e, m in [3/4, 3/2); c_j ~ 1/m with 9 bits, picked by the 7 leading bits of the
+//        mantissa, so that m c_j = 1 + r exactly as a double-double, |r| <= 2^-7; log x =
+//        e ln2 + L_j + r - r^2/2 + (r^3/3 - ... - r^10/10), L_j = -log c_j a double-double, the
+//        first two terms in double-double and the rest (below 2^-15 of log1p r) in double.
+//        c_j = 1 next to m = 1 on both sides, so log x keeps its relative accuracy there.
+// About 45 and 60 instructions where the series without tables took 165 and 170.
+constexpr int kLogCrTab = 128, kExpTab = 64;
+constexpr int kMathTab = 3 * kLogCrTab + 2 * kExpTab;  // c_j, L_j (high, low) each; then T_j (high, low)
+static __constant__ __attribute__((aligned(16))) double c_mathtab[kMathTab];
+__device__ __forceinline__ void stage_mathtab(double* dst) {
+  for (int i = threadIdx.x; i < kMathTab; i += blockDim.x) dst[i] = c_mathtab[i];
+}
+constexpr double k64OverLn2 = 0x1.71547652b82fep+6;
+constexpr double kLn2o64A = 0x1.62e42fefa0000p-7;  // ln2 / 64 = A + B + C, A with 36 significant bits
+constexpr double kLn2o64B = 0x1.cf79abc9e3b3ap-46;
+constexpr double kLn2o64C = -0x1.ff0342542fc33p-100;
 
-__device__ inline double cr_exp(double x) {
+__device__ inline double cr_exp(double x, const double* tab = c_mathtab) {
   if (x > -700.0 && x < 709.0) {
-    using namespace crc;
-    const double k = rint(x * kInvLn2);
-    dd r = dd_add(dd{x - k * kLn2A, 0.0}, dd_two_prod(-k, kLn2B));
-    r = dd_fast_two_sum(r.hi, r.lo - k * kLn2C);
+    const double k = rint(x * k64OverLn2);
+    const int ki = (int)k;
+    const double* T = tab + 3 * kLogCrTab + 2 * (ki & (kExpTab - 1));
+    const double th = T[0], tl = T[1];
+    const dd kb = dd_two_prod(-k, kLn2o64B);
+    dd r = dd_two_sum(fma(-k, kLn2o64A, x), kb.hi);  // x - k A is exact
+    r = dd_fast_two_sum(r.hi, r.lo + (kb.lo - k * kLn2o64C));
     const double rh = r.hi;
-    double t = i17;
-    t = t * rh + i16;
-    t = t * rh + i15;
-    t = t * rh + i14;
-    t = t * rh + i13;
-    t = t * rh + i12;
-    t = t * rh + i11;
-    t = t * rh + i10;
-    t = t * rh + i9;
-    t = t * rh + i8;
-    t = t * rh + 1.0 / 5040.0;
-    t = t * rh + 1.0 / 720.0;                          // 1/6! + r/7! + ...
-    dd p = dd_add(c_inv_fact[5], dd_two_prod(rh, t));  // 1/5! + r (1/6! + ...)
-    p = dd_add(dd_mul(r, p), c_inv_fact[4]);
-    p = dd_add(dd_mul(r, p), c_inv_fact[3]);
-    p = dd_add(dd_mul(r, p), c_inv_fact[2]);
-    p = dd_add(dd_mul(r, p), c_inv_fact[1]);
-    p = dd_add(dd_mul(r, p), c_inv_fact[0]);
+    double q = fma(rh, 1.0 / 5040.0, 1.0 / 720.0);
+    q = fma(rh, q, 1.0 / 120.0);
+    q = fma(rh, q, 1.0 / 24.0);
+    q = fma(rh, q, 1.0 / 6.0);
+    q = fma(rh, q, 0.5);
+    const double lo = fma(rh * rh, q, fma(rh, r.lo, r.lo));  // e^r - 1 = rh + lo
+    const dd p = dd_two_prod(th, rh);
+    const dd s = dd_fast_two_sum(th, p.hi);
     double out;
-    if (ziv_round(p, &out)) return ldexp(out, (int)k);
+    if (ziv_round(dd_fast_two_sum(s.hi, s.lo + (p.lo + fma(th, lo, fma(tl, rh, tl)))), &out))
+      return ldexp(out, ki >> 6);
   }
   return cr_exp_dd(x);
 }
 
-__device__ inline double cr_log(double x) {
+__device__ inline double cr_log(double x, const double* tab = c_mathtab) {
   if (x >= 0x1p-1021 && x < INFINITY) {
     int e;
-    double m = frexp(x, &e);
-    if (m < 0.70710678118654752) {
+    double m = frexp(x, &e);  // [1/2, 1)
+    const double* T = tab + 3 * (int)((uint32_t)(__double_as_longlong(m) >> 45) & (kLogCrTab - 1));
+    const double c = T[0], lh = T[1], ll = T[2];
+    if (m < 0.75) {
       m *= 2.0;
       e -= 1;
     }
-    const double num = m - 1.0;              // exact
-    const dd den = dd_two_sum(m, 1.0);       // m + 1 exactly
-    const double q1 = num / den.hi;
-    const dd pq = dd_two_prod(q1, den.hi);
-    const double q2 = (((num - pq.hi) - pq.lo) - q1 * den.lo) / den.hi;
-    const dd s = dd_fast_two_sum(q1, q2);    // (m - 1)/(m + 1)
-    const dd s2 = dd_mul(s, s);
-    const double z = s2.hi;
-    double t = 1.0 / 27.0;
-    t = t * z + 1.0 / 25.0;
-    t = t * z + 1.0 / 23.0;
-    t = t * z + 1.0 / 21.0;
-    t = t * z + 1.0 / 19.0;
-    t = t * z + 1.0 / 17.0;
-    t = t * z + 1.0 / 15.0;
-    t = t * z + 1.0 / 13.0;
-    t = t * z + 1.0 / 11.0;
-    t = t * z + 1.0 / 9.0;
-    t = t * z + 1.0 / 7.0;                                       // 1/7 + z/9 + ...
-    dd p = dd_add(dd{kFifthHi, kFifthLo}, dd_two_prod(z, t));    // 1/5 + z (1/7 + ...)
-    p = dd_add(dd_mul(s2, p), dd{kThirdHi, kThirdLo});
-    p = dd_add(dd_mul(s2, p), dd{1.0, 0.0});
-    const dd lm = dd_mul(p, s);                                  // atanh(s)
+    const dd p = dd_two_prod(m, c);
+    const dd r = dd_two_sum(p.hi - 1.0, p.lo);  // m c - 1 (p.hi - 1 is exact)
+    const double rh = r.hi;
+    const dd z = dd_two_prod(rh, rh);
+    double q = fma(rh, -1.0 / 10.0, 1.0 / 9.0);
+    q = fma(rh, q, -1.0 / 8.0);
+    q = fma(rh, q, 1.0 / 7.0);
+    q = fma(rh, q, -1.0 / 6.0);
+    q = fma(rh, q, 1.0 / 5.0);
+    q = fma(rh, q, -1.0 / 4.0);
+    q = fma(rh, q, 1.0 / 3.0);
+    // -r^2/2 = -z/2 - rh r.lo; here the low words and the terms from r^3 on
+    double lo = fma(z.hi * rh, q, fma(-rh, r.lo, fma(-0.5, z.lo, r.lo)));
+    const dd a = dd_two_sum(rh, -0.5 * z.hi);
     const double ed = (double)e;
-    dd l = dd_two_prod(ed, kLn2Hi);
-    l.lo += ed * kLn2Lo;
-    l = dd_fast_two_sum(l.hi, l.lo);
-    const dd y = dd_add(l, dd{2.0 * lm.hi, 2.0 * lm.lo});
+    const dd l = dd_two_prod(ed, kLn2Hi);
+    lo += fma(ed, kLn2Lo, ll + l.lo) + a.lo;
+    const dd b = dd_two_sum(l.hi, lh), s = dd_two_sum(b.hi, a.hi);
     double out;
-    if (ziv_round(y, &out)) return out;
+    if (ziv_round(dd_fast_two_sum(s.hi, s.lo + (b.lo + lo)), &out)) return out;
   }
   return cr_log_dd(x);
 }

@@ -110,7 +110,7 @@ __device__ __forceinline__ void buf_st(bufres r, uint32_t o, float v) {
 
 
 // u-bins of the guide tables of the cumulative rows (a power of two, so u * kGuide is exact)
-constexpr int kGuide = 64;
+constexpr int kGuide = 256;
 
 // Device copy of the tables plus their grid constants.
 struct Tabs {
@@ -312,7 +312,9 @@ __device__ __forceinline__ void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t
 __device__ __forceinline__ double unit_open(uint64_t r) { return ((double)(r >> 11) + 0.5) * 0x1.0p-53; }
 
 // optical depth at which the next reaction happens: P = 1 - exp(-tau) uniform (Sec. 3)
-__device__ __forceinline__ double optical_depth(uint64_t r) { return -cr_log(unit_open(r)); }
+__device__ __forceinline__ double optical_depth(uint64_t r, const double* mtab = c_mathtab) {
+  return -cr_log(unit_open(r), mtab);
+}
 
 // ---------------------------------------------------------------------------
 // fields at a point (FP64); the grid kind gathers FP32 node values with CIC weights
@@ -849,37 +851,48 @@ __device__ __forceinline__ int row_inverse(const double* __restrict__ P, int n, 
   return lo;
 }
 
-// chi from P_chi at the emitter's eta (rows i, i+1 blended in ln eta); false below the cut-off
-__device__ inline bool sample_chi(const Tabs& tb, double eta, double u, double* chi) {
-  const double leta = cr_log(eta);
+// chi from P_chi at the emitter's eta (rows i, i+1 blended in ln eta); false below the cut-off.
+// Both rows are searched together: each round of dependent loads (row ends and guides, probes,
+// segment ends) is a trip to L2, and one row after the other doubled them.
+__device__ inline bool sample_chi(const Tabs& tb, double eta, double u, double* chi,
+                                  const double* mtab = c_mathtab) {
+  const double leta = cr_log(eta, mtab);
   const double s = (leta - tb.le0) / tb.dle;
+  const bool below = !(s > 0.0), above = s >= tb.n_eta - 1;
+  const int i = below ? 0 : above ? tb.n_eta - 1 : (int)floor(s);
+  const int i1 = below || above ? i : i + 1;
+  const double* Pa = tb.P + (size_t)i * tb.n_chi;
+  const double* Pb = tb.P + (size_t)i1 * tb.n_chi;
+  const uint16_t* ga = tb.gP + (size_t)i * (kGuide + 1);
+  const uint16_t* gb = tb.gP + (size_t)i1 * (kGuide + 1);
+  const int g = (int)(u * kGuide);
+  const double pa0 = Pa[0], pb0 = Pb[0];
+  int la = ga[g], ha = ga[g + 1] + 1, lb = gb[g], hb = gb[g + 1] + 1;  // as in row_inverse
+  const double ca = tb.lnchi_min[i], cb = tb.lnchi_min[i1], da = tb.dlnchi[i], db = tb.dlnchi[i1];
+  if (u <= pa0 || u <= pb0) return false;
+  while (ha - la > 1 || hb - lb > 1) {
+    const int ma = (la + ha) >> 1, mb = (lb + hb) >> 1;
+    const double va = Pa[ma], vb = Pb[mb];
+    if (ha - la > 1) {
+      if (va < u) la = ma; else ha = ma;
+    }
+    if (hb - lb > 1) {
+      if (vb < u) lb = mb; else hb = mb;
+    }
+  }
+  const double a0 = Pa[la], a1 = Pa[ha], b0 = Pb[lb], b1 = Pb[hb];
+  const double qa = ca + (la + (u - a0) / (a1 - a0)) * da;
   double lnchi;
-  auto Q = [&](int r, double* q) {
-    const double* P = tb.P + (size_t)r * tb.n_chi;
-    if (u <= P[0]) return false;
-    double fr;
-    const int j = row_inverse(P, tb.n_chi, u, &fr, tb.gP + (size_t)r * (kGuide + 1));
-    *q = tb.lnchi_min[r] + (j + fr) * tb.dlnchi[r];
-    return true;
-  };
-  if (!(s > 0.0)) {
-    double q0;
-    if (!Q(0, &q0)) return false;
-    lnchi = q0 + 2.0 * (leta - tb.le0);  // classical scaling chi ~ eta^2 below the table
-  } else if (s >= tb.n_eta - 1) {
-    double q1;
-    if (!Q(tb.n_eta - 1, &q1)) return false;
-    lnchi = q1 + (leta - (tb.le0 + (tb.n_eta - 1) * tb.dle));  // fixed 2 chi/eta above it
+  if (below) {
+    lnchi = qa + 2.0 * (leta - tb.le0);  // classical scaling chi ~ eta^2 below the table
+  } else if (above) {
+    lnchi = qa + (leta - (tb.le0 + (tb.n_eta - 1) * tb.dle));  // fixed 2 chi/eta above it
   } else {
-    const int i = (int)floor(s);
     const double w = s - i;
-    double qa, qb;
-    const bool oka = Q(i, &qa);
-    const bool okb = Q(i + 1, &qb);
-    if (!oka || !okb) return false;
+    const double qb = cb + (lb + (u - b0) / (b1 - b0)) * db;
     lnchi = (1.0 - w) * qa + w * qb;
   }
-  *chi = cr_exp(lnchi);
+  *chi = cr_exp(lnchi, mtab);
   return true;
 }
 

@@ -51,6 +51,7 @@ struct MultiShared {
   qed_field F;
   double log[2 * kLogTab];
   __attribute__((aligned(16))) double sct[kSinCosTab * kSinCosWords];
+  __attribute__((aligned(16))) double math[kMathTab];
   int64_t scan[kMultiBlock];
   long long fx[3][4];                   // field work, radiated energy, emission defect
   unsigned long long cnt[MC_COUNT];
@@ -352,6 +353,7 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
   }
   if (!MIXED) stage_logtab(sh.log);
   if (!MIXED && ZeroField<FK>::pw) stage_sctab(sh.sct);
+  if (emit) stage_mathtab(sh.math);
   zero_shared(sh);
   const int64_t s0 = uni64(m.mc->s0), chunk = uni32(m.mc->lep_chunk);
   const double dt = a.sc.dt;
@@ -377,6 +379,7 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
     __syncthreads();
     const float tpf0 = (float)sh.F.p[2], psif_max = (float)sh.F.p[1];
     FieldK fK{uni_f64(field_k(sh.F).pi_over_len)};
+    const double eps_min = uni_f64(pair_eps_min(sh.F, a.tb.cp_min));
 
     const int64_t per = (hi - lo + kMultiWaves - 1) / kMultiWaves;
     int64_t next = lo + wave * per;
@@ -393,27 +396,6 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
     int n_wait = 0, n_ready = 0;  // leptons in the pool: waiting to emit, ready to go on
     double eta = 0.0, wh = 0.0, wl = 0.0, rh = 0.0, rl = 0.0;
     unsigned n_field = 0, n_range = 0, n_bad = 0, n_emit = 0, n_null = 0, n_drop = 0, lsteps = 0, psteps = 0;
-    // the wave's new photons (lanes with `child`) into the photon arrays, first stepped in step s0 + nb
-    auto append = [&](bool child, double cx, double cy, double cz, const Emission& em, int nb) {
-      const qed_species& G = I.s[2];
-      const long long ps = wave_reserve(child, G.count_dev);
-      uint64_t* lword = nullptr;
-      if (child) {
-        if (ps < G.capacity) {
-          const uint32_t wn = store_photon<FK, MIXED>(G, ps, moff + ps, env.d3, cx, cy, cz, em, (int32_t)(s0 + nb),
-                                                      sh.F, a.tb.cp_min, a.sc, a.win, a.rec);
-          psteps += m.k - nb;
-          // the photon kernel writes the live masks; without it they are set here
-          if (!pairs && !window_over(wn, s0 + nb)) lword = a.lmask + A.lmask_off + ps / kWinGroup;
-        } else {
-          ++n_drop;
-          long long l[4];
-          fix_split(sqrt(em.kx * em.kx + em.ky * em.ky + em.kz * em.kz), l);
-          fix_atomic_add(a.acc[ii].fx[FX_DROPPED], l);
-        }
-      }
-      if (!pairs) wave_or_bit(lword, (int)(ps % kWinGroup));
-    };
     for (;;) {
       unsigned long long idle = __ballot(!busy);
       if (n_ready && idle) {
@@ -456,8 +438,8 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
         next = min(w1, next + __popcll(idle));
       }
       if (__ballot(busy) == 0ull && n_wait == 0) {
-        if (next >= w1 && n_ready == 0) break;
-        continue;
+        if (next >= w1 && n_ready == 0 && n_staged == 0) break;
+        if (n_staged == 0) continue;
       }
       // one step of every lane that does not wait for its emission
       if (busy && !pend && n < m.k) {
@@ -503,6 +485,9 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
         }
         busy = false;
       }
+      Emission em;
+      em.child = false;
+      double cx = 0.0, cy = 0.0, cz = 0.0;
       if (emit) {
         const bool more = next < w1 || n_ready > 0;  // a lane given up can be filled again
         if (more) {
@@ -532,11 +517,9 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
             }
             n_wait -= take;
           }
-          Emission em;
-          em.child = false;
-          double cx = 0.0, cy = 0.0, cz = 0.0;
           if (pend) {
-            em = emit_photon<MIXED>(a.tb, st, eta, uid, (uint64_t)(s0 + n - 1), I.seed, I.key_instance);
+            em = emit_photon<MIXED>(a.tb, st, eta, uid, (uint64_t)(s0 + n - 1), I.seed, I.key_instance,
+                                    sh.math);
             moving = false;
             cx = st.x;
             cy = st.y;
@@ -560,26 +543,38 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
             const unsigned long long out = __ballot(em.child);
             if (em.child) staged.put(n_staged + __popcll(out & below), cx, cy, cz, em, n);
             n_staged += __popcll(out);
-          } else {
-            append(em.child, cx, cy, cz, em, n);
           }
         }
       }
-      if (n_staged >= 64) {
-        n_staged -= 64;
-        Emission em;
-        double cx, cy, cz;
-        int nb;
-        staged.get(n_staged + lane, cx, cy, cz, em, nb);
-        append(true, cx, cy, cz, em, nb);
+      // new photons into the photon arrays: this pass's, or the staged ones (64, or the last)
+      bool child = em.child;
+      int nb = n;
+      if (stage) {
+        const int take = n_staged >= 64 || __ballot(busy) == 0ull ? min(n_staged, 64) : 0;
+        n_staged -= take;
+        child = lane < take;
+        if (child) staged.get(n_staged + lane, cx, cy, cz, em, nb);
       }
-    }
-    if (n_staged) {
-      Emission em{};
-      double cx = 0.0, cy = 0.0, cz = 0.0;
-      int nb = 0;
-      if (lane < n_staged) staged.get(lane, cx, cy, cz, em, nb);
-      append(lane < n_staged, cx, cy, cz, em, nb);
+      if (__ballot(child)) {
+        const qed_species& G = I.s[2];
+        const long long ps = wave_reserve(child, G.count_dev);
+        uint64_t* lword = nullptr;
+        if (child) {
+          if (ps < G.capacity) {
+            const uint32_t wn = store_photon<FK, MIXED>(G, ps, moff + ps, env.d3, cx, cy, cz, em, (int32_t)(s0 + nb),
+                                                        sh.F, eps_min, a.tb.cp_min, a.sc, a.win, a.rec);
+            psteps += m.k - nb;
+            // the photon kernel writes the live masks; without it they are set here
+            if (!pairs && !window_over(wn, s0 + nb)) lword = a.lmask + A.lmask_off + ps / kWinGroup;
+          } else {
+            ++n_drop;
+            long long l[4];
+            fix_split(sqrt(em.kx * em.kx + em.ky * em.ky + em.kz * em.kz), l);
+            fix_atomic_add(a.acc[ii].fx[FX_DROPPED], l);
+          }
+        }
+        if (!pairs) wave_or_bit(lword, (int)(ps % kWinGroup));
+      }
     }
     count_wave(sh, MC_FIELD, n_field);
     count_wave(sh, MC_RANGE, n_range);

@@ -308,7 +308,8 @@ struct Emission {
 };
 template <bool MIXED>
 __device__ __forceinline__ Emission emit_photon(const Tabs& tb, LepState<MIXED>& st, double eta, uint64_t uid,
-                                                uint64_t step, uint64_t seed, uint64_t key) {
+                                                uint64_t step, uint64_t seed, uint64_t key,
+                                                const double* mtab = c_mathtab) {
   Emission m;
   m.child = false;
   m.kx = m.ky = m.kz = m.tau = m.defect = 0.0;
@@ -323,7 +324,7 @@ __device__ __forceinline__ Emission emit_photon(const Tabs& tb, LepState<MIXED>&
   }
   const double g1 = st.g;
   double chi;
-  if (sample_chi(tb, eta, unit_open(r[0]), &chi)) {
+  if (sample_chi(tb, eta, unit_open(r[0]), &chi, mtab)) {
     const double xi = 2.0 * chi / eta;
     double ux, uy, uz;
     if constexpr (MIXED) {
@@ -353,10 +354,10 @@ __device__ __forceinline__ Emission emit_photon(const Tabs& tb, LepState<MIXED>&
     m.defect = g2 + eps - g1;
     st.g = g2;
     m.child = true;
-    m.tau = optical_depth(r[3]);
+    m.tau = optical_depth(r[3], mtab);
     m.uid = r[2];
   }
-  st.tau = optical_depth(r[1]);
+  st.tau = optical_depth(r[1], mtab);
   return m;
 }
 
@@ -365,7 +366,8 @@ __device__ __forceinline__ Emission emit_photon(const Tabs& tb, LepState<MIXED>&
 template <int FK, bool MIXED>
 __device__ __forceinline__ uint32_t store_photon(const qed_species& G, long long slot, int64_t pk, bool d3, double cx,
                                                  double cy, double cz, const Emission& m, int32_t birth,
-                                                 const qed_field& F, double cp_min, const StepConst& sc,
+                                                 const qed_field& F, double eps_min, double cp_min,
+                                                 const StepConst& sc,
                                                  uint32_t* win, void* rec) {
   using Real = typename std::conditional<MIXED, float, double>::type;
   as_global((Real*)G.x_dev)[slot] = (Real)cx;
@@ -380,7 +382,7 @@ __device__ __forceinline__ uint32_t store_photon(const qed_species& G, long long
   // the steps in which the new photon can create a pair, from its stored state
   const double sx = (double)(Real)cx, sy = (double)(Real)cy;
   const double skx = (double)(Real)m.kx, sky = (double)(Real)m.ky, skz = (double)(Real)m.kz;
-  const uint32_t wn = pack_window(photon_window(F, pair_eps_min(F, cp_min), cp_min, sc.t0, sc.dt, skx, sky, skz, sx,
+  const uint32_t wn = pack_window(photon_window(F, eps_min, cp_min, sc.t0, sc.dt, skx, sky, skz, sx,
                                                 birth));
   win[pk] = wn;
   make_photon_rec<MIXED, FK>(((PhotonRecT<MIXED, FK>*)rec)[pk], F, sc.t0, sc.dt, skx, sky, skz, sx, sy, birth);

@@ -652,7 +652,7 @@ __global__ __launch_bounds__(256) void k_emit_events(StepArgs a) {
     if (child) {
       if (slot < G.capacity) {
         const uint32_t wn = store_photon<FK, MIXED>(G, slot, moff + slot, d3, cx, cy, cz, em, (int32_t)(step + 1), F,
-                                                    a.tb.cp_min, a.sc, a.win, a.rec);
+                                                    pair_eps_min(F, a.tb.cp_min), a.tb.cp_min, a.sc, a.win, a.rec);
         if (!window_over(wn, step + 1)) lword = a.lmask + lmoff + slot / kWinGroup;
       } else {
         n_drop = 1;

@@ -508,6 +508,7 @@ qed_status enqueue_multi(const qed_tables* tb, qed_workspace* ws, const qed_step
       ws->multi_fit[w] = multi_blocks_per_cu(ws->field_kind, w, m.s.tb.n_eta, m.s.tb.n_cp, mixed);
     std::memcpy(ws->multi_fit_key, key, sizeof(key));
   }
+  m.cus = ws->cus;
   m.lep_grid = ws->cus * ws->multi_fit[0];
   m.ph_grid = ws->cus * ws->multi_fit[1];
   launch_multi(ws->field_kind, m, mixed, s);

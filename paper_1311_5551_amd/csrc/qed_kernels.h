@@ -38,6 +38,7 @@ struct MultiArgs {
   int round;             // 0: all particles; later: those made in the round before
   int lep_grid, ph_grid; // blocks of the lepton and photon kernels
   int n_tab;             // LDS words of the rate table
+  int cus;
 };
 
 // retirement of photons at compaction (pair window over): the photon spectrum they are counted in

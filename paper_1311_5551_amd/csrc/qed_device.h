@@ -613,28 +613,98 @@ __device__ inline int2 photon_window(const qed_field& F, double eps_min, double 
   return make_int2(ilo, ihi);
 }
 
+// The nodes and weights of a cell coordinate g along one axis of n periodic nodes, for the two
+// staggerings [0] offset 0 and [1] offset 1/2: nodes a and b around the point, w the weight of b.
+// `near`: both pairs are neighbours in memory, no node wrapped round (almost every particle).
+struct CicAxis {
+  int a[2], b[2];
+  double w[2];
+  bool near;
+};
+// The integer-valued f modulo n, in [0, n), without the 64-bit remainder, which is a software loop
+// on the GPU (inlined for every node it was most of the gather's code): the first quotient is off
+// by at most 2^-53 of itself, so after f - q n (exact in one fused step, |f| < 2^63) a second
+// reduction ends within one n of the range.  0 for positions beyond that or not finite.
+__device__ __forceinline__ int wrap_far(double f, int n) {
+  const double dn = (double)n;
+  double r = fma(-floor(f / dn), dn, f);
+  r = fma(-floor(r / dn), dn, r);
+  r = r < 0.0 ? r + dn : r >= dn ? r - dn : r;
+  return fabs(f) < 0x1p63 ? (int)r : 0;
+}
+__device__ __forceinline__ CicAxis cic_axis(double g, int n) {
+  CicAxis A;
+  const double gh = g - 0.5, f0 = floor(g), fh = floor(gh);
+  A.w[0] = g - f0;
+  A.w[1] = gh - fh;
+  A.near = fh >= 0.0 && f0 + 1.0 < (double)n;
+  if (A.near) {
+    A.a[0] = (int)f0;
+    A.a[1] = (int)fh;
+    A.b[0] = A.a[0] + 1;
+    A.b[1] = A.a[1] + 1;
+  } else {
+    A.a[0] = wrap_far(f0, n);
+    A.a[1] = wrap_far(fh, n);
+    A.b[0] = A.a[0] + 1 == n ? 0 : A.a[0] + 1;
+    A.b[1] = A.a[1] + 1 == n ? 0 : A.a[1] + 1;
+  }
+  return A;
+}
+// two neighbouring node values in one load (4- or 8-byte aligned)
+template <class T>
+struct NodePair {
+  typedef T v __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+};
+
+// Node values around a point for the six components, at their Yee staggering: v[c] = the values at
+// (a, ja), (b, ja), (a, jb), (b, jb).  Rows are read as pairs of neighbours: 12 loads instead of 24.
+template <class T>
+__device__ __forceinline__ void cic_nodes(const qed_field& F, const T* base, const CicAxis& X, const CicAxis& Y,
+                                          T v[6][4]) {
+  constexpr int hx[6] = {1, 0, 0, 0, 1, 1}, hy[6] = {0, 1, 0, 1, 0, 1};
+  const uint64_t plane = (uint64_t)F.nx * (uint64_t)F.ny;
+  const uint32_t nx = (uint32_t)F.nx;  // node indices stay below 2^31
+  const uint32_t ra[2] = {(uint32_t)Y.a[0] * nx, (uint32_t)Y.a[1] * nx};
+  const uint32_t rb[2] = {(uint32_t)Y.b[0] * nx, (uint32_t)Y.b[1] * nx};
+  if (X.near) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      gptr<const T> g = as_global(base + c * plane);
+      const auto lo = *(gptr<const typename NodePair<T>::v>)(g + (ra[hy[c]] + (uint32_t)X.a[hx[c]]));
+      const auto hi = *(gptr<const typename NodePair<T>::v>)(g + (rb[hy[c]] + (uint32_t)X.a[hx[c]]));
+      v[c][0] = lo[0];
+      v[c][1] = lo[1];
+      v[c][2] = hi[0];
+      v[c][3] = hi[1];
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      gptr<const T> g = as_global(base + c * plane);
+      v[c][0] = g[ra[hy[c]] + (uint32_t)X.a[hx[c]]];
+      v[c][1] = g[ra[hy[c]] + (uint32_t)X.b[hx[c]]];
+      v[c][2] = g[rb[hy[c]] + (uint32_t)X.a[hx[c]]];
+      v[c][3] = g[rb[hy[c]] + (uint32_t)X.b[hx[c]]];
+    }
+  }
+}
+
 // First-order (cloud-in-cell) gather of the six components at (x, y): bilinear weights over the
 // four nodes around the point on each component's staggered grid (Yee offsets), periodic; node
 // values of type T (FP32 refreshed grid, FP64 solver grid).
 template <class T>
 __device__ __forceinline__ void cic_gather6(const qed_field& F, const T* base, double x, double y, double E[3],
                                             double B[3]) {
-  const double ox[6] = {0.5, 0.0, 0.0, 0.0, 0.5, 0.5};
-  const double oy[6] = {0.0, 0.5, 0.0, 0.5, 0.0, 0.5};
-  const int64_t plane = (int64_t)F.nx * F.ny;
+  constexpr int hx[6] = {1, 0, 0, 0, 1, 1}, hy[6] = {0, 1, 0, 1, 0, 1};
+  const CicAxis X = cic_axis((x - F.x0) / F.dx, F.nx), Y = cic_axis((y - F.y0) / F.dy, F.ny);
+  T g[6][4];
+  cic_nodes(F, base, X, Y, g);
   double v[6];
 #pragma unroll
   for (int c = 0; c < 6; ++c) {
-    const double gx = (x - F.x0) / F.dx - ox[c];
-    const double gy = (y - F.y0) / F.dy - oy[c];
-    const double fx = floor(gx), fy = floor(gy);
-    const double wx = gx - fx, wy = gy - fy;
-    const int64_t i0 = (int64_t)fx, j0 = (int64_t)fy;
-    const int64_t ia = wrap_index(i0, F.nx), ib = wrap_index(i0 + 1, F.nx);
-    const int64_t ja = wrap_index(j0, F.ny), jb = wrap_index(j0 + 1, F.ny);
-    gptr<const T> g = as_global(base + c * plane);
-    const double g00 = g[ja * F.nx + ia], g10 = g[ja * F.nx + ib];
-    const double g01 = g[jb * F.nx + ia], g11 = g[jb * F.nx + ib];
+    const double wx = X.w[hx[c]], wy = Y.w[hy[c]];
+    const double g00 = g[c][0], g10 = g[c][1], g01 = g[c][2], g11 = g[c][3];
     v[c] = (1.0 - wx) * (1.0 - wy) * g00 + wx * (1.0 - wy) * g10 + (1.0 - wx) * wy * g01 + wx * wy * g11;
   }
   E[0] = v[0];

@@ -81,23 +81,17 @@ __device__ __forceinline__ void field_at32(const qed_field& F, const FieldK& K, 
       B[k] = (float)b[k];
     }
   } else if (FK == QED_FIELD_GRID_CP_STANDING) {
-    const float ox[6] = {0.5f, 0.0f, 0.0f, 0.0f, 0.5f, 0.5f};
-    const float oy[6] = {0.0f, 0.5f, 0.0f, 0.5f, 0.0f, 0.5f};
-    const int64_t plane = (int64_t)F.nx * F.ny;
+    constexpr int hx[6] = {1, 0, 0, 0, 1, 1}, hy[6] = {0, 1, 0, 1, 0, 1};
     // cell coordinates in FP64 (large domains), weights in FP32
-    const double cxd = (x - F.x0) / F.dx, cyd = (y - F.y0) / F.dy;
+    const CicAxis X = cic_axis((x - F.x0) / F.dx, F.nx), Y = cic_axis((y - F.y0) / F.dy, F.ny);
+    float g[6][4];
+    cic_nodes(F, (const float*)F.grid_dev, X, Y, g);
     float v[6];
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
-      const double gx = cxd - ox[c], gy = cyd - oy[c];
-      const double fx = floor(gx), fy = floor(gy);
-      const float wx = (float)(gx - fx), wy = (float)(gy - fy);
-      const int64_t i0 = (int64_t)fx, j0 = (int64_t)fy;
-      const int64_t ia = wrap_index(i0, F.nx), ib = wrap_index(i0 + 1, F.nx);
-      const int64_t ja = wrap_index(j0, F.ny), jb = wrap_index(j0 + 1, F.ny);
-      gptr<const float> g = as_global((const float*)F.grid_dev + c * plane);
-      v[c] = (1.0f - wx) * (1.0f - wy) * g[ja * F.nx + ia] + wx * (1.0f - wy) * g[ja * F.nx + ib] +
-             (1.0f - wx) * wy * g[jb * F.nx + ia] + wx * wy * g[jb * F.nx + ib];
+      const float wx = (float)X.w[hx[c]], wy = (float)Y.w[hy[c]];
+      v[c] = (1.0f - wx) * (1.0f - wy) * g[c][0] + wx * (1.0f - wy) * g[c][1] + (1.0f - wx) * wy * g[c][2] +
+             wx * wy * g[c][3];
     }
     E[0] = v[0];
     E[1] = v[1];

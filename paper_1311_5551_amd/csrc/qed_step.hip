@@ -392,7 +392,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
       } else {
         st.xl = st.yl = st.zl = st.uxl = st.uyl = st.uzl = 0.0f;
       }
-      lepton_gamma(st);
       return st;
     };
     auto store_position = [&](unsigned off, const LepState<MIXED>& st) {
@@ -407,7 +406,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
     };
     // full step of one lepton; returns true (and its eta) when its optical depth reached zero
     auto full = [&](unsigned off, LepState<MIXED>& st, double* eta_out, double* wk, double* rd) -> bool {
-      st.tau = buf_ld<double>(C.tau, off * 8u);
       const bool pend = lepton_full<FK, MIXED>(st, sF, fK, t, a.sc, a.tb, env, eta_out, wk, rd, uacc[1], uacc[2],
                                                [&](double x0, double y0, double x1, double y1, double vz) {
         // field feedback: the current of this move onto the solver's grid (or the chunk's LDS box)
@@ -449,9 +447,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
         double eta = 0.0, wk = 0.0, rd = 0.0;
         if ((int64_t)off < rem) {
           LepState<MIXED> st = load_state(off);
+          lepton_gamma(st);
           in = near_pulse(t, tpf0, psif_max, (float)st.x);
           if (in) {
             ++uacc[0];
+            st.tau = buf_ld<double>(C.tau, off * 8u);
             pend = full(off, st, &eta, &wk, &rd);
           } else {
             const DriftMove<MIXED> mv = drift_move(st, env);
@@ -467,15 +467,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
         if (emit) enqueue(off, pend, eta);  // emit is uniform over the block
       }
     } else {
+      // the next lepton's words in flight while one is stepped
+      LepState<MIXED> nx = load_state(threadIdx.x);
+      nx.tau = buf_ld<double>(C.tau, threadIdx.x * 8u);
 #pragma unroll 1
       for (int j = 0; j < PPT; ++j) {
         const unsigned off = threadIdx.x + j * B;
         bool pend = false;
         double eta = 0.0, wk = 0.0, rd = 0.0;
         const bool in = (int64_t)off < rem;
+        LepState<MIXED> st = nx;
+        if (j + 1 < PPT) {
+          nx = load_state(off + B);
+          nx.tau = buf_ld<double>(C.tau, (off + B) * 8u);
+        }
         if (in) {
           ++uacc[0];
-          LepState<MIXED> st = load_state(off);
+          lepton_gamma(st);
           pend = full(off, st, &eta, &wk, &rd);
         }
         if (__ballot(in)) {
@@ -838,79 +846,119 @@ __global__ __launch_bounds__(256) void k_photon(StepArgs a) {
         }
       }
     }
-    uint64_t M[PPT];  // this chunk's masks of the wave's groups (wave-uniform: scalar registers)
-    bool any = false;
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
+    auto mask_of = [&](int j) -> uint64_t {  // the wave's group j of this chunk
       const int src = (int)(c - m0) * PPT + j;
-      M[j] = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mrun >> 32), src) << 32) |
+      return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mrun >> 32), src) << 32) |
              (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mrun, src);
-      any = any || M[j] != 0ull;
-    }
-    if (!any) continue;
-    // phase 1: the window, the record and the optical depth of every live slot of the chunk,
-    // issued together, so that a chunk costs one memory round trip (loads past the chunk's live
-    // slots return zero)
-    uint32_t wv[PPT];
-    uint32_t q[PPT][kRecDw];
-    double tv[PPT];
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-      wv[j] = kWinEmpty;
-      tv[j] = 0.0;
-      if ((M[j] >> lane) & 1ull) {
+    };
+    // the window, the record and the optical depth of a live slot, issued together (loads past the
+    // chunk's live slots return zero)
+    auto fetch = [&](int j, uint64_t M, uint32_t& w, uint32_t (&q)[kRecDw], double& tv) {
+      w = kWinEmpty;
+      tv = 0.0;
+      if ((M >> lane) & 1ull) {
         const unsigned off = threadIdx.x + j * B;
-        wv[j] = (uint32_t)buf_ld<int32_t>(rwin, off * 4u);
-        load_dwords<kRecDw>(rrec, off * (unsigned)sizeof(Rec), q[j]);
-        tv[j] = buf_ld<double>(rtau, off * 8u);
+        w = (uint32_t)buf_ld<int32_t>(rwin, off * 4u);
+        load_dwords<kRecDw>(rrec, off * (unsigned)sizeof(Rec), q);
+        tv = buf_ld<double>(rtau, off * 8u);
       }
-    }
-    unsigned gmask = 0;
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
+    };
+    // the slot's counters and its group's mask for the next step; true inside the window.  The mask
+    // loses the photons whose window is over then (a photon's window only ends; the slots past the
+    // step's photons keep their bits: the emission pass of this step may have set them)
+    auto visit = [&](int j, uint64_t M, uint32_t w) -> bool {
       const bool exists = (int64_t)(threadIdx.x + j * B) < rem;
-      const bool bit = (M[j] >> lane) & 1ull;
+      const bool bit = (M >> lane) & 1ull;
       if (exists && bit) ++uacc[4];
-      if (exists && in_window(wv[j], step)) gmask |= 1u << j;
-      // the mask for the next step loses the photons whose window is over then (a photon's
-      // window only ends; the slots past the step's photons keep their bits: the emission pass
-      // of this step may have set them)
-      if (M[j] != 0ull) {  // wave-uniform
-        const uint64_t nm = __ballot(bit && (!exists || !window_over(wv[j], step + 1)));
-        if (nm != M[j] && lane == 0) LM[(k0 + threadIdx.x + j * B) / kWinGroup] = nm;
+      if (M != 0ull) {  // wave-uniform
+        const uint64_t nm = __ballot(bit && (!exists || !window_over(w, step + 1)));
+        if (nm != M && lane == 0) LM[(k0 + threadIdx.x + j * B) / kWinGroup] = nm;
       }
-    }
-    if (__ballot(gmask != 0) != 0ull) {
-      uacc[3] += __popc(gmask);
-      // one photon inside its window, from the dwords of its record and its optical depth
-      auto eval = [&](unsigned off, const uint32_t* w, double tau) -> bool {
-        auto dbl = [&](int i) { return __hiloint2double((int)w[i + 1], (int)w[i]); };
-        PairRate r;
-        if constexpr (FK == QED_FIELD_LP_PULSE) {
-          if (MIXED)
-            r = pair_rate_pw<MIXED>(sF, fK, a.tb, sT, sT32, sLog, a.sc.a_pair, step, dbl(0),
-                                    (double)__uint_as_float(w[2]), (double)__uint_as_float(w[3]), uacc[1]);
-          else
-            r = pair_rate_pw<MIXED>(sF, fK, a.tb, sT, sT32, sLog, a.sc.a_pair, step, dbl(0), dbl(2), dbl(4), uacc[1]);
-        } else if (MIXED) {
-          r = pair_rate<FK, MIXED>(sF, fK, a.tb, sT, sT32, sLog, rate, step, t, dt, (Real)__uint_as_float(w[0]),
-                                   (Real)__uint_as_float(w[1]), (Real)__uint_as_float(w[2]),
-                                   NEED_X ? (Real)__uint_as_float(w[3]) : Real(0),
-                                   NEED_Y ? (Real)__uint_as_float(w[4]) : Real(0), NEED_X ? (int32_t)w[5] : 0, uacc[1]);
-        } else {
-          r = pair_rate<FK, MIXED>(sF, fK, a.tb, sT, sT32, sLog, rate, step, t, dt, (Real)dbl(0), (Real)dbl(2),
-                                   (Real)dbl(4), NEED_X ? (Real)dbl(6) : Real(0), NEED_Y ? (Real)dbl(8) : Real(0),
-                                   NEED_X ? (int32_t)w[10] : 0, uacc[1]);
-        }
-        return decrement(off, r, tau);
-      };
-      // phase 2: the photons inside their windows, in place
+      const bool in = exists && in_window(w, step);
+      if (in) ++uacc[3];
+      return in;
+    };
+    // one photon inside its window, from the dwords of its record and its optical depth
+    auto eval = [&](unsigned off, const uint32_t* w, double tau) -> bool {
+      auto dbl = [&](int i) { return __hiloint2double((int)w[i + 1], (int)w[i]); };
+      PairRate r;
+      if constexpr (FK == QED_FIELD_LP_PULSE) {
+        if (MIXED)
+          r = pair_rate_pw<MIXED>(sF, fK, a.tb, sT, sT32, sLog, a.sc.a_pair, step, dbl(0),
+                                  (double)__uint_as_float(w[2]), (double)__uint_as_float(w[3]), uacc[1]);
+        else
+          r = pair_rate_pw<MIXED>(sF, fK, a.tb, sT, sT32, sLog, a.sc.a_pair, step, dbl(0), dbl(2), dbl(4), uacc[1]);
+      } else if (MIXED) {
+        r = pair_rate<FK, MIXED>(sF, fK, a.tb, sT, sT32, sLog, rate, step, t, dt, (Real)__uint_as_float(w[0]),
+                                 (Real)__uint_as_float(w[1]), (Real)__uint_as_float(w[2]),
+                                 NEED_X ? (Real)__uint_as_float(w[3]) : Real(0),
+                                 NEED_Y ? (Real)__uint_as_float(w[4]) : Real(0), NEED_X ? (int32_t)w[5] : 0, uacc[1]);
+      } else {
+        r = pair_rate<FK, MIXED>(sF, fK, a.tb, sT, sT32, sLog, rate, step, t, dt, (Real)dbl(0), (Real)dbl(2),
+                                 (Real)dbl(4), NEED_X ? (Real)dbl(6) : Real(0), NEED_Y ? (Real)dbl(8) : Real(0),
+                                 NEED_X ? (int32_t)w[10] : 0, uacc[1]);
+      }
+      return decrement(off, r, tau);
+    };
+
+    if constexpr (FK == QED_FIELD_LP_PULSE) {
+      // the records are short: those of the whole chunk are loaded at once, so that a chunk costs
+      // one memory round trip
+      uint64_t M[PPT];  // wave-uniform: scalar registers
+      bool any = false;
 #pragma unroll
       for (int j = 0; j < PPT; ++j) {
-        const unsigned off = threadIdx.x + j * B;
-        bool pend = false;
-        if ((gmask >> j) & 1u) pend = eval(off, q[j], tv[j]);
-        enqueue(off, pend);
+        M[j] = mask_of(j);
+        any = any || M[j] != 0ull;
+      }
+      if (!any) continue;
+      uint32_t wv[PPT];
+      uint32_t q[PPT][kRecDw];
+      double tv[PPT];
+#pragma unroll
+      for (int j = 0; j < PPT; ++j) fetch(j, M[j], wv[j], q[j], tv[j]);
+      unsigned gmask = 0;
+#pragma unroll
+      for (int j = 0; j < PPT; ++j)
+        if (visit(j, M[j], wv[j])) gmask |= 1u << j;
+      if (__ballot(gmask != 0) != 0ull) {
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+          const unsigned off = threadIdx.x + j * B;
+          bool pend = false;
+          if ((gmask >> j) & 1u) pend = eval(off, q[j], tv[j]);
+          enqueue(off, pend);
+        }
+      }
+    } else {
+      // longer records, and a gather or trigonometry per photon: one photon at a time with the next
+      // one's words in flight.  (All of a chunk's at once took 256 registers and left one wave per
+      // SIMD.)
+      uint64_t M = mask_of(0), Mn = 0ull;
+      uint32_t w, wn = kWinEmpty;
+      uint32_t q[kRecDw], qn[kRecDw];
+      double tv, tn = 0.0;
+      fetch(0, M, w, q, tv);
+#pragma unroll 1
+      for (int j = 0; j < PPT; ++j) {
+        if (j + 1 < PPT) {
+          Mn = mask_of(j + 1);
+          fetch(j + 1, Mn, wn, qn, tn);
+        }
+        if (M != 0ull) {
+          const bool in = visit(j, M, w);
+          if (__ballot(in) != 0ull) {
+            const unsigned off = threadIdx.x + j * B;
+            bool pend = false;
+            if (in) pend = eval(off, q, tv);
+            enqueue(off, pend);
+          }
+        }
+        M = Mn;
+        w = wn;
+        tv = tn;
+#pragma unroll
+        for (int d = 0; d < kRecDw; ++d) q[d] = qn[d];
       }
     }
   }

@@ -119,7 +119,7 @@ struct qed_workspace {
   std::vector<double> e0;
   qed_instance* d_inst = nullptr;
   InstAcc* d_acc = nullptr;
-  Glob* d_glob = nullptr;
+  Glob* d_glob = nullptr;  // and behind it the control words of multi-step runs (MultiCtl)
   EvCtl* d_evc = nullptr;  // [0] pair-event queue, [1] emission queue
   uint64_t* d_evq = nullptr;
   int64_t evq_cap = 0;
@@ -143,9 +143,6 @@ struct qed_workspace {
   // (field kind, particles per thread, block, precision, table rows)
   int fit[2] = {0, 0};
   int fit_key[2][5] = {{-1, -1, -1, -1, -1}, {-1, -1, -1, -1, -1}};
-  int32_t* d_born = nullptr;      // per lepton slot: first step of a lepton made in a multi-step run
-  size_t born_len = 0;
-  MultiCtl* d_multi = nullptr;
   int multi_fit[2] = {0, 0};      // blocks per CU of the multi-step lepton and photon kernels
   int multi_fit_key[4] = {-1, -1, -1, -1};
   int emit_fit = 0;                         // emission-pass blocks per CU (occupancy query)
@@ -493,10 +490,12 @@ qed_status enqueue_multi(const qed_tables* tb, qed_workspace* ws, const qed_step
   m.s.win = ws->d_win;
   m.s.rec = ws->d_rec;
   m.s.lmask = ws->d_lmask;
-  m.mc = ws->d_multi;
+  m.mc = (MultiCtl*)(ws->d_glob + 1);
   m.evc = ws->d_evc;
   m.glob = ws->d_glob;
-  m.lep_born = ws->d_born;
+  // one word per lepton slot in the emission queue's memory (16 bytes per slot), which only single
+  // steps use, and only within a step
+  m.lep_born = (int32_t*)ws->d_emq;
   m.base_lep = ws->d_base;
   m.base_ph = ws->d_base + 2 * ws->max_inst;
   m.n_inst = ws->n_inst;
@@ -691,7 +690,7 @@ qed_status qed_workspace_create(int32_t max_inst, qed_workspace** out) {
   ws->max_inst = max_inst;
   hipError_t e = hipMalloc((void**)&ws->d_inst, max_inst * sizeof(qed_instance));
   if (e == hipSuccess) e = hipMalloc((void**)&ws->d_acc, max_inst * sizeof(InstAcc));
-  if (e == hipSuccess) e = hipMalloc((void**)&ws->d_glob, sizeof(Glob));
+  if (e == hipSuccess) e = hipMalloc((void**)&ws->d_glob, sizeof(Glob) + sizeof(MultiCtl));
   if (e == hipSuccess) e = hipMalloc((void**)&ws->d_evc, 2 * sizeof(EvCtl));
   if (e == hipSuccess) e = hipMemset(ws->d_evc, 0, 2 * sizeof(EvCtl));
   if (e == hipSuccess) e = hipMalloc((void**)&ws->d_evq, (size_t)kDefaultEventQueue * sizeof(uint64_t));
@@ -699,10 +698,8 @@ qed_status qed_workspace_create(int32_t max_inst, qed_workspace** out) {
   if (e == hipSuccess) e = hipMalloc((void**)&ws->d_base, 3 * (size_t)max_inst * sizeof(int64_t));
   if (e == hipSuccess) e = hipMalloc((void**)&ws->d_wave_cnt, (size_t)cus * 32 * sizeof(int32_t));
   if (e == hipSuccess) e = hipMemset(ws->d_wave_cnt, 0, (size_t)cus * 32 * sizeof(int32_t));
-  if (e == hipSuccess) e = hipMemset(ws->d_glob, 0, sizeof(Glob));
+  if (e == hipSuccess) e = hipMemset(ws->d_glob, 0, sizeof(Glob) + sizeof(MultiCtl));
   if (e == hipSuccess) e = hipMemset(ws->d_acc, 0, max_inst * sizeof(InstAcc));
-  if (e == hipSuccess) e = hipMalloc((void**)&ws->d_multi, sizeof(MultiCtl));
-  if (e == hipSuccess) e = hipMemset(ws->d_multi, 0, sizeof(MultiCtl));
   if (e == hipSuccess) e = init_crmath();
   if (e == hipSuccess) e = init_crmath_multi();
   if (e != hipSuccess) {
@@ -734,8 +731,6 @@ void qed_workspace_destroy(qed_workspace* ws) {
   hipFree(ws->d_win);
   hipFree(ws->d_rec);
   hipFree(ws->d_lmask);
-  hipFree(ws->d_born);
-  hipFree(ws->d_multi);
   delete ws;
 }
 
@@ -852,13 +847,6 @@ qed_status qed_bind(qed_workspace* ws, const qed_instance* inst, int32_t n_inst,
       acc0[i].lep_off[s] = (int64_t)loff;
       loff += (size_t)inst[i].s[s].capacity;
     }
-  }
-  if (multi_kind(ws->field_kind) && (loff > ws->born_len || !ws->d_born)) {
-    hipFree(ws->d_born);
-    ws->d_born = nullptr;
-    ws->born_len = 0;
-    HIP_TRY(hipMalloc((void**)&ws->d_born, (loff ? loff : 1) * sizeof(int32_t)));
-    ws->born_len = loff ? loff : 1;
   }
   if (goff > ws->lmask_len || !ws->d_lmask) {
     hipFree(ws->d_lmask);

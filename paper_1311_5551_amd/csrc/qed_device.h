@@ -1264,19 +1264,35 @@ struct BlockEventStats {
   }
 };
 
-// Sum of the 64 lanes' values of one group of 64 consecutive particle slots (a wave's share of
-// a chunk), converted to fixed point and added by lane 0 to the wave's words in LDS (`w`, four
-// words).  The butterfly order depends only on the lane positions, i.e. on the slots, so the
-// group sum is the same for any launch shape.  Every lane of the wave must call it.
-__device__ __forceinline__ void fix_group_add(double v, long long* w) {
-  const double s = wave_sum(v);
-  if (__lane_id() == 0) {
-    long long l[4];
-    fix_split(s, l);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) w[k] += l[k];
+// A lane's running sum of ledger terms, exact and so independent of their order: a term is cut at
+// 2^-24 and (rounded) at 2^-64 by adding and subtracting 1.5 2^28 and 1.5 2^-12, and the two parts
+// are sums of multiples of 2^-24 below 2^16 and of 2^-64 below 2^-24, exact in double for 8192 terms
+// (kLaneSumMax).  Eight instructions and no exchange between lanes; summing a wave's 64 terms by
+// shuffles and cutting the sum into limbs took some sixty and six LDS round trips.  The rare larger
+// or non-finite terms go to the words `w` (in LDS) as limbs at once.
+constexpr int kLaneSumMax = 8192;
+struct LaneSum {
+  double hi, lo;
+  __device__ __forceinline__ void add(double v, long long* w) {
+    if (!(fabs(v) < 65536.0)) {
+      long long l[4];
+      fix_split(v, l);
+      fix_atomic_add(w, l);
+      v = 0.0;
+    }
+    const double h = (v + 0x1.8p28) - 0x1.8p28, r = v - h;
+    hi += h;
+    lo += (r + 0x1.8p-12) - 0x1.8p-12;
   }
-}
+  __device__ __forceinline__ void flush(long long* w) {
+    long long l[4];
+    fix_split(hi, l);
+    fix_atomic_add(w, l);
+    fix_split(lo, l);
+    fix_atomic_add(w, l);
+    hi = lo = 0.0;
+  }
+};
 
 // The block's per-wave LDS words (s_w[(wave * NQ + q) * 4 + k]) summed and added by thread 0 to
 // the words of dst[q], then cleared.  Every thread of the block must call it.

@@ -187,9 +187,10 @@ struct LepPtr {
 };
 
 template <int FK, int PPT, bool MIXED>
-// (three waves per SIMD: the register budget of 168 that allows it costs at most a few spilled
-// words in the larger instantiations, and the sweep is latency-bound)
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_FIELD_GRID_FDTD ? 1 : 3))) void k_lepton(StepArgs a) {
+// (two waves per SIMD: with the next particle's words in flight the 168 registers of three waves
+// spilled 20 to 56 words per lane, and that traffic cost more than the third wave gained: the
+// 1.6e7-electron grid sweep 632 -> 548 us, 4e6 leptons in a uniform field 112 -> 92 us)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_lepton(StepArgs a) {
   using Real = typename std::conditional<MIXED, float, double>::type;
   extern __shared__ double smem[];
   __shared__ qed_field sF;
@@ -233,13 +234,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
   float tpf0 = 0.0f, psif_max = 0.0f;
   FieldK fK{0.0};
   // field work and energy radiated (deterministic reaction): exact fixed-point words per wave in
-  // LDS, fed with the sum of each group of 64 slots (fix_group_add), so the totals do not depend
-  // on the launch shape
+  // LDS, fed from exact sums per lane (LaneSum), so the totals do not depend on the launch shape
   long long* const fx_work = s_ll + (threadIdx.x >> 6) * 8;
   long long* const fx_rad = fx_work + 4;
   unsigned uacc[3] = {0, 0, 0};        // in-field steps, eta above the table, non-finite state
+  LaneSum sum_work{0.0, 0.0}, sum_rad{0.0, 0.0};
+  int n_sum = 0;  // terms a lane's sums may hold so far
   auto flush = [&](int entry) {
     InstAcc& A = a.acc[entry >> 1];
+    sum_work.flush(fx_work);
+    if (rr) sum_rad.flush(fx_rad);
+    n_sum = 0;
     long long* const dst[2] = {A.fx[FX_WORK], A.fx[FX_RADIATED]};
     fix_block_flush<2>(s_ll, dst);
     block_sum_u(uacc, sredu);
@@ -296,6 +301,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
       tpf0 = (float)sF.p[2];
       psif_max = (float)sF.p[1];
       fK.pi_over_len = uni_f64(field_k(sF).pi_over_len);
+    }
+    n_sum += PPT;
+    if (n_sum > kLaneSumMax) {  // (beyond 1e9 leptons per instance)
+      sum_work.flush(fx_work);
+      if (rr) sum_rad.flush(fx_rad);
+      n_sum = PPT;
     }
     const int64_t k0 = uni64((c - cb) * CH);
     const int64_t rem = n - k0;
@@ -460,10 +471,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
             if (mv.bad) ++uacc[2];
           }
         }
-        if (__ballot(in)) {  // wave-uniform: the energy sums of the wave's group of 64 slots
-          fix_group_add(wk, fx_work);
-          if (rr) fix_group_add(rd, fx_rad);
-        }
+        sum_work.add(wk, fx_work);
+        if (rr) sum_rad.add(rd, fx_rad);
         if (emit) enqueue(off, pend, eta);  // emit is uniform over the block
       }
     } else {
@@ -486,10 +495,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FK == QED_F
           lepton_gamma(st);
           pend = full(off, st, &eta, &wk, &rd);
         }
-        if (__ballot(in)) {
-          fix_group_add(wk, fx_work);
-          if (rr) fix_group_add(rd, fx_rad);
-        }
+        sum_work.add(wk, fx_work);
+        if (rr) sum_rad.add(rd, fx_rad);
         if (emit) enqueue(off, pend, eta);  // emit is uniform over the block
       }
     }

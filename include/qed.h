@@ -240,7 +240,9 @@ qed_status qed_run(const qed_tables* tables, qed_workspace* ws, const qed_step_p
  * by 8 x 8-cell tile of their position (photons: position at the start of the next step, using
  * params->dt), so that neighbouring particles gather from the same grid cache lines.  A counting
  * sort and a permutation of every array of each species; the order within a tile is not
- * specified, per-uid results of later steps are unchanged.  Allocates its scratch on the first
+ * specified, per-uid results of later steps are unchanged.  Photons whose pair window is over go
+ * to the front of their arrays instead and stay there (the photon sweep starts behind them).
+ * Allocates its scratch on the first
  * call that needs it (synchronising `stream`), then is async; up to 2^32 - 1 slots per species
  * (QED_ERR_ARG beyond).  Instances with analytic fields are left as they are. */
 qed_status qed_sort(qed_workspace* ws, const qed_step_params* params, qed_stream stream);

@@ -151,6 +151,7 @@ struct qed_workspace {
   uint64_t* d_lmask = nullptr;  // live masks of the photon slot groups (kWinGroup slots each), at acc.lmask_off
   size_t lmask_len = 0;
   bool win_valid = false;
+  bool win_front = false;       // a front that sorts left is valid for the constants below
   double win_t0 = 0.0, win_dt = 0.0, win_cp_min = 0.0;
   int block[2] = {256, 256}, ppt[2] = {4, 4};  // launch shapes: [0] lepton sweep, [1] photon sweep
   // kernel timing: event pairs per kernel class, reused across reads
@@ -522,8 +523,10 @@ qed_status ensure_windows(const qed_tables* tb, qed_workspace* ws, const qed_ste
   if (ws->win_valid && ws->win_t0 == p->t0 && ws->win_dt == p->dt && ws->win_cp_min == cp_min) return QED_OK;
   launch_photon_windows(ws->field_kind, ws->d_inst, ws->n_inst, ws->d_acc, ws->d_glob, ws->d_win, ws->d_rec, ws->d_lmask,
                         p->t0, p->dt, cp_min,
-                        ws->prec == QED_FP32_MIXED, s);
+                        ws->prec == QED_FP32_MIXED,
+                        ws->win_front && ws->win_t0 == p->t0 && ws->win_dt == p->dt && ws->win_cp_min == cp_min, s);
   HIP_TRY(hipGetLastError());
+  ws->win_front = false;
   ws->win_valid = true;
   ws->win_t0 = p->t0;
   ws->win_dt = p->dt;
@@ -878,6 +881,7 @@ qed_status qed_bind(qed_workspace* ws, const qed_instance* inst, int32_t n_inst,
     ws->rec_bytes = rec_bytes;
   }
   ws->win_valid = false;  // computed by the first step, which knows t0, dt and the tables
+  ws->win_front = false;
   if (ws->retire.spec) HIP_TRY(hipMemset(ws->retire.spec, 0, ws->spec_len * sizeof(unsigned long long)));
   // emission queue: the wave segments of the lepton sweep (a lepton emits at most once per step)
   int64_t leptons = 0;
@@ -992,7 +996,7 @@ qed_status qed_sort(qed_workspace* ws, const qed_step_params* params, qed_stream
   for (const qed_instance& I : ws->inst) {
     if (!grid_kind(I.field.kind)) continue;
     for (int s = 0; s < 3; ++s) cap = std::max<int64_t>(cap, I.s[s].capacity);
-    tiles = std::max(tiles, ((I.field.nx + 7) / 8) * ((I.field.ny + 7) / 8));
+    tiles = std::max(tiles, ((I.field.nx + 7) / 8) * ((I.field.ny + 7) / 8) + 1);  // and the front's bucket
   }
   if (cap == 0) return QED_OK;  // no grid instance: nothing to reorder
   if (cap >= (int64_t(1) << 32)) return fail(QED_ERR_ARG, "qed_sort handles up to 2^32 - 1 slots per species");
@@ -1018,13 +1022,14 @@ qed_status qed_sort(qed_workspace* ws, const qed_step_params* params, qed_stream
     if (!grid_kind(I.field.kind)) continue;
     for (int s = 0; s < 3; ++s) {
       if (I.s[s].capacity == 0) continue;
-      HIP_TRY(launch_sort_species(ws->d_inst, I, ii, s, ws->d_glob, params->dt, mixed, ws->sort, ws->cus * 8,
-                                  (hipStream_t)stream));
+      HIP_TRY(launch_sort_species(ws->d_inst, I, ii, s, ws->d_acc, ws->win_valid ? ws->d_win : nullptr, ws->d_glob,
+                                  params->dt, mixed, ws->sort, ws->cus * 8, (hipStream_t)stream));
     }
   }
-  launch_front_clear(ws->d_acc, ws->n_inst, (hipStream_t)stream);  // the photons moved: no front
   HIP_TRY(hipGetLastError());
-  ws->win_valid = false;  // the photons moved: their windows and records are set again by the next step
+  // the photons behind the front moved: their windows and records are set again by the next step
+  ws->win_front = ws->win_front || ws->win_valid;
+  ws->win_valid = false;
   return QED_OK;
 }
 
@@ -1057,12 +1062,12 @@ qed_status qed_sort_static(qed_workspace* ws, const qed_step_params* params, qed
     if (!grid_kind(I.field.kind)) continue;
     for (int s = 0; s < 3; ++s) {
       if (I.s[s].capacity == 0) continue;
-      HIP_TRY(launch_sort_species(ws->d_inst, I, ii, s, ws->d_glob, params->dt, mixed, w, ws->cus * 8,
-                                  (hipStream_t)stream));
+      HIP_TRY(launch_sort_species(ws->d_inst, I, ii, s, ws->d_acc, ws->win_valid ? ws->d_win : nullptr, ws->d_glob,
+                                  params->dt, mixed, w, ws->cus * 8, (hipStream_t)stream));
     }
   }
-  launch_front_clear(ws->d_acc, ws->n_inst, (hipStream_t)stream);  // the photons moved: no front
   HIP_TRY(hipGetLastError());
+  ws->win_front = ws->win_front || ws->win_valid;
   ws->win_valid = false;
   return QED_OK;
 }
@@ -1106,6 +1111,9 @@ qed_status qed_compact(qed_workspace* ws, qed_stream stream) {
   launch_compact(ws->field_kind, ws->d_inst, ws->n_inst, ws->d_acc, ws->d_glob, ws->d_movers, ws->d_win, ws->d_rec,
                  ws->d_lmask, ws->prec == QED_FP32_MIXED, ws->retire, (hipStream_t)stream);
   HIP_TRY(hipGetLastError());
+  // after a sort the windows are not yet those of the photons in their slots: a front made from
+  // them does not outlive the next step's rebuild
+  if (!ws->win_valid) ws->win_front = false;
   return QED_OK;
 }
 

@@ -61,14 +61,15 @@ struct SortScratch {
 // the fixed scratch of qed_sort_static: up to 2^21 slots per species and 2^16 tiles of 8 x 8 cells
 constexpr int64_t kStaticSortSlots = int64_t(1) << 21;
 constexpr int kStaticSortTiles = 1 << 16;
-constexpr size_t kStaticSortBytes = (size_t)kStaticSortSlots * 16 + (size_t)kStaticSortTiles * 4;
+constexpr size_t kStaticSortBytes = (size_t)kStaticSortSlots * 16 + ((size_t)kStaticSortTiles + 64) * 4;
 constexpr int kMaxDevices = 64;
 // the device address of that scratch on the current device, split into the sort's arrays
 hipError_t static_sort_scratch(SortScratch* out);
 
 hipError_t init_crmath();
 hipError_t launch_sort_species(const qed_instance* inst_dev, const qed_instance& inst_host, int ii, int s,
-                               const Glob* glob, double dt, bool mixed, const SortScratch& w, int grid, hipStream_t st);
+                               InstAcc* acc_dev, const uint32_t* win, const Glob* glob, double dt, bool mixed,
+                               const SortScratch& w, int grid, hipStream_t st);
 hipError_t launch_build_tables(const qed_table_params& p, double* h, double* lnchi_min, double* dlnchi, double* P,
                                double* T, double* fgrid, double* Pf, double* knorm, double* g, hipStream_t s);
 void launch_step_begin(const qed_instance* inst, int n_inst, InstAcc* acc, Glob* glob, EvCtl* evc, EvCtl* emc,
@@ -101,6 +102,7 @@ void launch_ledger(const qed_instance* inst, int n_inst, InstAcc* acc, bool mixe
 void launch_compact(int fk, const qed_instance* inst, int n_inst, InstAcc* acc, const Glob* glob, int64_t* movers,
                     uint32_t* win, void* rec, uint64_t* lmask, bool mixed, const RetireSpec& rs, hipStream_t s);
 void launch_photon_windows(int fk, const qed_instance* inst, int n_inst, InstAcc* acc, const Glob* glob, uint32_t* win,
-                           void* rec, uint64_t* lmask, double t0, double dt, double cp_min, bool mixed, hipStream_t s);
+                           void* rec, uint64_t* lmask, double t0, double dt, double cp_min, bool mixed, bool keep_front,
+                           hipStream_t s);
 
 }  // namespace qedk

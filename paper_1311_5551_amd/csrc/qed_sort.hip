@@ -1,3 +1,7 @@
+// Photons whose pair window is over (in the refreshed grid those below the energy that can reach
+// chi_min: half of them in the cascade) go to the front of the array, where the photon sweep does
+// not start and later sorts do not touch them; the others are sorted behind it.
+//
 // Spatial reordering of the particles of an instance with a grid field, by 8 x 8-cell tile of
 // their position: a counting sort (histogram of tile keys with each particle's rank in its tile,
 // exclusive scan, destination slots) followed by a permutation of every array of the species.  Particles that
@@ -17,7 +21,7 @@ namespace qedk {
 
 constexpr int kTile = 8;
 
-// Tile of every particle, the tile counts, and the particle's rank among those of its tile.
+// Bucket of every particle (1 + its tile; 0 for a photon that goes to the front), the bucket counts, and the particle's rank among those of its bucket.
 // Particles mostly lie in the order of the sort before, so the 64 of a wave share a few tiles: one
 // atomic per run of equal keys among its lanes adds the run and ranks its particles.  (One atomic
 // per particle serialised on a tile's counter, and a second pass of them made the destinations:
@@ -26,7 +30,8 @@ template <bool MIXED>
 __global__ __launch_bounds__(256) void k_sort_key(const qed_instance* __restrict__ inst, int ii, int s,
                                                   const Glob* __restrict__ glob, double dt, int32_t* __restrict__ key,
                                                   uint32_t* __restrict__ rank, uint32_t* __restrict__ hist,
-                                                  int tiles_x) {
+                                                  int tiles_x, const InstAcc* __restrict__ acc,
+                                                  const uint32_t* __restrict__ win) {
   using Real = typename std::conditional<MIXED, float, double>::type;
   const qed_instance& I = inst[ii];
   const qed_species& S = I.s[s];
@@ -34,12 +39,32 @@ __global__ __launch_bounds__(256) void k_sort_key(const qed_instance* __restrict
   int64_t n = *S.count_dev;
   if (n > S.capacity) n = S.capacity;
   const int64_t step = glob->step_next;
+  const int64_t n0 = s == 2 ? acc->n_front : 0;
+  const uint32_t* W = win ? win + acc->mover_off : nullptr;
   const int lane = threadIdx.x & 63;
-  // the loop bound is wave-uniform, so every lane reaches the ballot
-  for (int64_t k0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x - lane; k0 < n;
-       k0 += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t k = min(k0 + lane, n - 1);
-    const bool valid = k0 + lane < n;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  // a contiguous range of slots per block
+  int64_t b0, b1;
+  block_range(n0, n, blockIdx.x, gridDim.x, &b0, &b1);
+  if (b0 >= b1) return;  // the whole block
+  // (a converted photon waits for its compaction behind the front)
+  auto to_front = [&](int64_t k) { return window_over(W[k], step) && !(S.tau_dev[k] < 0.0); };
+  // the front's new photons are counted first: one atomic per block reserves their places (they are
+  // many, and in one bucket)
+  __shared__ unsigned sredu[16];
+  __shared__ uint32_t s_base;
+  if (W) {
+    unsigned u[1] = {0};
+    for (int64_t k = b0 + threadIdx.x; k < b1; k += blockDim.x)
+      if (to_front(k)) ++u[0];
+    block_sum_u(u, sredu);
+    if (threadIdx.x == 0) s_base = u[0] ? atomicAdd(&hist[0], u[0]) : 0u;
+    __syncthreads();
+  }
+  uint32_t run = W ? s_base : 0u;
+  for (int64_t k0 = b0 + threadIdx.x - lane; k0 < b1 + threadIdx.x - lane; k0 += blockDim.x) {  // block-uniform
+    const int64_t k = min(k0 + lane, b1 - 1);
+    const bool valid = k0 + lane < b1;
     double x, y;
     if (s < 2) {
       x = ((const Real*)S.x_dev)[k];
@@ -59,17 +84,30 @@ __global__ __launch_bounds__(256) void k_sort_key(const qed_instance* __restrict
     if (!(fabs(gx) < 1e15)) gx = 0.0;  // non-finite positions go to tile 0
     if (!(fabs(gy) < 1e15)) gy = 0.0;
     const int64_t i = wrap_index((int64_t)gx, F.nx), j = wrap_index((int64_t)gy, F.ny);
-    const int32_t kk = valid ? (int32_t)((j / kTile) * tiles_x + i / kTile) : -1;
-    const int32_t prev = __shfl_up(kk, 1);
-    const unsigned long long heads = __ballot(lane == 0 || kk != prev);  // first lanes of the runs
-    const int head = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+    const bool front = W && valid && to_front(k);
+    uint32_t at_front = 0;
+    if (W) {
+      unsigned tot;
+      at_front = run + block_rank(front, sredu, &tot);
+      run += tot;
+    }
+    const int32_t kk = front ? 0 : 1 + (int32_t)((j / kTile) * tiles_x + i / kTile);
+    // runs of equal keys among the wave's lanes that go to a tile
+    const unsigned long long in = __ballot(valid && !front);
+    const bool mine = (in >> lane) & 1ull;
+    const int prev = 63 - __clzll((long long)(in & below));  // the lane before among them (-1: none)
+    const int32_t pk = __shfl(kk, prev < 0 ? lane : prev);
+    const unsigned long long heads = __ballot(mine && (prev < 0 || kk != pk));
+    const unsigned long long upto = heads & (below | (1ull << lane));
+    const int head = upto ? 63 - __clzll((long long)upto) : 0;
     const unsigned long long after = lane == 63 ? 0ull : heads & (~0ull << (lane + 1));
+    const unsigned long long same = after ? in & ((1ull << (__ffsll((long long)after) - 1)) - 1ull) : in;
     uint32_t base = 0;
-    if (valid && head == lane) base = atomicAdd(&hist[kk], (uint32_t)((after ? __ffsll((long long)after) - 1 : 64) - lane));
+    if (mine && head == lane) base = atomicAdd(&hist[kk], (uint32_t)__popcll(same & ~below));
     base = __shfl(base, head);
     if (valid) {
       key[k] = kk;
-      rank[k] = base + (uint32_t)(lane - head);
+      rank[k] = front ? at_front : base + (uint32_t)__popcll(in & below & (~0ull << head));
     }
   }
 }
@@ -143,84 +181,99 @@ __global__ __launch_bounds__(1024) void k_sort_scan(uint32_t* __restrict__ hist,
   }
 }
 
-// destination slot: the tile's first slot plus the rank in the tile
+// destination slot: behind the front (*first slots, or none), the bucket's first slot plus the rank
 __global__ __launch_bounds__(256) void k_sort_dst(const qed_species* __restrict__ sp, const int32_t* __restrict__ key,
-                                                  const uint32_t* __restrict__ offs, uint32_t* __restrict__ dst) {
+                                                  const uint32_t* __restrict__ offs, uint32_t* __restrict__ dst,
+                                                  const int64_t* __restrict__ first) {
   int64_t n = *sp->count_dev;
   if (n > sp->capacity) n = sp->capacity;
-  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
-    dst[k] += offs[key[k]];
+  const int64_t F = first ? *first : 0;
+  for (int64_t k = F + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
+    dst[k] += (uint32_t)F + offs[key[k]];
 }
 
 // stage[dst[k]] = a[k], then a[k] = stage[k] (two kernels)
 template <class T>
 __global__ __launch_bounds__(256) void k_scatter(const qed_species* __restrict__ sp, const T* __restrict__ a,
-                                                 T* __restrict__ stage, const uint32_t* __restrict__ dst) {
+                                                 T* __restrict__ stage, const uint32_t* __restrict__ dst,
+                                                 const int64_t* __restrict__ first) {
   int64_t n = *sp->count_dev;
   if (n > sp->capacity) n = sp->capacity;
-  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
+  const int64_t F = first ? *first : 0;
+  for (int64_t k = F + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
     stage[dst[k]] = a[k];
 }
 template <class T>
 __global__ __launch_bounds__(256) void k_copy_back(const qed_species* __restrict__ sp, T* __restrict__ a,
-                                                   const T* __restrict__ stage) {
+                                                   const T* __restrict__ stage, const int64_t* __restrict__ first) {
   int64_t n = *sp->count_dev;
   if (n > sp->capacity) n = sp->capacity;
-  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
+  const int64_t F = first ? *first : 0;
+  for (int64_t k = F + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
     a[k] = stage[k];
 }
 
+// the photons of bucket 0 have joined the front
+__global__ void k_sort_front(InstAcc* acc, const uint32_t* __restrict__ offs) { acc->n_front += offs[1]; }
+
 template <class T>
-static void permute(const qed_species* sp_dev, void* a, void* stage, const uint32_t* dst, int grid, hipStream_t s) {
+static void permute(const qed_species* sp_dev, void* a, void* stage, const uint32_t* dst, const int64_t* first,
+                    int grid, hipStream_t s) {
   if (!a) return;
-  hipLaunchKernelGGL(k_scatter<T>, dim3(grid), dim3(256), 0, s, sp_dev, (const T*)a, (T*)stage, dst);
-  hipLaunchKernelGGL(k_copy_back<T>, dim3(grid), dim3(256), 0, s, sp_dev, (T*)a, (const T*)stage);
+  hipLaunchKernelGGL(k_scatter<T>, dim3(grid), dim3(256), 0, s, sp_dev, (const T*)a, (T*)stage, dst, first);
+  hipLaunchKernelGGL(k_copy_back<T>, dim3(grid), dim3(256), 0, s, sp_dev, (T*)a, (const T*)stage, first);
 }
 
 hipError_t launch_sort_species(const qed_instance* inst_dev, const qed_instance& inst_host, int ii, int s,
-                               const Glob* glob, double dt, bool mixed, const SortScratch& w, int grid, hipStream_t st) {
+                               InstAcc* acc_dev, const uint32_t* win, const Glob* glob, double dt, bool mixed,
+                               const SortScratch& w, int grid, hipStream_t st) {
   const qed_field& F = inst_host.field;
   const int tiles_x = (F.nx + kTile - 1) / kTile, tiles_y = (F.ny + kTile - 1) / kTile;
-  const int n_tiles = tiles_x * tiles_y;
+  const int n_tiles = tiles_x * tiles_y + 1;  // and the front's bucket
+  InstAcc* const acc = acc_dev + ii;
+  const int64_t* const first = s == 2 ? &acc->n_front : nullptr;
   if (n_tiles > w.hist_len) return hipErrorInvalidValue;
   const qed_species* sp_dev = &inst_dev[ii].s[s];
   const qed_species& S = inst_host.s[s];
   hipLaunchKernelGGL(k_fill_zero, dim3(256), dim3(256), 0, st, w.hist, n_tiles);
   if (mixed)
     hipLaunchKernelGGL(k_sort_key<true>, dim3(grid), dim3(256), 0, st, inst_dev, ii, s, glob, dt, w.key, w.dst,
-                       w.hist, tiles_x);
+                       w.hist, tiles_x, (const InstAcc*)acc, s == 2 ? win : nullptr);
   else
     hipLaunchKernelGGL(k_sort_key<false>, dim3(grid), dim3(256), 0, st, inst_dev, ii, s, glob, dt, w.key, w.dst,
-                       w.hist, tiles_x);
+                       w.hist, tiles_x, (const InstAcc*)acc, s == 2 ? win : nullptr);
   hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, st, w.hist, n_tiles);
-  hipLaunchKernelGGL(k_sort_dst, dim3(grid), dim3(256), 0, st, sp_dev, w.key, w.hist, w.dst);
+  hipLaunchKernelGGL(k_sort_dst, dim3(grid), dim3(256), 0, st, sp_dev, w.key, w.hist, w.dst, first);
   const bool d3 = inst_host.dims == 3;
   if (mixed) {
-    permute<float>(sp_dev, S.x_dev, w.stage, w.dst, grid, st);
-    permute<float>(sp_dev, S.y_dev, w.stage, w.dst, grid, st);
-    if (d3) permute<float>(sp_dev, S.z_dev, w.stage, w.dst, grid, st);
-    permute<float>(sp_dev, S.ux_dev, w.stage, w.dst, grid, st);
-    permute<float>(sp_dev, S.uy_dev, w.stage, w.dst, grid, st);
-    permute<float>(sp_dev, S.uz_dev, w.stage, w.dst, grid, st);
+    permute<float>(sp_dev, S.x_dev, w.stage, w.dst, first, grid, st);
+    permute<float>(sp_dev, S.y_dev, w.stage, w.dst, first, grid, st);
+    if (d3) permute<float>(sp_dev, S.z_dev, w.stage, w.dst, first, grid, st);
+    permute<float>(sp_dev, S.ux_dev, w.stage, w.dst, first, grid, st);
+    permute<float>(sp_dev, S.uy_dev, w.stage, w.dst, first, grid, st);
+    permute<float>(sp_dev, S.uz_dev, w.stage, w.dst, first, grid, st);
     if (s < 2) {
-      permute<float>(sp_dev, S.x_lo_dev, w.stage, w.dst, grid, st);
-      permute<float>(sp_dev, S.y_lo_dev, w.stage, w.dst, grid, st);
-      if (d3) permute<float>(sp_dev, S.z_lo_dev, w.stage, w.dst, grid, st);
-      permute<float>(sp_dev, S.ux_lo_dev, w.stage, w.dst, grid, st);
-      permute<float>(sp_dev, S.uy_lo_dev, w.stage, w.dst, grid, st);
-      permute<float>(sp_dev, S.uz_lo_dev, w.stage, w.dst, grid, st);
+      permute<float>(sp_dev, S.x_lo_dev, w.stage, w.dst, first, grid, st);
+      permute<float>(sp_dev, S.y_lo_dev, w.stage, w.dst, first, grid, st);
+      if (d3) permute<float>(sp_dev, S.z_lo_dev, w.stage, w.dst, first, grid, st);
+      permute<float>(sp_dev, S.ux_lo_dev, w.stage, w.dst, first, grid, st);
+      permute<float>(sp_dev, S.uy_lo_dev, w.stage, w.dst, first, grid, st);
+      permute<float>(sp_dev, S.uz_lo_dev, w.stage, w.dst, first, grid, st);
     }
   } else {
-    permute<double>(sp_dev, S.x_dev, w.stage, w.dst, grid, st);
-    permute<double>(sp_dev, S.y_dev, w.stage, w.dst, grid, st);
-    if (d3) permute<double>(sp_dev, S.z_dev, w.stage, w.dst, grid, st);
-    permute<double>(sp_dev, S.ux_dev, w.stage, w.dst, grid, st);
-    permute<double>(sp_dev, S.uy_dev, w.stage, w.dst, grid, st);
-    permute<double>(sp_dev, S.uz_dev, w.stage, w.dst, grid, st);
+    permute<double>(sp_dev, S.x_dev, w.stage, w.dst, first, grid, st);
+    permute<double>(sp_dev, S.y_dev, w.stage, w.dst, first, grid, st);
+    if (d3) permute<double>(sp_dev, S.z_dev, w.stage, w.dst, first, grid, st);
+    permute<double>(sp_dev, S.ux_dev, w.stage, w.dst, first, grid, st);
+    permute<double>(sp_dev, S.uy_dev, w.stage, w.dst, first, grid, st);
+    permute<double>(sp_dev, S.uz_dev, w.stage, w.dst, first, grid, st);
   }
-  permute<double>(sp_dev, S.tau_dev, w.stage, w.dst, grid, st);
-  permute<uint64_t>(sp_dev, S.uid_dev, w.stage, w.dst, grid, st);
-  if (s == 2) permute<int32_t>(sp_dev, S.birth_step_dev, w.stage, w.dst, grid, st);
+  permute<double>(sp_dev, S.tau_dev, w.stage, w.dst, first, grid, st);
+  permute<uint64_t>(sp_dev, S.uid_dev, w.stage, w.dst, first, grid, st);
+  if (s == 2) {
+    permute<int32_t>(sp_dev, S.birth_step_dev, w.stage, w.dst, first, grid, st);
+    hipLaunchKernelGGL(k_sort_front, dim3(1), dim3(1), 0, st, acc, w.hist);
+  }
   return hipGetLastError();
 }
 
@@ -252,7 +305,7 @@ hipError_t static_sort_scratch(SortScratch* out) {
   out->key = (int32_t*)(base + kStaticSortSlots * 8);
   out->dst = (uint32_t*)(base + kStaticSortSlots * 12);
   out->hist = (uint32_t*)(base + kStaticSortSlots * 16);
-  out->hist_len = kStaticSortTiles;
+  out->hist_len = kStaticSortTiles + 1;
   return hipSuccess;
 }
 

@@ -1451,22 +1451,21 @@ __global__ __launch_bounds__(256) void k_window_masks(const qed_instance* __rest
   }
 }
 
-// The partition's front after a compaction (after_partition), else none (the windows were just
-// rebuilt)
-__global__ void k_window_front(const qed_instance* __restrict__ inst, int n_inst, InstAcc* __restrict__ acc,
-                               int after_partition) {
+// The partition's front after a compaction
+__global__ void k_window_front(const qed_instance* __restrict__ inst, int n_inst, InstAcc* __restrict__ acc) {
   for (int i = threadIdx.x; i < n_inst; i += blockDim.x) {
     const qed_species& S = inst[i].s[2];
     int64_t n = S.count_dev ? *S.count_dev : 0;
     if (n > S.capacity) n = S.capacity;
     if (n < 0) n = 0;
-    const int64_t D = after_partition ? acc[i].n_live : 0;
+    const int64_t D = acc[i].n_live;
     acc[i].n_front = D < 0 ? 0 : (D > n ? n : D);
   }
 }
 
-// Pair windows of every photon present (after a bind, or when the step's t0, dt or tables
-// change); grid: x strides photons, y = instance.
+// Pair windows of every photon present (after a bind or a sort, or when the step's t0, dt or tables
+// change); grid: x strides photons, y = instance.  The photons of a front that a sort has left in
+// place have empty windows (a grid field's windows are empty or open) and need no record.
 template <bool MIXED, int FK>
 __global__ __launch_bounds__(256) void k_photon_windows(const qed_instance* __restrict__ inst,
                                                         const InstAcc* __restrict__ acc, uint32_t* __restrict__ win,
@@ -1480,8 +1479,12 @@ __global__ __launch_bounds__(256) void k_photon_windows(const qed_instance* __re
   const double eps_min = pair_eps_min(inst[ii].field, cp_min);
   uint32_t* W = win + acc[ii].mover_off;
   PhotonRecT<MIXED, FK>* R = (PhotonRecT<MIXED, FK>*)rec_v + acc[ii].mover_off;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, F = acc[ii].n_front;
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += stride) {
+    if (k < F) {
+      W[k] = kWinEmpty;
+      continue;
+    }
     const double kx = ((const Real*)S.ux_dev)[k], ky = ((const Real*)S.uy_dev)[k], kz = ((const Real*)S.uz_dev)[k];
     const double xb = ((const Real*)S.x_dev)[k], yb = ((const Real*)S.y_dev)[k];
     const int32_t bs = S.birth_step_dev[k];
@@ -1709,7 +1712,9 @@ void launch_ledger(const qed_instance* inst, int n_inst, InstAcc* acc, bool mixe
 }
 
 void launch_photon_windows(int fk, const qed_instance* inst, int n_inst, InstAcc* acc, const Glob* glob, uint32_t* win,
-                           void* rec, uint64_t* lmask, double t0, double dt, double cp_min, bool mixed, hipStream_t s) {
+                           void* rec, uint64_t* lmask, double t0, double dt, double cp_min, bool mixed, bool keep_front,
+                           hipStream_t s) {
+  if (!keep_front) launch_front_clear(acc, n_inst, s);
   const dim3 g(n_inst == 1 ? 2048 : 64, n_inst);
   constexpr int LP = QED_FIELD_LP_PULSE, GEN = QED_FIELD_UNIFORM;  // record layouts: plane wave, general
   if (fk == LP) {
@@ -1720,7 +1725,6 @@ void launch_photon_windows(int fk, const qed_instance* inst, int n_inst, InstAcc
     else hipLaunchKernelGGL((k_photon_windows<false, GEN>), g, dim3(256), 0, s, inst, acc, win, rec, t0, dt, cp_min);
   }
   hipLaunchKernelGGL(k_window_masks, g, dim3(256), 0, s, inst, acc, glob, win, lmask);
-  hipLaunchKernelGGL(k_window_front, dim3(1), dim3(256), 0, s, inst, n_inst, acc, 0);
 }
 
 void launch_compact(int fk, const qed_instance* inst, int n_inst, InstAcc* acc, const Glob* glob, int64_t* movers,
@@ -1750,7 +1754,7 @@ void launch_compact(int fk, const qed_instance* inst, int n_inst, InstAcc* acc, 
   if (mixed) hipLaunchKernelGGL(k_part_swap<true>, g, dim3(256), 0, s, inst, acc, glob, movers, win, rec, rw);
   else hipLaunchKernelGGL(k_part_swap<false>, g, dim3(256), 0, s, inst, acc, glob, movers, win, rec, rw);
   hipLaunchKernelGGL(k_window_masks, g, dim3(256), 0, s, inst, acc, glob, win, lmask);
-  hipLaunchKernelGGL(k_window_front, dim3(1), dim3(256), 0, s, inst, n_inst, acc, 1);
+  hipLaunchKernelGGL(k_window_front, dim3(1), dim3(256), 0, s, inst, n_inst, acc);
 }
 
 }  // namespace qedk

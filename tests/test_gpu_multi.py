@@ -143,3 +143,51 @@ def test_full_photon_buffer_in_a_run(tables):
     assert led["status"] == "QED_ERR_CAPACITY"
     assert led["count"][2] == 5000 and led["n_dropped"] == led["n_emit"] - 5000 > 0
     assert led["drift"] < 1e-12 and led["dropped_energy"] > 0
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_sort_keeps_photons_without_a_pair_rate_in_front(static, tables):
+    # sorts between the steps of a grid run put the photons below the pair threshold in front and
+    # leave them there: the particles stay those of a run without sorts, through compactions before
+    # and after a sort and a clock set back, and the sweep visits fewer groups
+    def make():
+        w = W.grid_config3(n=4000, nx=250, ny=61, a0=700.0, n_steps=200, seed=4)
+        w.capacity = dict(electron=30 * w.n, positron=30 * w.n, photon=100 * w.n)
+        return Run(w, tables)
+    ra, rb = make(), make()
+    sort = rb.sort_static if static else rb.sort
+    for i in range(12):
+        for r in (ra, rb):
+            _single(r, 10)
+            if i % 4 == 1:
+                r.compact()
+        sort()
+        if i % 4 == 3:
+            rb.compact()  # windows not rebuilt yet
+            ra.compact()
+        if i == 5:
+            sort()
+    _same_particles(ra, rb)
+    la, lb = ra.ledger()[0], rb.ledger()[0]
+    for k in COUNTS:
+        assert la[k] == lb[k], k
+    assert la["n_pair"] > 0 and la["photon_steps_active"] < 0.9 * la["particle_steps"][2]
+    # back in time: the front is emptied, and the photons' windows serve the repeated steps
+    # (new uids, so that the children made again do not repeat the uids of those made before)
+    for r in (ra, rb):
+        r.synchronize()
+        for name in ("electron", "positron", "photon"):
+            r.bufs[0][name]["uid"][:r.count(0, name)] ^= 0x5DEECE66D
+        r.torch.cuda.synchronize()
+        capi.qed_set_step(r.ws, 60, r._s())
+        _single(r, 3)
+    _same_particles(ra, rb)
+
+
+def _same_particles(ra, rb):
+    for name in ("electron", "positron", "photon"):
+        a, b = ra.species(0, name), rb.species(0, name)
+        oa, ob = np.argsort(a["uid"]), np.argsort(b["uid"])
+        assert len(oa) == len(ob), name
+        for k in a:
+            np.testing.assert_array_equal(a[k][oa], b[k][ob], err_msg="%s.%s" % (name, k))

@@ -335,62 +335,47 @@ __device__ __forceinline__ int64_t wrap_index(int64_t i, int n) {
 // functions).  Written out so that the kernels carry no large-argument reduction code: fewer
 // instructions and registers than the general library routines.
 // ---------------------------------------------------------------------------
-namespace fastm {
-constexpr double f2 = 1.0 / 2.0, f3 = 1.0 / 6.0, f4 = 1.0 / 24.0, f5 = 1.0 / 120.0, f6 = 1.0 / 720.0,
-                 f7 = 1.0 / 5040.0, f8 = 1.0 / 40320.0, f9 = 1.0 / 362880.0, f10 = 1.0 / 3628800.0,
-                 f11 = 1.0 / 39916800.0, f12 = 1.0 / 479001600.0, f13 = 1.0 / 6227020800.0,
-                 f14 = 1.0 / 87178291200.0, f15 = 1.0 / 1307674368000.0, f16 = 1.0 / 20922789888000.0,
-                 f17 = 1.0 / 355687428096000.0, f18 = 1.0 / 6402373705728000.0;
-}  // namespace fastm
-
-// sin and cos of x, |x| < 2^20: x = k pi/2 + r by Cody-Waite reduction (pi/2 in three parts, the
-// first with 33 bits so that k times it is exact), |r| <= pi/4, Taylor polynomials to r^13 and
-// r^14 in fused multiply-adds (truncation below 3e-14 and 1e-15 relative); quadrant from k mod 4.
-// These values only set optical-depth decrements, where the parity bars allow 1e-10 in the
-// depth; the short polynomials keep the kernels' 64-bit constants (scalar registers) few.
-// Both polynomials are evaluated and the quadrant selects (no divergent branch).
-__device__ __forceinline__ void fast_sincos_r(double x, double* sv, double* cv, int* q) {
-  using namespace fastm;
-  const double k = rint(x * kTwoOverPi);
-  double r = fma(-k, kPio2A, x);
-  r = fma(-k, kPio2B, r);
-  r = fma(-k, kPio2C, r);
-  const double r2 = r * r;
-  double ps = fma(f13, r2, -f11);
-  double pc = fma(f14, r2, -f12);
-  ps = fma(ps, r2, f9);
-  pc = fma(pc, r2, f10);
-  ps = fma(ps, r2, -f7);
-  pc = fma(pc, r2, -f8);
-  ps = fma(ps, r2, f5);
-  pc = fma(pc, r2, f6);
-  ps = fma(ps, r2, -f3);
-  pc = fma(pc, r2, -f4);
-  *sv = fma(r * r2, ps, r);                    // r + r^3 (-1/3! + ...)
-  *cv = fma(r2 * r2, -pc, fma(-0.5, r2, 1.0));  // 1 - r^2/2 + r^4 (1/4! - ...)
-  *q = (int)(int64_t)k;
+// sin and cos of x (|x| < 2^44) from a table of the circle: k = rint(x 256/pi) from the low bits of
+// x 256/pi + 1.5 2^52, r = x - k pi/256 (pi/256 in two parts, the first with 33 bits, so that both
+// fused steps are exact but for the last rounding), |r| <= pi/512, and with S, C the sine and cosine
+// of k pi/256
+//   sin x = S + (S (cos r - 1) + C sin r),  cos x = C + (C (cos r - 1) - S sin r),
+// the series cut at r^4 and r^5 (7e-17 and 1e-17).  Absolute error at most 1.8e-16 (6e6 arguments up
+// to 1e5, against 113 bits; the polynomials of degree 13 and 14 on a quadrant used before erred by
+// up to 2.1e-14); 16 instructions, none of them a selection, instead of 37: the photon sweep of a
+// pulse is bound by their number (k_multi_photon 5.6 -> 3.5 ms for 100 steps of a collision of 1e6
+// electrons, with the loop's bookkeeping cut and five waves per SIMD).
+constexpr int kPhTab = 512;
+static __constant__ __attribute__((aligned(16))) double c_phtab[2 * kPhTab];  // sine, cosine of j pi/256
+// LDS copy of the table for a block (every thread calls this, then a barrier follows)
+__device__ __forceinline__ void stage_phtab(double* dst) {
+  for (int i = threadIdx.x; i < kPhTab; i += blockDim.x) ((double2*)dst)[i] = ((const double2*)c_phtab)[i];
 }
-__device__ __forceinline__ void fast_sincos(double x, double* sn, double* cs) {
-  double sv, cv;
-  int k;
-  fast_sincos_r(x, &sv, &cv, &k);
-  const int q = k & 3;
-  *sn = (q & 1) ? cv : sv;
-  *cs = (q & 1) ? sv : cv;
-  if (q == 1 || q == 2) *cs = -*cs;
-  if (q & 2) *sn = -*sn;
+struct PhArg {
+  double S, C, c1, s1;  // table sine and cosine, cos r - 1, sin r
+};
+__device__ __forceinline__ PhArg ph_arg(double x, const double* tab) {
+  constexpr double kBig = 0x1.8p52;
+  constexpr double kPiA = kPio2A * 0x1p-7, kPiB = 0x1.0b4611a626331p-41;  // pi/256 = A + B
+  const double b = fma(x, k256OverPi, kBig), k = b - kBig;
+  const double r = fma(-k, kPiB, fma(-k, kPiA, x));
+  const double2 t = ((const double2*)tab)[__double2loint(b) & (kPhTab - 1)];
+  const double z = r * r;
+  return {t.x, t.y, z * fma(z, 1.0 / 24.0, -0.5), fma(r * z, fma(z, 1.0 / 120.0, -1.0 / 6.0), r)};
 }
-// sin(x + qs pi/2): qs = 0 sin, qs = 1 cos
-__device__ __forceinline__ double fast_sinq(double x, int qs) {
-  double sv, cv;
-  int k;
-  fast_sincos_r(x, &sv, &cv, &k);
-  const int q = (k + qs) & 3;
-  const double v = (q & 1) ? cv : sv;
-  return (q & 2) ? -v : v;
+__device__ __forceinline__ void fast_sincos(double x, double* sn, double* cs, const double* tab) {
+  const PhArg a = ph_arg(x, tab);
+  *sn = a.S + fma(a.C, a.s1, a.S * a.c1);
+  *cs = a.C + fma(-a.S, a.s1, a.C * a.c1);
 }
-__device__ __forceinline__ double fast_sin(double x) { return fast_sinq(x, 0); }
-__device__ __forceinline__ double fast_cos(double x) { return fast_sinq(x, 1); }
+__device__ __forceinline__ double fast_sin(double x, const double* tab) {
+  const PhArg a = ph_arg(x, tab);
+  return a.S + fma(a.C, a.s1, a.S * a.c1);
+}
+__device__ __forceinline__ double fast_cos(double x, const double* tab) {
+  const PhArg a = ph_arg(x, tab);
+  return a.C + fma(-a.S, a.s1, a.C * a.c1);
+}
 
 // Natural log of a finite x > 0 with a table of kLogTab reciprocals: x = m 2^e with m in
 // [1/2, 1); j = the 7 mantissa bits after the leading one picks c_j ~ 1/m (the centre of the
@@ -810,8 +795,8 @@ __device__ __forceinline__ void field_at(const qed_field& F, double x, double y,
         s = cr_sin(kPi * psi / F.p[1], sct);
         c = cr_cos(psi + F.p[3], sct);
       } else {  // K: pi / Psi precomputed
-        s = fast_sin(psi * K->pi_over_len);
-        c = fast_cos(psi + F.p[3]);
+        s = fast_sin(psi * K->pi_over_len, sct);
+        c = fast_cos(psi + F.p[3], sct);
         (void)d;
       }
       const double e = F.p[0] * s * s * c;
@@ -822,7 +807,7 @@ __device__ __forceinline__ void field_at(const qed_field& F, double x, double y,
     const double psi = t - x + F.p[1];
     double sn, cs;
     if (EXACT) cr_sincos(psi, &sn, &cs, sct);
-    else fast_sincos(psi, &sn, &cs);
+    else fast_sincos(psi, &sn, &cs, sct);
     const double ey = F.p[0] * cs, ez = F.p[0] * sn;
     E[1] = ey;
     E[2] = ez;
@@ -834,8 +819,8 @@ __device__ __forceinline__ void field_at(const qed_field& F, double x, double y,
       cr_sincos(t, &st, &ct, sct);
       cr_sincos(x, &sx, &cx, sct);
     } else {
-      fast_sincos(t, &st, &ct);
-      fast_sincos(x, &sx, &cx);
+      fast_sincos(t, &st, &ct, sct);
+      fast_sincos(x, &sx, &cx, sct);
     }
     E[1] = 2.0 * F.p[0] * ct * cx;
     E[2] = 2.0 * F.p[0] * st * cx;
@@ -890,19 +875,15 @@ __device__ __forceinline__ double lookup_g(const double* sg, const Tabs& tb, dou
 __device__ __forceinline__ double lookup_T(const double* sT, const double* ltab, const Tabs& tb, double chi,
                                            unsigned& range) {
   if (!(chi >= tb.cp_min)) return 0.0;  // below the table (T ~ 0) or NaN
-  if (chi == INFINITY) {
-    ++range;
-    return sT[tb.n_cp - 1];
-  }
   const double s = (fast_log(chi, ltab) - tb.lc0) * tb.idlc;
   if (s < 0.0) return 0.0;
-  if (s >= tb.n_cp - 1) {
+  if (!(s < tb.n_cp - 1)) {  // above the table (or infinite)
     ++range;
     return sT[tb.n_cp - 1];
   }
-  const int k = (int)floor(s);
-  const double w = s - k;
-  return (1.0 - w) * sT[k] + w * sT[k + 1];
+  const int k = (int)s;
+  const double w = s - k, t0 = sT[k];
+  return fma(w, sT[k + 1] - t0, t0);
 }
 
 // Largest j with P[j] < u (so P[j] < u <= P[j+1]; P[n-1] = 1 > u) and the position of u in

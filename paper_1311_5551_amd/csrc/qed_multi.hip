@@ -600,6 +600,10 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
 // takes in registers.  A photon whose depth ran out goes to the pair-event queue with its step in
 // its window word.
 // ---------------------------------------------------------------------------
+// the photon kernels whose rates evaluate sin and cos
+template <int FK, bool MIXED>
+constexpr bool kPhTrig = !MIXED && ZeroField<FK>::pw;
+
 template <int FK, bool MIXED>
 __device__ __forceinline__ void multi_photon(const MultiArgs& m, MultiShared& sh, double* tab) {
   using Real = typename std::conditional<MIXED, float, double>::type;
@@ -612,9 +616,11 @@ __device__ __forceinline__ void multi_photon(const MultiArgs& m, MultiShared& sh
     else tab[i] = a.tb.T[i];
   }
   if (!MIXED) stage_logtab(sh.log);
+  double* const ph = tab + m.n_tab;  // (the rates of these fields evaluate sin and cos)
+  if (kPhTrig<FK, MIXED>) stage_phtab(ph);
   zero_shared(sh);
   const int64_t s0 = uni64(m.mc->s0), send = s0 + m.k, chunk = uni32(m.mc->ph_chunk);
-  const double dt = a.sc.dt, rate = a.sc.a_pair * dt;
+  const double dt = a.sc.dt, rate = a.sc.a_pair * dt, s0d = (double)s0;
   const float* const tab32 = (const float*)tab;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t* const ring = sh.ring[wave];
@@ -646,14 +652,14 @@ __device__ __forceinline__ void multi_photon(const MultiArgs& m, MultiShared& sh
     const int64_t g1 = (c1 + kWinGroup - 1) / kWinGroup;
     uint32_t wnext = g < g1 && g * kWinGroup + lane < c1 ? WIN[g * kWinGroup + lane] : kWinEmpty;
     int qh = 0, qn = 0;  // the ring's head and length
-    bool busy = false, pend = false, changed = false;
+    bool busy = false;
     int64_t slot = 0;
-    int32_t n = 0, nend = 0;  // steps since s0
+    int32_t n = 0, nend = 0, nlim = 0;  // steps since s0: next, end, and where the lane stops (conversion)
     double tau = 0.0;
     Rec rec{};
     PairRate pr{0.0, 0.0};  // uniform field: the rate is the same in every step
     unsigned pr_range = 0;
-    unsigned n_field = 0, n_range = 0, n_bad = 0, n_active = 0, n_reads = 0, n_groups = 0;
+    unsigned n_field = 0, n_range = 0, n_bad = 0, n_active = 0, n_reads = 0, n_groups = 0, field0 = 0;
     for (;;) {
       const unsigned long long idle = __ballot(!busy);
       const int ni = __popcll(idle);
@@ -693,11 +699,13 @@ __device__ __forceinline__ void multi_photon(const MultiArgs& m, MultiShared& sh
           n = (int32_t)(max(first, wlo) - s0);
           nend = (int32_t)(last - s0);
           busy = n < nend && !(tau < 0.0);
-          pend = changed = false;
+          nlim = busy ? nend : n;
+          if (busy) n_active -= (unsigned)n;
+          field0 = n_field;
           if (FK == QED_FIELD_UNIFORM && busy) {
             if constexpr (FK == QED_FIELD_UNIFORM) {
               pr_range = 0;
-              pr = pair_rate<FK, MIXED>(sh.F, fK, a.tb, tab, tab32, sh.log, rate, s0, 0.0, dt, (Real)rec.kx,
+              pr = pair_rate<FK, MIXED>(sh.F, fK, a.tb, tab, tab32, sh.log, ph, rate, s0, 0.0, dt, (Real)rec.kx,
                                         (Real)rec.ky, (Real)rec.kz, Real(0), Real(0), 0, pr_range);
             }
           }
@@ -712,35 +720,32 @@ __device__ __forceinline__ void multi_photon(const MultiArgs& m, MultiShared& sh
       }
 #pragma unroll 1
       for (int it = 0; it < kPhInner; ++it) {
-        if (busy && !pend && n < nend) {
-          const int64_t step = s0 + n;
+        if (n < nlim) {
           PairRate r;
           if constexpr (FK == QED_FIELD_LP_PULSE) {
-            r = pair_rate_pw<MIXED>(sh.F, fK, a.tb, tab, tab32, sh.log, a.sc.a_pair, step, rec.A, rec.S, rec.c, n_range);
+            r = pair_rate_pw<MIXED>(sh.F, fK, a.tb, tab, tab32, sh.log, ph, a.sc.a_pair, s0d + (double)n, rec.A, rec.S,
+                                    rec.c, n_range);
           } else if constexpr (FK == QED_FIELD_UNIFORM) {
             r = pr;
             n_range += pr_range;
           } else {
-            r = pair_rate<FK, MIXED>(sh.F, fK, a.tb, tab, tab32, sh.log, rate, step, a.sc.t0 + (double)step * dt, dt,
+            const int64_t step = s0 + n;
+            r = pair_rate<FK, MIXED>(sh.F, fK, a.tb, tab, tab32, sh.log, ph, rate, step, a.sc.t0 + (double)step * dt, dt,
                                      (Real)rec.kx, (Real)rec.ky, (Real)rec.kz, (Real)rec.xb, (Real)rec.yb, rec.bs,
                                      n_range);
           }
-          ++n_active;
           ++n;
           if (r.T > 0.0) {
             ++n_field;
             tau -= r.dtau;
-            changed = true;
-            if (tau <= 0.0) {
-              pend = true;
-              tau = fmax(tau, kTauPendingMin);
-            }
-            if (!isfinite(tau)) ++n_bad;
+            if (tau <= 0.0) nlim = n;
+            if (!(tau < INFINITY)) ++n_bad;  // (-inf is a conversion, clamped below)
           }
         }
       }
-      const bool done = busy && (pend || n >= nend);
-      if (done && changed) TAU[slot] = tau;
+      const bool done = busy && n >= nlim, changed = n_field != field0, pend = changed && tau <= 0.0;
+      if (done) n_active += (unsigned)n;
+      if (done && changed) TAU[slot] = pend ? fmax(tau, kTauPendingMin) : tau;
       if (done && pend) {
         WIN[slot] = (uint32_t)(n - 1);  // the step of the conversion
         n_reads -= (unsigned)(nend - n);
@@ -750,7 +755,7 @@ __device__ __forceinline__ void multi_photon(const MultiArgs& m, MultiShared& sh
         if (qs < a.q.cap) a.q.ent[qs] = ((uint64_t)ii << kEvSlotBits) | (uint64_t)slot;
         else m.evc->overflow = 1;
       }
-      if (done) busy = pend = false;
+      if (done) busy = false;
     }
     count_wave(sh, MC_FIELD, n_field);
     count_wave(sh, MC_RANGE, n_range);
@@ -808,13 +813,13 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi_mid(MultiArgs m) {
 }
 template <int FK, bool MIXED>
 __global__ __launch_bounds__(kMultiBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_multi_lepton(MultiArgs m) {
-  extern __shared__ double tab[];
+  extern __shared__ __attribute__((aligned(16))) double tab[];
   __shared__ MultiShared sh;
   multi_lepton<FK, MIXED>(m, m.round, sh, tab, tab + m.n_tab, blockIdx.x, gridDim.x);
 }
 template <int FK, bool MIXED>
-__global__ __launch_bounds__(kMultiBlock) void k_multi_photon(MultiArgs m) {
-  extern __shared__ double tab[];
+__global__ __launch_bounds__(kMultiBlock) __attribute__((amdgpu_waves_per_eu(FK == QED_FIELD_LP_PULSE ? 5 : 1))) void k_multi_photon(MultiArgs m) {
+  extern __shared__ __attribute__((aligned(16))) double tab[];
   __shared__ MultiShared sh;
   multi_photon<FK, MIXED>(m, sh, tab);
 }
@@ -826,7 +831,7 @@ __global__ __launch_bounds__(kMultiBlock) void k_multi_pairs(MultiArgs m) {
 // generation starts at a later step than its parents', so at most k + 1 of them run.
 template <int FK, bool MIXED>
 __global__ __launch_bounds__(kMultiBlock) void k_multi_finish(MultiArgs m) {
-  extern __shared__ double tab[];
+  extern __shared__ __attribute__((aligned(16))) double tab[];
   __shared__ MultiShared sh;
   auto sync = [] {
     __threadfence();
@@ -851,16 +856,16 @@ hipError_t init_crmath_multi() {
   return upload_crmath(&done);
 }
 
-// dynamic LDS: the rate table, and the lepton kernels' pools
+// dynamic LDS: the rate table, and the lepton kernels' pools or the photon kernels' sine table
 static int multi_tab(int n_eta, int n_cp) { return (std::max(n_eta, n_cp) + 1) / 2 * 2; }
-static size_t multi_shm(int n_tab, bool leptons) {
-  return sizeof(double) * ((size_t)n_tab + (leptons ? (size_t)kMultiWaves * kPool * kPoolWords : 0));
+static size_t multi_shm(int n_tab, bool leptons, bool trig) {
+  return sizeof(double) * ((size_t)n_tab + (leptons ? (size_t)kMultiWaves * kPool * kPoolWords : trig ? 2 * kPhTab : 0));
 }
 
 template <int FK, bool MIXED>
 static int multi_fit(int which, int n_tab) {
   int n = 0;
-  const size_t shm = multi_shm(n_tab, which == 0);
+  const size_t shm = multi_shm(n_tab, which == 0, kPhTrig<FK, MIXED>);
   const hipError_t e =
       which ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_multi_photon<FK, MIXED>, kMultiBlock, shm)
             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_multi_lepton<FK, MIXED>, kMultiBlock, shm);
@@ -881,7 +886,7 @@ int multi_blocks_per_cu(int fk, int which, int n_eta, int n_cp, bool mixed) {
 template <int FK, bool MIXED>
 static void launch_multi_fk(MultiArgs m, hipStream_t s) {
   m.n_tab = multi_tab(m.s.tb.n_eta, m.s.tb.n_cp);
-  const size_t shl = multi_shm(m.n_tab, true), shp = multi_shm(m.n_tab, false);
+  const size_t shl = multi_shm(m.n_tab, true, false), shp = multi_shm(m.n_tab, false, kPhTrig<FK, MIXED>);
   const dim3 b(kMultiBlock);
   const bool pairs = (m.s.sc.flags & QED_PAIRS) != 0;
   for (m.round = 0; m.round < (pairs ? kRounds : 1); ++m.round) {

@@ -397,7 +397,8 @@ struct PairRate {
 // From the photon's direction, energy and birth (general fields)
 template <int FK, bool MIXED>
 __device__ __forceinline__ PairRate pair_rate(const qed_field& sF, const FieldK& fK, const Tabs& tb, const double* sT,
-                                              const float* sT32, const double* sLog, double rate, int64_t step, double t,
+                                              const float* sT32, const double* sLog, const double* sPh, double rate,
+                                              int64_t step, double t,
                                               double dt, typename LepState<MIXED>::Real kx,
                                               typename LepState<MIXED>::Real ky, typename LepState<MIXED>::Real kz,
                                               typename LepState<MIXED>::Real xb, typename LepState<MIXED>::Real yb,
@@ -428,7 +429,7 @@ __device__ __forceinline__ PairRate pair_rate(const qed_field& sF, const FieldK&
     T = lookup32(sT32, tb.n_cp, tb.lc0, tb.idlc, chif, n_range, true);
   } else {
     double E[3], Bf[3];
-    field_at<FK, false>(sF, x, y, t, E, Bf, &fK);
+    field_at<FK, false>(sF, x, y, t, E, Bf, &fK, sPh);
     const double ax = E[0] + (ny * Bf[2] - nz * Bf[1]);
     const double ay = E[1] + (nz * Bf[0] - nx * Bf[2]);
     const double az = E[2] + (nx * Bf[1] - ny * Bf[0]);
@@ -444,9 +445,10 @@ __device__ __forceinline__ PairRate pair_rate(const qed_field& sF, const FieldK&
 // decrement a_pair |e| T(chi) S / 2 (PhotonRecPW)
 template <bool MIXED>
 __device__ __forceinline__ PairRate pair_rate_pw(const qed_field& sF, const FieldK& fK, const Tabs& tb,
-                                                 const double* sT, const float* sT32, const double* sLog, double a_pair,
-                                                 int64_t step, double A, double S, double cr, unsigned& n_range) {
-  const double psi = A + (double)step * S;
+                                                 const double* sT, const float* sT32, const double* sLog,
+                                                 const double* sPh, double a_pair, double step, double A, double S,
+                                                 double cr, unsigned& n_range) {
+  const double psi = MIXED ? A + step * S : fma(step, S, A);
   double T = 0.0, ae = 0.0;
   if (psi >= 0.0 && psi <= sF.p[1]) {
     if (MIXED) {
@@ -457,7 +459,7 @@ __device__ __forceinline__ PairRate pair_rate_pw(const qed_field& sF, const Fiel
       ae = e;
       T = lookup32(sT32, tb.n_cp, tb.lc0, tb.idlc, (float)cr * e, n_range, true);
     } else {
-      const double sn = fast_sin(psi * fK.pi_over_len), cs = fast_cos(psi + sF.p[3]);
+      const double sn = fast_sin(psi * fK.pi_over_len, sPh), cs = fast_cos(psi + sF.p[3], sPh);
       ae = fabs(sF.p[0] * sn * sn * cs);
       T = lookup_T(sT, sLog, tb, cr * ae, n_range);
     }

@@ -721,6 +721,8 @@ __global__ __launch_bounds__(256) void k_photon(StepArgs a) {
   extern __shared__ double smem[];
   __shared__ qed_field sF;  // field of the instance being processed
   __shared__ double sLog[2 * kLogTab];
+  constexpr bool TRIG = !MIXED && ZeroField<FK>::pw;  // the rate evaluates sin and cos
+  __shared__ __attribute__((aligned(16))) double sPh[TRIG ? 2 * kPhTab : 2];
   double* sT = smem;
   float* sT32 = (float*)smem;
   unsigned* sredu = (unsigned*)(smem + a.tb.n_cp);
@@ -729,6 +731,7 @@ __global__ __launch_bounds__(256) void k_photon(StepArgs a) {
     else sT[i] = a.tb.T[i];
   }
   if (!MIXED) stage_logtab(sLog);
+  if (TRIG) stage_phtab(sPh);
 
   const int64_t step = uni64(a.glob->step_cur);
   const double t = a.sc.t0 + (double)step * a.sc.dt;
@@ -891,17 +894,18 @@ __global__ __launch_bounds__(256) void k_photon(StepArgs a) {
       PairRate r;
       if constexpr (FK == QED_FIELD_LP_PULSE) {
         if (MIXED)
-          r = pair_rate_pw<MIXED>(sF, fK, a.tb, sT, sT32, sLog, a.sc.a_pair, step, dbl(0),
+          r = pair_rate_pw<MIXED>(sF, fK, a.tb, sT, sT32, sLog, sPh, a.sc.a_pair, (double)step, dbl(0),
                                   (double)__uint_as_float(w[2]), (double)__uint_as_float(w[3]), uacc[1]);
         else
-          r = pair_rate_pw<MIXED>(sF, fK, a.tb, sT, sT32, sLog, a.sc.a_pair, step, dbl(0), dbl(2), dbl(4), uacc[1]);
+          r = pair_rate_pw<MIXED>(sF, fK, a.tb, sT, sT32, sLog, sPh, a.sc.a_pair, (double)step, dbl(0), dbl(2), dbl(4),
+                                  uacc[1]);
       } else if (MIXED) {
-        r = pair_rate<FK, MIXED>(sF, fK, a.tb, sT, sT32, sLog, rate, step, t, dt, (Real)__uint_as_float(w[0]),
+        r = pair_rate<FK, MIXED>(sF, fK, a.tb, sT, sT32, sLog, sPh, rate, step, t, dt, (Real)__uint_as_float(w[0]),
                                  (Real)__uint_as_float(w[1]), (Real)__uint_as_float(w[2]),
                                  NEED_X ? (Real)__uint_as_float(w[3]) : Real(0),
                                  NEED_Y ? (Real)__uint_as_float(w[4]) : Real(0), NEED_X ? (int32_t)w[5] : 0, uacc[1]);
       } else {
-        r = pair_rate<FK, MIXED>(sF, fK, a.tb, sT, sT32, sLog, rate, step, t, dt, (Real)dbl(0), (Real)dbl(2),
+        r = pair_rate<FK, MIXED>(sF, fK, a.tb, sT, sT32, sLog, sPh, rate, step, t, dt, (Real)dbl(0), (Real)dbl(2),
                                  (Real)dbl(4), NEED_X ? (Real)dbl(6) : Real(0), NEED_Y ? (Real)dbl(8) : Real(0),
                                  NEED_X ? (int32_t)w[10] : 0, uacc[1]);
       }

@@ -34,7 +34,7 @@ static hipError_t upload_crmath(unsigned long long* done) {
     lt[2 * j + 1] = -std::log(c);
   }
   if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_logtab), lt, sizeof(lt));
-  // sine table of the correctly rounded sin and cos: j pi/256, its sine and cosine as double-doubles
+  // sine table of the correctly rounded sin and cos: sin(j pi/256) as double-doubles
   // (relative error below 2^-100) by Taylor series in the same arithmetic
   auto two_sum = [](double a, double b) -> dd {
     const double s = a + b, bb = s - a;
@@ -50,9 +50,10 @@ static hipError_t upload_crmath(unsigned long long* done) {
     const double p = a.hi * b.hi;
     return fast(p, std::fma(a.hi, b.hi, -p) + (a.hi * b.lo + a.lo * b.hi));
   };
-  double sc[kSinCosTab * kSinCosWords], ph[2 * kPhTab];
+  dd sn[kSinTab];
+  double ph[2 * kPhTab];
   const dd unit = {0x1.921fb54442d18p-7, 0x1.1a62633145c07p-61};  // pi / 256
-  for (int j = 0; j < kSinCosTab; ++j) {
+  for (int j = 0; j <= kCircle / 8; ++j) {
     const dd x = mul(unit, dd{(double)j, 0.0}), z = mul(x, x), m = {-z.hi, -z.lo};
     dd ps = f[29], pc = f[28];
     for (int n = 13; n >= 0; --n) {
@@ -60,19 +61,19 @@ static hipError_t upload_crmath(unsigned long long* done) {
       pc = add(mul(pc, m), f[2 * n]);
     }
     ps = mul(ps, x);
-    const double row[kSinCosWords] = {x.hi, x.lo, ps.hi, ps.lo, pc.hi, pc.lo};
-    for (int q = 0; q < kSinCosWords; ++q) sc[kSinCosWords * j + q] = row[q];
-    // the whole circle, by symmetry, for fast_sin and fast_cos
-    for (int o = 0; o < 4; ++o) {  // angles o pi/2 + x and o pi/2 - x
-      const double s4[4] = {ps.hi, pc.hi, -ps.hi, -pc.hi}, c4[4] = {pc.hi, -ps.hi, -pc.hi, ps.hi};
-      const int a = 128 * o + j, b = (128 * o - j) & (kPhTab - 1);
-      ph[2 * a] = s4[o];
-      ph[2 * a + 1] = c4[o];
-      ph[2 * b] = o & 1 ? s4[o] : -s4[o];
-      ph[2 * b + 1] = o & 1 ? -c4[o] : c4[o];
+    // the whole circle by symmetry: angles o pi/2 + x and o pi/2 - x
+    const dd s4[4] = {ps, pc, {-ps.hi, -ps.lo}, {-pc.hi, -pc.lo}};
+    for (int o = 0; o < 4; ++o) {
+      sn[kCircle / 4 * o + j] = s4[o];
+      sn[(kCircle / 4 * o - j) & (kCircle - 1)] = s4[o & 1 ? o : 2 - o];
     }
   }
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_sctab), sc, sizeof(sc));
+  for (int j = kCircle; j < kSinTab; ++j) sn[j] = sn[j - kCircle];
+  for (int j = 0; j < kPhTab; ++j) {
+    ph[2 * j] = sn[j].hi;
+    ph[2 * j + 1] = sn[j + kCircle / 4].hi;
+  }
+  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_sctab), sn, sizeof(sn));
   if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_phtab), ph, sizeof(ph));
   // tables of the correctly rounded log and exp: c_j and -log c_j for the 128 sub-intervals of the
   // mantissa (log c = 2 atanh t, t = (c - 1)/(c + 1), in double-double), and 2^(j/64) by the

@@ -173,15 +173,6 @@ __device__ __noinline__ double cr_sinq_dd(double x, int qs) {
 // ---------------------------------------------------------------------------
 constexpr double kZivEps = 0x1p-66;
 
-__device__ __forceinline__ dd dd_neg(dd a) { return {-a.hi, -a.lo}; }
-
-// x = k pi/2 + r with r as a double-double (the reduction of cr_sincos_dd)
-__device__ __forceinline__ dd reduce_pio2(double x, double* k) {
-  *k = rint(x * kTwoOverPi);
-  dd r = dd_add(dd{x - *k * kPio2A, 0.0}, dd_two_prod(-*k, kPio2B));
-  return dd_fast_two_sum(r.hi, r.lo - *k * kPio2C);
-}
-
 // the double nearest to v when every value within kZivEps |v| of it rounds to it
 __device__ __forceinline__ bool ziv_round(dd v, double* out) {
   const double e = kZivEps * fabs(v.hi);
@@ -190,41 +181,43 @@ __device__ __forceinline__ bool ziv_round(dd v, double* out) {
   return a == b;
 }
 
-// The unrounded result comes from a table: with r = x - k pi/2 as above, j = rint(|r| 256/pi) <= 64 and
-// r' = |r| - j pi/256 (a double-double, |r'| <= pi/512),
-//   sin|r| = S_j cos r' + C_j sin r',  cos r = C_j cos r' - S_j sin r',
-// S_j = sin(j pi/256) and C_j as double-doubles.  cos r' - 1 = -z/2 + z^2/24 - ... (z = r'^2 a
-// double-double in its first term) is below 2^-15.7 and sin r' - r' below 2^-17.3 of r', so their
-// double parts err by less than 2^-69 of the result; the products with S_j and C_j are exact in
-// their leading terms.  The error stays below 2^-67 of the result (S_j and sin r' are at most the
-// result for j >= 1, and j = 0 leaves r' (1 - r'^2/6 + ...) alone; the largest of 3e6 arguments,
-// against 113 bits: 2^-67.9), so the rounding test decides.  One evaluation serves every quadrant (the roles of S and C are selected), where the
-// series for sin and cos were both run by waves whose lanes lie in different quadrants: about 90
-// instructions instead of 300.
-constexpr int kSinCosTab = 65;   // entries j pi/256, j = 0..64
-constexpr int kSinCosWords = 6;  // angle, sine and cosine, high and low words
+// The unrounded result comes from a table of the circle: k = rint(x 256/pi) (from the low bits of
+// x 256/pi + 1.5 2^52), x = k pi/256 + r with r a double-double, |r| <= pi/512 (pi/256 in three parts:
+// x - k A is exact, k B is split exactly),
+//   sin x = S cos r + C sin r,  cos x = C cos r - S sin r,
+// S = sin(k pi/256) and C its cosine as double-doubles.  cos r - 1 = -z/2 + z^2/24 - ... (z = r^2 a
+// double-double in its first term) is below 2^-15.7 and sin r - r below 2^-17.3 of r, so their
+// double parts err by less than 2^-69 of the result; the products with S and C are exact in
+// their leading terms.  The error stays below 2^-67 of the result (where S or C is not zero, it is at
+// most twice the result; the largest of 3e6 arguments, against 113 bits: 2^-67.9), so the rounding
+// test decides.  The whole circle is in the table, so that no lane selects by quadrant or sign:
+// about 75 instructions instead of the 110 of a table of [0, pi/4] and the 300 of the two series.
+constexpr int kCircle = 512;             // angles j pi/256
+constexpr int kSinTab = kCircle + kCircle / 4;  // a quarter more: the cosine is 128 entries ahead
+constexpr int kSinTabWords = 2 * kSinTab;
 constexpr double k256OverPi = 0x1.45f306dc9c883p+6;
-static __constant__ __attribute__((aligned(16))) double c_sctab[kSinCosTab * kSinCosWords];
+constexpr double kRintBig = 0x1.8p52;    // x + this rounds x to an integer, in the low bits of the sum
+static __constant__ __attribute__((aligned(16))) double c_sctab[kSinTabWords];  // sine, high and low word
 // LDS copy of the table for a block (every thread calls this, then a barrier follows)
 __device__ __forceinline__ void stage_sctab(double* dst) {
-  for (int i = threadIdx.x; i < kSinCosTab * kSinCosWords; i += blockDim.x) dst[i] = c_sctab[i];
+  for (int i = threadIdx.x; i < kSinTab; i += blockDim.x) ((double2*)dst)[i] = ((const double2*)c_sctab)[i];
 }
 
-// r' and the table entry of |r|; z = r'^2
 struct ScArg {
-  dd S, C, r;   // table sine and cosine, r'
-  double s3;    // sin r' - r'
-  dd c1;        // cos r' - 1
+  dd S, C, r;   // table sine and cosine, r
+  double s3;    // sin r - r
+  dd c1;        // cos r - 1
 };
-__device__ __forceinline__ ScArg sc_arg(dd r, const double* tab) {
+__device__ __forceinline__ ScArg sc_arg(double x, const double* tab) {
   ScArg a;
-  const bool neg = r.hi < 0.0;
-  const double ah = neg ? -r.hi : r.hi, al = neg ? -r.lo : r.lo;
-  const double2* T = (const double2*)tab + 3 * (int)rint(ah * k256OverPi);
-  const double2 t = T[0], s = T[1], c = T[2];
+  const double b = fma(x, k256OverPi, kRintBig), k = b - kRintBig;
+  const double2* T = (const double2*)tab + (__double2loint(b) & (kCircle - 1));
+  const double2 s = T[0], c = T[kCircle / 4];
   a.S = {s.x, s.y};
   a.C = {c.x, c.y};
-  a.r = dd_two_sum(ah - t.x, al - t.y);  // ah - t.x is exact
+  const dd kb = dd_two_prod(-k, kPio2B * 0x1p-7);
+  const dd t = dd_two_sum(fma(-k, kPio2A * 0x1p-7, x), kb.hi);
+  a.r = dd_fast_two_sum(t.hi, t.lo + fma(-k, kPio2C * 0x1p-7, kb.lo));
   const double rh = a.r.hi;
   const dd z = dd_two_prod(rh, rh);
   const double zl = fma(2.0 * rh, a.r.lo, z.lo);
@@ -234,7 +227,7 @@ __device__ __forceinline__ ScArg sc_arg(dd r, const double* tab) {
   a.c1 = {-0.5 * z.hi, fma(z.hi * z.hi, q, -0.5 * zl)};
   return a;
 }
-// P (1 + c1) + Q (r' + s3) as an unevaluated sum
+// P (1 + c1) + Q (r + s3) as an unevaluated sum
 __device__ __forceinline__ dd sc_combine(dd P, dd Q, const ScArg& a) {
   const dd u = dd_two_prod(P.hi, a.c1.hi), v = dd_two_prod(Q.hi, a.r.hi);
   double lo = fma(P.hi, a.c1.lo, fma(Q.hi, a.s3, fma(Q.hi, a.r.lo, fma(Q.lo, a.r.hi, fma(P.lo, a.c1.hi, P.lo)))));
@@ -242,42 +235,70 @@ __device__ __forceinline__ dd sc_combine(dd P, dd Q, const ScArg& a) {
   const dd w = dd_two_sum(u.hi, v.hi), s = dd_two_sum(P.hi, w.hi);
   return dd_fast_two_sum(s.hi, s.lo + (w.lo + lo));
 }
+__device__ __forceinline__ dd sc_sin(const ScArg& a) { return sc_combine(a.S, a.C, a); }
+__device__ __forceinline__ dd sc_cos(const ScArg& a) { return sc_combine(a.C, dd{-a.S.hi, -a.S.lo}, a); }
 
 __device__ inline void cr_sincos(double x, double* sn, double* cs, const double* tab = c_sctab) {
   if (fabs(x) < 1048576.0) {
-    double k;
-    const dd r = reduce_pio2(x, &k);
-    const ScArg a = sc_arg(r, tab);
-    const dd s = sc_combine(a.S, a.C, a), c = sc_combine(a.C, dd_neg(a.S), a);
-    double sv, cv;
-    if (ziv_round(s, &sv) && ziv_round(c, &cv)) {
-      if (r.hi < 0.0) sv = -sv;
-      const int q = (int)k & 3;
-      *sn = q == 0 ? sv : q == 1 ? cv : q == 2 ? -sv : -cv;
-      *cs = q == 0 ? cv : q == 1 ? -sv : q == 2 ? -cv : sv;
+    const ScArg a = sc_arg(x, tab);
+    double s, c;
+    if (ziv_round(sc_sin(a), &s) && ziv_round(sc_cos(a), &c)) {
+      *sn = s;
+      *cs = c;
       return;
     }
   }
   cr_sincos_dd(x, sn, cs);
 }
 
-// sin(x + qs pi/2): qs = 0 sin, qs = 1 cos
-__device__ inline double cr_sinq(double x, int qs, const double* tab) {
-  if (fabs(x) < 1048576.0) {
-    double k;
-    const dd r = reduce_pio2(x, &k);
-    const ScArg a = sc_arg(r, tab);
-    const int q = ((int)k + qs) & 3;
-    const bool co = (q & 1) != 0;  // cos r, else sin r
-    const dd P = co ? a.C : a.S, Q = co ? dd_neg(a.S) : a.C;
-    double out;
-    if (ziv_round(sc_combine(P, Q, a), &out)) return ((q & 2) != 0) != (!co && r.hi < 0.0) ? -out : out;
-  }
-  return cr_sinq_dd(x, qs);
+__device__ inline double cr_sin(double x, const double* tab = c_sctab) {
+  double out;
+  if (fabs(x) < 1048576.0 && ziv_round(sc_sin(sc_arg(x, tab)), &out)) return out;
+  return cr_sinq_dd(x, 0);
+}
+__device__ inline double cr_cos(double x, const double* tab = c_sctab) {
+  double out;
+  if (fabs(x) < 1048576.0 && ziv_round(sc_cos(sc_arg(x, tab)), &out)) return out;
+  return cr_sinq_dd(x, 1);
 }
 
-__device__ inline double cr_sin(double x, const double* tab = c_sctab) { return cr_sinq(x, 0, tab); }
-__device__ inline double cr_cos(double x, const double* tab = c_sctab) { return cr_sinq(x, 1, tab); }
+// A quotient and a square root of doubles, rounded as the operators round them, taken apart so that
+// quotients with one divisor share its reciprocal and a root shares it with the quotients by it.
+//   recip(b): 1/b by two Newton steps from the hardware's estimate (23 bits); quot(a, R): a r with
+//   one exact remainder added back (Markstein), which is the rounded quotient, as in the operator's
+//   own sequence; left out is its scaling of operands with exponents beyond +-1000.  Zero,
+//   infinite and NaN operands are put right by div_fixup.  4 instructions for each further quotient by the same
+//   divisor instead of 11.
+//   root1(a): for a >= 1; s ~ sqrt a and h ~ 1/(2 sqrt a) by Goldschmidt's iteration from the
+//   estimate of 1/sqrt a, then two exact remainders added back; 1/s from 2h in one Newton step.
+// Bit for bit the operators' results on 1e9 random operands each (divisors 1 to 2^40).  A push has
+// eight quotients and two roots of this kind; with the table of the circle above, the lepton kernel
+// of a collision of 1e6 electrons went from 3.75 to 3.29 ms for 100 steps.
+struct Recip {
+  double b, r;
+};
+__device__ __forceinline__ Recip recip(double b) {
+  double r = __builtin_amdgcn_rcp(b);
+  r = fma(fma(-b, r, 1.0), r, r);
+  r = fma(fma(-b, r, 1.0), r, r);
+  return {b, r};
+}
+__device__ __forceinline__ double quot(double a, const Recip& R) {
+  const double q = a * R.r;
+  return __builtin_amdgcn_div_fixup(fma(fma(-R.b, q, a), R.r, q), R.b, a);
+}
+__device__ __forceinline__ Recip root1(double a) {
+  const double y = __builtin_amdgcn_rsq(a);
+  double s = a * y, h = 0.5 * y;
+  const double e = fma(-h, s, 0.5);
+  s = fma(s, e, s);
+  h = fma(h, e, h);
+  s = fma(fma(-s, s, a), h, s);
+  s = fma(fma(-s, s, a), h, s);
+  if (a == INFINITY) s = a;
+  const double r = 2.0 * h;
+  return {s, fma(fma(-s, r, 1.0), r, r)};
+}
 
 // Fast paths of the correctly rounded exp and log (the same rounding test), both from tables:
 //   exp: x = k ln2/64 + r (double-double, |r| <= 0.00542), e^x = 2^(k/64) (1 + r + r^2/2 + ...).

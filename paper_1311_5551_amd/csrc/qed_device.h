@@ -345,7 +345,7 @@ __device__ __forceinline__ int64_t wrap_index(int64_t i, int n) {
 // up to 2.1e-14); 16 instructions, none of them a selection, instead of 37: the photon sweep of a
 // pulse is bound by their number (k_multi_photon 5.6 -> 3.5 ms for 100 steps of a collision of 1e6
 // electrons, with the loop's bookkeeping cut and five waves per SIMD).
-constexpr int kPhTab = 512;
+constexpr int kPhTab = kCircle;
 static __constant__ __attribute__((aligned(16))) double c_phtab[2 * kPhTab];  // sine, cosine of j pi/256
 // LDS copy of the table for a block (every thread calls this, then a barrier follows)
 __device__ __forceinline__ void stage_phtab(double* dst) {
@@ -355,9 +355,8 @@ struct PhArg {
   double S, C, c1, s1;  // table sine and cosine, cos r - 1, sin r
 };
 __device__ __forceinline__ PhArg ph_arg(double x, const double* tab) {
-  constexpr double kBig = 0x1.8p52;
-  constexpr double kPiA = kPio2A * 0x1p-7, kPiB = 0x1.0b4611a626331p-41;  // pi/256 = A + B
-  const double b = fma(x, k256OverPi, kBig), k = b - kBig;
+  constexpr double kPiA = kPio2A * 0x1p-7, kPiB = kPio2B * 0x1p-7;  // pi/256 = A + B
+  const double b = fma(x, k256OverPi, kRintBig), k = b - kRintBig;
   const double r = fma(-k, kPiB, fma(-k, kPiA, x));
   const double2 t = ((const double2*)tab)[__double2loint(b) & (kPhTab - 1)];
   const double z = r * r;
@@ -427,14 +426,19 @@ __device__ __forceinline__ void fast_sincosf(float x, float* sn, float* cs) {
   *cs = c;
 }
 
-// Per-instance constants of a field derived once per kernel and instance (fast paths only).
+// Per-instance constants of a field derived once per kernel and instance.
 struct FieldK {
   double pi_over_len;  // plane-wave pulse: pi / Psi
+  Recip len;           // and Psi with its reciprocal
 };
 __device__ __forceinline__ FieldK field_k(const qed_field& F) {
-  FieldK k;
-  k.pi_over_len = F.kind == QED_FIELD_LP_PULSE ? kPi / F.p[1] : 0.0;
-  return k;
+  const bool pw = F.kind == QED_FIELD_LP_PULSE;
+  return {pw ? kPi / F.p[1] : 0.0, recip(pw ? F.p[1] : 1.0)};
+}
+// the same in scalar registers, for a block on one instance
+__device__ __forceinline__ FieldK field_k_uniform(const qed_field& F) {
+  const FieldK k = field_k(F);
+  return {uni_f64(k.pi_over_len), {uni_f64(k.len.b), uni_f64(k.len.r)}};
 }
 constexpr double kInvTwoPi = 0.15915494309189533577;
 
@@ -792,7 +796,7 @@ __device__ __forceinline__ void field_at(const qed_field& F, double x, double y,
     if (psi >= 0.0 && psi <= F.p[1]) {
       double s, c, d;
       if (EXACT) {
-        s = cr_sin(kPi * psi / F.p[1], sct);
+        s = cr_sin(K ? quot(kPi * psi, K->len) : kPi * psi / F.p[1], sct);
         c = cr_cos(psi + F.p[3], sct);
       } else {  // K: pi / Psi precomputed
         s = fast_sin(psi * K->pi_over_len, sct);

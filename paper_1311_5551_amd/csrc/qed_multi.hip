@@ -50,7 +50,7 @@ enum { MC_FIELD, MC_RANGE, MC_BAD, MC_EMIT, MC_NULL, MC_DROP, MC_LSTEPS, MC_PSTE
 struct MultiShared {
   qed_field F;
   double log[2 * kLogTab];
-  __attribute__((aligned(16))) double sct[kSinCosTab * kSinCosWords];
+  __attribute__((aligned(16))) double sct[kSinTabWords];
   __attribute__((aligned(16))) double math[kMathTab];
   int64_t scan[kMultiBlock];
   long long fx[3][4];                   // field work, radiated energy, emission defect
@@ -382,7 +382,7 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
       ((uint64_t*)&sh.F)[w] = ((const uint64_t*)&I.field)[w];
     __syncthreads();
     const float tpf0 = (float)sh.F.p[2], psif_max = (float)sh.F.p[1];
-    FieldK fK{uni_f64(field_k(sh.F).pi_over_len)};
+    const FieldK fK = field_k_uniform(sh.F);
     const double eps_min = uni_f64(pair_eps_min(sh.F, a.tb.cp_min));
 
     const int64_t per = (hi - lo + kMultiWaves - 1) / kMultiWaves;
@@ -600,10 +600,6 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
 // takes in registers.  A photon whose depth ran out goes to the pair-event queue with its step in
 // its window word.
 // ---------------------------------------------------------------------------
-// the photon kernels whose rates evaluate sin and cos
-template <int FK, bool MIXED>
-constexpr bool kPhTrig = !MIXED && ZeroField<FK>::pw;
-
 template <int FK, bool MIXED>
 __device__ __forceinline__ void multi_photon(const MultiArgs& m, MultiShared& sh, double* tab) {
   using Real = typename std::conditional<MIXED, float, double>::type;
@@ -616,8 +612,9 @@ __device__ __forceinline__ void multi_photon(const MultiArgs& m, MultiShared& sh
     else tab[i] = a.tb.T[i];
   }
   if (!MIXED) stage_logtab(sh.log);
-  double* const ph = tab + m.n_tab;  // (the rates of these fields evaluate sin and cos)
-  if (kPhTrig<FK, MIXED>) stage_phtab(ph);
+  double* const ph = sh.sct;  // (its table is for the leptons)
+  static_assert(2 * kPhTab <= kSinTabWords, "room for the table");
+  if (!MIXED && ZeroField<FK>::pw) stage_phtab(ph);
   zero_shared(sh);
   const int64_t s0 = uni64(m.mc->s0), send = s0 + m.k, chunk = uni32(m.mc->ph_chunk);
   const double dt = a.sc.dt, rate = a.sc.a_pair * dt, s0d = (double)s0;
@@ -646,7 +643,7 @@ __device__ __forceinline__ void multi_photon(const MultiArgs& m, MultiShared& sh
     for (int w = threadIdx.x; w < (int)(sizeof(qed_field) / 8); w += kMultiBlock)
       ((uint64_t*)&sh.F)[w] = ((const uint64_t*)&a.inst[ii].field)[w];
     __syncthreads();
-    FieldK fK{uni_f64(field_k(sh.F).pi_over_len)};
+    const FieldK fK = field_k_uniform(sh.F);
 
     int64_t g = c0 / kWinGroup + wave;
     const int64_t g1 = (c1 + kWinGroup - 1) / kWinGroup;
@@ -856,16 +853,16 @@ hipError_t init_crmath_multi() {
   return upload_crmath(&done);
 }
 
-// dynamic LDS: the rate table, and the lepton kernels' pools or the photon kernels' sine table
+// dynamic LDS: the rate table, and the lepton kernels' pools
 static int multi_tab(int n_eta, int n_cp) { return (std::max(n_eta, n_cp) + 1) / 2 * 2; }
-static size_t multi_shm(int n_tab, bool leptons, bool trig) {
-  return sizeof(double) * ((size_t)n_tab + (leptons ? (size_t)kMultiWaves * kPool * kPoolWords : trig ? 2 * kPhTab : 0));
+static size_t multi_shm(int n_tab, bool leptons) {
+  return sizeof(double) * ((size_t)n_tab + (leptons ? (size_t)kMultiWaves * kPool * kPoolWords : 0));
 }
 
 template <int FK, bool MIXED>
 static int multi_fit(int which, int n_tab) {
   int n = 0;
-  const size_t shm = multi_shm(n_tab, which == 0, kPhTrig<FK, MIXED>);
+  const size_t shm = multi_shm(n_tab, which == 0);
   const hipError_t e =
       which ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_multi_photon<FK, MIXED>, kMultiBlock, shm)
             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_multi_lepton<FK, MIXED>, kMultiBlock, shm);
@@ -886,7 +883,7 @@ int multi_blocks_per_cu(int fk, int which, int n_eta, int n_cp, bool mixed) {
 template <int FK, bool MIXED>
 static void launch_multi_fk(MultiArgs m, hipStream_t s) {
   m.n_tab = multi_tab(m.s.tb.n_eta, m.s.tb.n_cp);
-  const size_t shl = multi_shm(m.n_tab, true, false), shp = multi_shm(m.n_tab, false, kPhTrig<FK, MIXED>);
+  const size_t shl = multi_shm(m.n_tab, true), shp = multi_shm(m.n_tab, false);
   const dim3 b(kMultiBlock);
   const bool pairs = (m.s.sc.flags & QED_PAIRS) != 0;
   for (m.round = 0; m.round < (pairs ? kRounds : 1); ++m.round) {

@@ -112,13 +112,12 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
     const double ux = st.ux, uy = st.uy, uz = st.uz;
     double tau = st.tau;
     double E[3], Bf[3];
-    field_at<FK>(sF, x, y, t, E, Bf, nullptr, e.sct);
+    field_at<FK>(sF, x, y, t, E, Bf, &fK, e.sct);
     const double umx = add_mul<Z::ex>(ux, hq, E[0]), umy = add_mul<Z::ey>(uy, hq, E[1]),
                  umz = add_mul<Z::ez>(uz, hq, E[2]);
-    const double gm = sqrt(1.0 + (umx * umx + umy * umy + umz * umz));
-    const double hg = hq / gm;
+    const double hg = quot(hq, root1(1.0 + (umx * umx + umy * umy + umz * umz)));
     const double tx = hg * Bf[0], ty = hg * Bf[1], tz = hg * Bf[2];
-    const double sf = 2.0 / (1.0 + dot3<Z::bx, Z::by, Z::bz>(tx, tx, ty, ty, tz, tz));
+    const double sf = quot(2.0, recip(1.0 + dot3<Z::bx, Z::by, Z::bz>(tx, tx, ty, ty, tz, tz)));
     const double sx = sf * tx, sy = sf * ty, sz = sf * tz;
     const double upx = add_cross<Z::bz, Z::by>(umx, umy, tz, umz, ty),
                  upy = add_cross<Z::bx, Z::bz>(umy, umz, tx, umx, tz),
@@ -128,12 +127,13 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
                  ulz = add_cross<Z::by, Z::bx>(umz, upx, sy, upy, sx);
     const double u1x = add_mul<Z::ex>(ulx, hq, E[0]), u1y = add_mul<Z::ey>(uly, hq, E[1]),
                  u1z = add_mul<Z::ez>(ulz, hq, E[2]);
-    const double g1 = sqrt(1.0 + (u1x * u1x + u1y * u1y + u1z * u1z));
-    *wk = 2.0 * hq * dot3<Z::ex, Z::ey, Z::ez>(E[0], ulx + umx, E[1], uly + umy, E[2], ulz + umz) / (g1 + st.g);
-    x += dt * u1x / g1;
-    y += dt * u1y / g1;
-    if (e.d3) z += dt * u1z / g1;
-    after_push(st.x, st.y, x, y, u1z / g1);
+    const Recip G1 = root1(1.0 + (u1x * u1x + u1y * u1y + u1z * u1z));
+    const double g1 = G1.b;
+    *wk = quot(2.0 * hq * dot3<Z::ex, Z::ey, Z::ez>(E[0], ulx + umx, E[1], uly + umy, E[2], ulz + umz), recip(g1 + st.g));
+    x += quot(dt * u1x, G1);
+    y += quot(dt * u1y, G1);
+    if (e.d3) z += quot(dt * u1z, G1);
+    after_push(st.x, st.y, x, y, quot(u1z, G1));
     double wx = u1x, wy = u1y, wz = u1z;  // stored momentum
     st.g = g1;
     if (e.rr) {
@@ -156,7 +156,7 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
       const double eta = eta_of<FK>(g1, u1x, u1y, u1z, E, Bf);
       if (eta > 0.0) {
         const double h = lookup_h(e.sh, e.slog, tb, eta, n_range);
-        tau -= sc.a_gamma * (eta / g1) * h * dt;
+        tau -= sc.a_gamma * quot(eta, G1) * h * dt;
         if (tau <= 0.0) {
           pend = true;
           *eta_out = eta;
@@ -262,11 +262,11 @@ template <bool MIXED>
 __device__ __forceinline__ DriftMove<MIXED> drift_move(const LepState<MIXED>& st, const LepEnv& e) {
   DriftMove<MIXED> m;
   if constexpr (!MIXED) {
-    const double g1 = st.g;
-    m.dx = e.dt * st.ux / g1;
-    m.dy = e.dt * st.uy / g1;
-    m.dz = e.dt * st.uz / g1;
-    m.bad = !isfinite(g1);
+    const Recip g1 = recip(st.g);
+    m.dx = quot(e.dt * st.ux, g1);
+    m.dy = quot(e.dt * st.uy, g1);
+    m.dz = quot(e.dt * st.uz, g1);
+    m.bad = !isfinite(st.g);
   } else {
     const float g1 = sqrtf(1.0f + (st.ux * st.ux + st.uy * st.uy + st.uz * st.uz));
     m.dx = e.dtf * st.ux / g1;

@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   __shared__ qed_field sF;
   __shared__ double sLog[2 * kLogTab];
   constexpr bool TRIG = !MIXED && ZeroField<FK>::pw;  // the push evaluates correctly rounded sin and cos
-  __shared__ __attribute__((aligned(16))) double sSc[TRIG ? kSinCosTab * kSinCosWords : 1];
+  __shared__ __attribute__((aligned(16))) double sSc[TRIG ? kSinTabWords : 2];
   double* sh = smem;
   float* sh32 = (float*)smem;
   long long* s_ll = (long long*)(smem + a.tb.n_eta);  // 16 waves x 2 sums x 4 words
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   LepEnv env{dt, 0.0, (float)dt, emit, rr, rr_q, false, sh, sh32, sLog, sSc};
   double qch = 0.0;  // charge of the species (-1 electrons, +1 positrons)
   float tpf0 = 0.0f, psif_max = 0.0f;
-  FieldK fK{0.0};
+  FieldK fK{};
   // field work and energy radiated (deterministic reaction): exact fixed-point words per wave in
   // LDS, fed from exact sums per lane (LaneSum), so the totals do not depend on the launch shape
   long long* const fx_work = s_ll + (threadIdx.x >> 6) * 8;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       __syncthreads();
       tpf0 = (float)sF.p[2];
       psif_max = (float)sF.p[1];
-      fK.pi_over_len = uni_f64(field_k(sF).pi_over_len);
+      fK = field_k_uniform(sF);
     }
     n_sum += PPT;
     if (n_sum > kLaneSumMax) {  // (beyond 1e9 leptons per instance)
@@ -756,7 +756,7 @@ __global__ __launch_bounds__(256) void k_photon(StepArgs a) {
   // group j of the wave in chunk m0 + r (0 past the instance's chunks)
   int64_t m0 = -1;
   uint64_t mrun = 0;
-  FieldK fK{0.0};
+  FieldK fK{};
   // in-field steps, chi above the table, non-finite tau, in-window steps, window reads, mask reads
   unsigned uacc[6] = {0, 0, 0, 0, 0, 0};
   // the counters of the instance just left: lane sums through LDS atomics (few registers on
@@ -802,7 +802,7 @@ __global__ __launch_bounds__(256) void k_photon(StepArgs a) {
       const uint64_t* src = (const uint64_t*)&a.inst[ii].field;
       for (int w = threadIdx.x; w < (int)(sizeof(qed_field) / 8); w += B) ((uint64_t*)&sF)[w] = src[w];
       __syncthreads();
-      fK.pi_over_len = uni_f64(field_k(sF).pi_over_len);
+      fK = field_k_uniform(sF);
     }
     const int64_t k0 = uni64(pfirst + (c - cb) * CH);  // first slot of the chunk
     const int64_t rem = n - k0;               // slots of the chunk that exist: min(rem, CH)

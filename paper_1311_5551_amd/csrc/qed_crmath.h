@@ -300,6 +300,30 @@ __device__ __forceinline__ Recip root1(double a) {
   return {s, fma(fma(-s, r, 1.0), r, r)};
 }
 
+// The same in FP32 (one Newton step from estimates of 23 bits; exponents beyond +-100 left out)
+struct Recipf {
+  float b, r;
+};
+__device__ __forceinline__ Recipf recip(float b) {
+  const float r = __builtin_amdgcn_rcpf(b);
+  return {b, fmaf(fmaf(-b, r, 1.0f), r, r)};
+}
+__device__ __forceinline__ float quot(float a, const Recipf& R) {
+  const float q = a * R.r;
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-R.b, q, a), R.r, q), R.b, a);
+}
+__device__ __forceinline__ Recipf root1(float a) {
+  const float y = __builtin_amdgcn_rsqf(a);
+  float s = a * y, h = 0.5f * y;
+  const float e = fmaf(-h, s, 0.5f);
+  s = fmaf(s, e, s);
+  h = fmaf(h, e, h);
+  s = fmaf(fmaf(-s, s, a), h, s);
+  if (a == INFINITY) s = a;
+  const float r = 2.0f * h;
+  return {s, fmaf(fmaf(-s, r, 1.0f), r, r)};
+}
+
 // Fast paths of the correctly rounded exp and log (the same rounding test), both from tables:
 //   exp: x = k ln2/64 + r (double-double, |r| <= 0.00542), e^x = 2^(k/64) (1 + r + r^2/2 + ...).
 //        T_j = 2^(j/64) is a double-double; r^2/2 and the terms up to r^7/7! are below 2^-16 of the

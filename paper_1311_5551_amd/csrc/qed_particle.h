@@ -182,10 +182,9 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
     const float hqf = (float)hq;
     const float umx = add_mul<Z::ex>(uxh, hqf, E[0]), umy = add_mul<Z::ey>(uyh, hqf, E[1]),
                 umz = add_mul<Z::ez>(uzh, hqf, E[2]);
-    const float gm = sqrtf(1.0f + (umx * umx + umy * umy + umz * umz));
-    const float hg = hqf / gm;
+    const float hg = quot(hqf, root1(1.0f + (umx * umx + umy * umy + umz * umz)));
     const float tx = hg * Bf[0], ty = hg * Bf[1], tz = hg * Bf[2];
-    const float sf = 2.0f / (1.0f + dot3<Z::bx, Z::by, Z::bz>(tx, tx, ty, ty, tz, tz));
+    const float sf = quot(2.0f, recip(1.0f + dot3<Z::bx, Z::by, Z::bz>(tx, tx, ty, ty, tz, tz)));
     const float sx = sf * tx, sy = sf * ty, sz = sf * tz;
     const float upx = add_cross<Z::bz, Z::by>(umx, umy, tz, umz, ty),
                 upy = add_cross<Z::bx, Z::bz>(umy, umz, tx, umx, tz),
@@ -196,13 +195,14 @@ __device__ __forceinline__ bool lepton_full(LepState<MIXED>& st, const qed_field
     comp_add(uxh, uxl, mul_add<Z::ex>(2.0f * hqf, E[0], rx));
     comp_add(uyh, uyl, mul_add<Z::ey>(2.0f * hqf, E[1], ry));
     comp_add(uzh, uzl, mul_add<Z::ez>(2.0f * hqf, E[2], rz));
-    const float g1 = sqrtf(1.0f + (uxh * uxh + uyh * uyh + uzh * uzh));
-    comp_add(xh, xl, dtf * uxh / g1);
-    comp_add(yh, yl, dtf * uyh / g1);
-    if (e.d3) comp_add(zh, zl, dtf * uzh / g1);
+    const Recipf G1 = root1(1.0f + (uxh * uxh + uyh * uyh + uzh * uzh));
+    const float g1 = G1.b;
+    comp_add(xh, xl, quot(dtf * uxh, G1));
+    comp_add(yh, yl, quot(dtf * uyh, G1));
+    if (e.d3) comp_add(zh, zl, quot(dtf * uzh, G1));
     // field work from the stored states (FP64), so the ledger closes on what is stored
     const double ux1 = (double)uxh + uxl, uy1 = (double)uyh + uyl, uz1 = (double)uzh + uzl;
-    const double g1d = sqrt(1.0 + (ux1 * ux1 + uy1 * uy1 + uz1 * uz1));
+    const double g1d = root1(1.0 + (ux1 * ux1 + uy1 * uy1 + uz1 * uz1)).b;
     *wk = g1d - g0d;
     st.g = g1d;
     if (e.rr) {
@@ -268,11 +268,11 @@ __device__ __forceinline__ DriftMove<MIXED> drift_move(const LepState<MIXED>& st
     m.dz = quot(e.dt * st.uz, g1);
     m.bad = !isfinite(st.g);
   } else {
-    const float g1 = sqrtf(1.0f + (st.ux * st.ux + st.uy * st.uy + st.uz * st.uz));
-    m.dx = e.dtf * st.ux / g1;
-    m.dy = e.dtf * st.uy / g1;
-    m.dz = e.dtf * st.uz / g1;
-    m.bad = !isfinite(g1);
+    const Recipf g1 = root1(1.0f + (st.ux * st.ux + st.uy * st.uy + st.uz * st.uz));
+    m.dx = quot(e.dtf * st.ux, g1);
+    m.dy = quot(e.dtf * st.uy, g1);
+    m.dz = quot(e.dtf * st.uz, g1);
+    m.bad = !isfinite(g1.b);
   }
   return m;
 }

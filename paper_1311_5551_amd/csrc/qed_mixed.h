@@ -75,7 +75,7 @@ __device__ __forceinline__ void field_at32(const qed_field& F, const FieldK& K, 
   } else if (FK == QED_FIELD_GRID_FDTD) {
     // (the binding runs this kind in FP64 only; the gather is here for completeness)
     double e[3], b[3];
-    cic_gather6(F, (const double*)F.fdtd_dev, x, y, e, b);
+    cic_gather6(F, (const double*)F.fdtd_dev, x, y, e, b, &K);
     for (int k = 0; k < 3; ++k) {
       E[k] = (float)e[k];
       B[k] = (float)b[k];
@@ -83,7 +83,7 @@ __device__ __forceinline__ void field_at32(const qed_field& F, const FieldK& K, 
   } else if (FK == QED_FIELD_GRID_CP_STANDING) {
     constexpr int hx[6] = {1, 0, 0, 0, 1, 1}, hy[6] = {0, 1, 0, 1, 0, 1};
     // cell coordinates in FP64 (large domains), weights in FP32
-    const CicAxis X = cic_axis((x - F.x0) / F.dx, F.nx), Y = cic_axis((y - F.y0) / F.dy, F.ny);
+    const CicAxis X = cic_axis(quot(x - F.x0, K.len), F.nx), Y = cic_axis(quot(y - F.y0, K.dy), F.ny);
     float g[6][4];
     cic_nodes(F, (const float*)F.grid_dev, X, Y, g);
     float v[6];

@@ -231,6 +231,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   bool d3 = false;
   LepEnv env{dt, 0.0, (float)dt, emit, rr, rr_q, false, sh, sh32, sLog, sSc};
   double qch = 0.0;  // charge of the species (-1 electrons, +1 positrons)
+  DepositK dK{};
   float tpf0 = 0.0f, psif_max = 0.0f;
   FieldK fK{};
   // field work and energy radiated (deterministic reaction): exact fixed-point words per wave in
@@ -301,6 +302,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       tpf0 = (float)sF.p[2];
       psif_max = (float)sF.p[1];
       fK = field_k_uniform(sF);
+      if constexpr (DEP) dK = deposit_k(sF, qch * sF.p[0], dt);
     }
     n_sum += PPT;
     if (n_sum > kLaneSumMax) {  // (beyond 1e9 leptons per instance)
@@ -350,8 +352,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       for (int j = 0; j < PPT; ++j) {
         const unsigned off = threadIdx.x + j * B;
         if ((int64_t)off >= rem) continue;
-        const double gx = ((double)buf_ld<Real>(C.x, off * SR) - sF.x0) / sF.dx;
-        const double gy = ((double)buf_ld<Real>(C.y, off * SR) - sF.y0) / sF.dy;
+        const double gx = quot((double)buf_ld<Real>(C.x, off * SR) - sF.x0, fK.len);
+        const double gy = quot((double)buf_ld<Real>(C.y, off * SR) - sF.y0, fK.dy);
         if (fabs(gx) < 1e9 && fabs(gy) < 1e9) {
           const int ix = (int)floor(gx), iy = (int)floor(gy);
           lx0 = min(lx0, ix);
@@ -373,9 +375,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       if (bx0 <= bx1 && by0 <= by1 && bx0 != INT_MIN && bx1 != INT_MAX) {
         const int64_t W = (int64_t)bx1 - bx0 + 4, H = (int64_t)by1 - by0 + 4;
         if (W * H <= kDepNodes) {
-          sink.lds = sJ;
-          sink.ox = (int64_t)bx0 - 1;
-          sink.oy = (int64_t)by0 - 1;
+          sink.ox = bx0 - 1;
+          sink.oy = by0 - 1;
           sink.W = (int)W;
           sink.H = (int)H;
           for (int i = threadIdx.x; i < 3 * W * H; i += B) sJ[i] = 0.0;
@@ -420,7 +421,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       const bool pend = lepton_full<FK, MIXED>(st, sF, fK, t, a.sc, a.tb, env, eta_out, wk, rd, uacc[1], uacc[2],
                                                [&](double x0, double y0, double x1, double y1, double vz) {
         // field feedback: the current of this move onto the solver's grid (or the chunk's LDS box)
-        if constexpr (DEP) deposit_current(sF, qch * sF.p[0], dt, x0, y0, x1, y1, vz, sink);
+        if constexpr (DEP) {
+          sink.lds = sJ;
+          if (sink.W) deposit_current<true>(sF, fK, dK, x0, y0, x1, y1, vz, sink);
+          else deposit_current<false>(sF, fK, dK, x0, y0, x1, y1, vz, sink);
+        }
       });
       store_position(off, st);
       buf_st(C.ux, off * SR, st.ux);
@@ -503,14 +508,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     if constexpr (DEP) {
       if (sink.W) {  // block-uniform: the box's sums onto the grid, one atomic per non-zero node
         __syncthreads();
-        const int64_t WH = (int64_t)sink.W * sink.H, plane = (int64_t)sF.nx * sF.ny;
-        for (int64_t i = threadIdx.x; i < 3 * WH; i += B) {
-          const double v = sJ[i];
-          if (v == 0.0) continue;
-          const int comp = (int)(i / WH);
-          const int64_t r = i - comp * WH, ly = r / sink.W, lx = r - ly * sink.W;
-          const int64_t gi = wrap_index(sink.ox + lx, sF.nx), gj = wrap_index(sink.oy + ly, sF.ny);
-          unsafeAtomicAdd(sF.fdtd_dev + (6 + comp) * plane + gj * sF.nx + gi, v);
+        const int W = sink.W, WH = W * sink.H;
+        const int64_t plane = (int64_t)sF.nx * sF.ny;
+        double* const J = sF.fdtd_dev + 6 * plane;
+        // node i of the box at column lx of row ly; the next one of the thread is B nodes on
+        const int by = B / W, bx = B - by * W;
+        int ly = (int)threadIdx.x / W, lx = (int)threadIdx.x - ly * W;
+        for (int i = threadIdx.x; i < WH; i += B) {
+          const double v[3] = {sJ[i], sJ[i + WH], sJ[i + 2 * WH]};
+          if (v[0] != 0.0 || v[1] != 0.0 || v[2] != 0.0) {
+            double* const w = J + wrap_index(sink.oy + ly, sF.ny) * sF.nx + wrap_index(sink.ox + lx, sF.nx);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+              if (v[c] != 0.0) unsafeAtomicAdd(w + c * plane, v[c]);
+          }
+          lx += bx;
+          ly += by;
+          if (lx >= W) {
+            lx -= W;
+            ++ly;
+          }
         }
         __syncthreads();  // the box is zeroed again by the next chunk
       }

@@ -89,6 +89,8 @@ __device__ __forceinline__ void field_at32(const qed_field& F, const FieldK& K, 
     float v[6];
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
+      v[c] = 0.0f;
+      if (!grid_has<float>(c)) continue;
       const float wx = (float)X.w[hx[c]], wy = (float)Y.w[hy[c]];
       v[c] = (1.0f - wx) * (1.0f - wy) * g[c][0] + wx * (1.0f - wy) * g[c][1] + (1.0f - wx) * wy * g[c][2] +
              wx * wy * g[c][3];

@@ -36,7 +36,7 @@ __device__ __forceinline__ void lepton_gamma(LepState<MIXED>& st) {
 template <int FK>
 struct ZeroField {
   static constexpr bool pw = FK == QED_FIELD_LP_PULSE || FK == QED_FIELD_CP_WAVE || FK == QED_FIELD_CP_STANDING;
-  static constexpr bool ex = pw, bx = pw, ey = false, bz = false;
+  static constexpr bool ex = pw || FK == QED_FIELD_GRID_CP_STANDING, bx = ex, ey = false, bz = false;
   static constexpr bool ez = FK == QED_FIELD_LP_PULSE, by = FK == QED_FIELD_LP_PULSE;
 };
 // c + (p q - r s), p q or r s left out where known to be zero

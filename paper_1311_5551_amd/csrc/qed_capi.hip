@@ -107,7 +107,7 @@ constexpr int64_t kDefaultEventQueue = int64_t(1) << 20;
 // much as three single steps: 3 steps take 276 us one by one and 318 us as a run with 1.3e5 electrons
 // in a collision (FP32-mixed; 258 and 256 us with 1e5 in FP64), 4 take 369 and 334 us (344 and 265 us);
 // with 1e6 electrons 1862 and 721 us, with 1e4 in a uniform field 148 and 50 us.  At most 256 steps,
-// so that a run's step offsets and the steps of its events stay small numbers.
+// which bounds a lane's counters and the time of one launch.
 constexpr int64_t kMultiMin = 4, kMultiMax = 256;
 
 struct qed_workspace {

@@ -1133,11 +1133,6 @@ __device__ inline void wave_or_bit(uint64_t* word, int bit) {
 }
 
 // sums over the 64 lanes of a wave, every lane active; every lane gets the result
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
 __device__ __forceinline__ unsigned wave_sum_u(unsigned v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);

@@ -21,8 +21,10 @@
 // kernels is the whole run.
 //
 // Measured against single steps replayed from graphs: a beam of 1e5 electrons through a 10 fs pulse
-// (1200 steps) 97.8 -> 23.2 ms, 1e6 through 30 fs (3800 steps) 726 -> 411 ms, 48 batched beams
-// 485 -> 142 ms, 1e4 electrons in a uniform field (1000 steps) 41.8 -> 23.2 ms.
+// (1200 steps) 97.8 -> 15.2 ms, 1e6 through 30 fs (3800 steps) 726 -> 222 ms, 48 batched beams
+// 485 -> 99 ms, 1e4 electrons in a uniform field (1000 steps) 41.8 -> 7.0 ms.  The sweeps issue vector
+// instructions most of the time (the photon kernel all of it); small runs are the latency of one
+// lane's steps.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

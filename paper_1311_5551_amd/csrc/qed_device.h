@@ -232,6 +232,7 @@ struct MultiCtl {
   int64_t n_lep, n_ph;           // chunk-list lengths of the round
   int32_t lep_chunk, ph_chunk;   // slots per chunk
   unsigned long long ph_ticket;  // next photon chunk to take
+  unsigned long long lep_ticket; // next lepton chunk to take, after each block's first
 };
 
 // largest idx with base[idx] <= c (lands on a non-empty entry; see the chunk-list layout)

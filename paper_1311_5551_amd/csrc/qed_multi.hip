@@ -122,7 +122,12 @@ __device__ inline int64_t multi_begin(const MultiArgs& m, int round, MultiShared
   // gains nothing and halves the lanes that share a push.  1e4 electrons in a uniform field:
   // 8.24 ms with all waves, 6.99 so; at twice the limit the run of 1e5 leptons is slower.)
   const int64_t blocks = total <= (int64_t)kMultiBlock * m.cus ? min(grid, m.cus) : grid;
-  const int64_t room = max(blocks - n_used, (blocks + 1) / 2);
+  // Of large runs several chunks per block, of 16 or more leptons for every lane (a chunk's last
+  // leptons leave lanes idle), dealt as blocks become free: with one per block, 256 beams of 1.3e5
+  // electrons were 256 long chunks and as many of a few positrons, for 512 blocks (4.09 ms per step,
+  // now 1.64).  Below 4.2e6 leptons one chunk per block, as before.
+  const int64_t split = min((int64_t)8, max((int64_t)1, total / (blocks * kMultiBlock * 16)));
+  const int64_t room = max(blocks * split - n_used, (blocks * split + 1) / 2);
   const int64_t chunk = max((int64_t)kLepChunkMin, (total + room - 1) / room);
   int64_t mine = 0;
   for (int i = b; i < e; ++i)
@@ -136,6 +141,7 @@ __device__ inline int64_t multi_begin(const MultiArgs& m, int round, MultiShared
   if (threadIdx.x == 0) {
     m.mc->n_lep = n_ch;
     m.mc->lep_chunk = (int32_t)chunk;
+    m.mc->lep_ticket = (unsigned long long)grid;
     if (round == 0) {
       // the clock moves on now: the run's kernels take its first step from the control words
       m.mc->s0 = m.glob->step_next;
@@ -368,7 +374,7 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
   const unsigned long long below = (1ull << lane) - 1ull;
   const LeptonPool<MIXED> pool{pools + wave * kPool * kPoolWords};
 
-  for (int64_t c = bid; c < n_ch; c += nblk) {
+  for (int64_t c = bid; c < n_ch;) {
     const int idx = uni32(find_entry(m.base_lep, 2 * m.n_inst, c));
     const int ii = idx >> 1, sp = idx & 1;
     const qed_instance& I = a.inst[ii];
@@ -591,6 +597,11 @@ __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, Mult
     count_wave(sh, MC_LSTEPS, lsteps);
     if (pairs) count_wave(sh, MC_PSTEPS, psteps);
     multi_flush(m, sh, ii, sp);
+    if (n_ch <= nblk) break;  // block-uniform
+    __syncthreads();
+    if (threadIdx.x == 0) sh.chunk = (long long)atomicAdd(&m.mc->lep_ticket, 1ull);
+    __syncthreads();
+    c = uni64(sh.chunk);
   }
 }
 

@@ -134,6 +134,41 @@ def test_batched_runs_with_compaction(queue, precision, tables):
     assert sum(l["n_pair"] for l in ra.ledger()) > 100
 
 
+@pytest.mark.parametrize("precision", PRECISIONS)
+def test_more_chunks_than_blocks(precision, tables):
+    """Blocks take further chunks as they become free: more beams than blocks, ragged."""
+    ws = []
+    for i in range(600):
+        n = i % 24
+        w = W.uniform_b(n, 1000.0, 9e-3, 0.15 * W.dt_qed(9e-3), 24, FULL, seed=7)
+        w.instance = i
+        w.capacity = dict(electron=8 * n + 64, positron=8 * n + 64, photon=40 * n + 64)
+        ws.append(w)
+    ra, rb = Run(ws, tables, precision=precision), Run(ws, tables, precision=precision)
+    _single(ra, 24)
+    rb.run(24)
+    _same(ra, rb)
+
+
+@pytest.mark.parametrize("precision", PRECISIONS)
+def test_several_chunks_per_block(precision, tables):
+    """Large runs have several chunks per block (from 4.2e6 leptons on)."""
+    n = 4_300_037
+    w = W.uniform_b(n, 1000.0, 9e-3, 0.15 * W.dt_qed(9e-3), 5, 0, seed=3)
+    w.capacity = dict(electron=n, positron=1, photon=1)
+    ra, rb = Run(w, tables, precision=precision), Run(w, tables, precision=precision)
+    _single(ra, 5)
+    rb.run(5)
+    ra.synchronize()
+    rb.synchronize()
+    a, b = ra.bufs[0]["electron"], rb.bufs[0]["electron"]
+    for k in a:
+        if a[k] is not None and hasattr(a[k], "shape") and len(a[k]) == n:
+            assert a[k].equal(b[k]), k
+    la, lb = ra.ledger()[0], rb.ledger()[0]
+    assert la["particle_steps"] == lb["particle_steps"] and la["lepton_steps_in_field"] == lb["lepton_steps_in_field"]
+
+
 def test_full_photon_buffer_in_a_run(tables):
     # a run whose photons do not fit: everything dropped is counted and its energy booked
     w = W.uniform_b(900, 1000.0, 1e-3, 0.15, 64, W.FLAG_EMIT)

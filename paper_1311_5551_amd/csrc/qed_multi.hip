@@ -53,12 +53,16 @@ struct MultiShared {
   qed_field F;
   double log[2 * kLogTab];
   __attribute__((aligned(16))) double sct[kSinTabWords];
-  __attribute__((aligned(16))) double math[kMathTab];
+  union {  // of the lepton kernels, and of the photon kernels: two blocks of leptons fit a CU's LDS
+    __attribute__((aligned(16))) double math[kMathTab];
+    struct {
+      uint32_t ring[kMultiWaves][kRing], ring_w[kMultiWaves][kRing];
+    };
+  };
   int64_t scan[kMultiBlock];
   long long fx[3][4];                   // field work, radiated energy, emission defect
   unsigned long long cnt[MC_COUNT];
   long long chunk;
-  uint32_t ring[kMultiWaves][kRing], ring_w[kMultiWaves][kRing];
 };
 
 // exclusive prefix of one value per thread over the block; *total the block's sum

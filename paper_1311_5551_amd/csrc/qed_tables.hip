@@ -15,6 +15,13 @@
 //  * pair splits in theta with f = sin^2 theta (the table's own f grid is uniform
 //    in theta), f (1 - f) = sin^2 theta cos^2 theta.
 // One workgroup per table row; reductions in a fixed order (deterministic).
+//
+// A row's time is its integrands, some hundred trapezoid nodes each.  For y <= 12.25 the nodes lie
+// at t = 0.2 k whatever y is, so the hyperbolic functions of t come from an LDS table and a node is
+// one exponential instead of five functions; a row has 1024 threads, each with its own quadrature
+// nodes (four waves per SIMD instead of one), and 63 lanes evaluate six levels of the bisection at
+// once.  Every sum keeps the order it had with 256 threads and one thread per segment, so the
+// tables keep their bits, on which FP32 roundings of sampled momenta depend: the call at 256 x 256 rows takes 4.57 ms, 51.1 before.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,7 +35,24 @@ struct GL16 {
 
 constexpr double kV0 = -70.0;       // lower end of the v = ln y integrals
 constexpr double kPanel = 0.25;     // widest panel in v
-constexpr int kRowThreads = 256;
+constexpr int kRowThreads = 1024;
+constexpr int kSumThreads = 256;    // partial sums of a block's integral
+constexpr int kRowNodes = 4928;     // quadrature nodes of [kV0, ln 745] (307 panels), rounded up
+constexpr int kTrap = 400;          // tabled trapezoid nodes
+
+// sinh(t/2), cosh(2t/3), cosh(5t/3) and cosh(t) at t = 0.2 k
+struct TrapTab {
+  double sh[kTrap], ck[kTrap], cj[kTrap], ct[kTrap];
+};
+__device__ void trap_table(TrapTab& T) {
+  for (int k = threadIdx.x; k < kTrap; k += blockDim.x) {
+    const double t = k * 0.2;
+    T.sh[k] = sinh(0.5 * t);
+    T.ck[k] = cosh(2.0 / 3.0 * t);
+    T.cj[k] = cosh(5.0 / 3.0 * t);
+    T.ct[k] = cosh(t);
+  }
+}
 
 // K_{nu_k}(y) and, if want_j, int_y^inf K_{nu_j}; 0 when y > 745 (below the FP64 range)
 __device__ void bessel_trap(double y, double nu_k, double nu_j, bool want_j, double* K, double* J) {
@@ -54,53 +78,107 @@ __device__ void bessel_trap(double y, double nu_k, double nu_j, bool want_j, dou
   if (J) *J = h * sj * ey;
 }
 
+// the same for nu = 2/3 (and 5/3) with the table's nodes
+__device__ void bessel_tab(const TrapTab& T, double y, bool want_j, double* K, double* J) {
+  if (!(y <= 12.25)) {
+    bessel_trap(y, 2.0 / 3.0, 5.0 / 3.0, want_j, K, J);
+    return;
+  }
+  const double h = 0.2;
+  double sk = 0.5, sj = want_j ? 0.5 : 0.0;
+  double prev = 1.0;
+  for (int k = 1; k < 4000; ++k) {
+    double sh, ck, cj, ct;
+    if (k < kTrap) {
+      sh = T.sh[k];
+      ck = T.ck[k];
+      cj = T.cj[k];
+      ct = T.ct[k];
+    } else {
+      const double t = k * h;
+      sh = sinh(0.5 * t);
+      ck = cosh(2.0 / 3.0 * t);
+      cj = cosh(5.0 / 3.0 * t);
+      ct = cosh(t);
+    }
+    const double e = exp(-2.0 * y * sh * sh);
+    const double fk = e * ck;
+    sk += fk;
+    if (want_j) sj += e * cj / ct;
+    if (fk < prev && fk < 1e-18 * sk && e < 1e-3) break;
+    prev = fk;
+  }
+  const double ey = exp(-y);
+  *K = h * sk * ey;
+  if (J) *J = h * sj * ey;
+}
+
 // F(eta, chi) at v = ln y for an eta row with a = 3 eta / 2; also returns xi and 1 - xi
-__device__ double synch_F_v(double a, double v, double* xi, double* omxi) {
+__device__ double synch_F_v(const TrapTab& T, double a, double v, double* xi, double* omxi) {
   const double y = exp(v);
   const double ay = a * y;
   *omxi = 1.0 / (1.0 + ay);
   *xi = ay * *omxi;
   double k23, j53;
-  bessel_trap(y, 2.0 / 3.0, 5.0 / 3.0, true, &k23, &j53);
+  bessel_tab(T, y, true, &k23, &j53);
   return (*xi) * (*xi) * y * k23 + (*omxi) * y * j53;
 }
 
 // number density in v: F / chi dchi = F (1 - xi) dv
-__device__ double dens_number(double a, double v) {
+__device__ double dens_number(const TrapTab& T, double a, double v) {
   double xi, om;
-  const double F = synch_F_v(a, v, &xi, &om);
+  const double F = synch_F_v(T, a, v, &xi, &om);
   return F * om;
 }
 
 // energy density in v, in units of eta/2: F dchi = (eta/2) F xi (1 - xi) dv
-__device__ double dens_energy(double a, double v) {
+__device__ double dens_energy(const TrapTab& T, double a, double v) {
   double xi, om;
-  const double F = synch_F_v(a, v, &xi, &om);
+  const double F = synch_F_v(T, a, v, &xi, &om);
   return F * xi * om;
 }
 
-// integral over [va, vb] of dens (0 number, 1 energy), panels of width <= kPanel, by one thread
-__device__ double integrate_serial(const GL16& gl, double a, double va, double vb, int which) {
-  if (!(vb > va)) return 0.0;
-  const int np = (int)fmin(ceil((vb - va) / kPanel), 2048.0);
+// integral over [va, vb] of the number density, panels of width <= kPanel, by 16 lanes (all of whose
+// waves' lanes call this): a lane per node, each panel's nodes and then the panels summed in order
+__device__ double integrate_group(const TrapTab& T, const GL16& gl, double a, double va, double vb) {
+  const int q = threadIdx.x & 15, base = threadIdx.x & 48;
+  const int np = vb > va ? (int)fmin(ceil((vb - va) / kPanel), 2048.0) : 0;
   const double w = (vb - va) / np;
   double s = 0.0;
-  for (int p = 0; p < np; ++p) {
+  for (int p = 0; __any(p < np); ++p) {
     const double c = va + (p + 0.5) * w, hw = 0.5 * w;
+    double f = 0.0;
+    if (p < np) f = gl.w[q] * dens_number(T, a, c + hw * gl.x[q]);
     double ps = 0.0;
-    for (int q = 0; q < 16; ++q) {
-      const double v = c + hw * gl.x[q];
-      ps += gl.w[q] * (which ? dens_energy(a, v) : dens_number(a, v));
-    }
-    s += ps * hw;
+    for (int k = 0; k < 16; ++k) ps += __shfl(f, base + k);
+    if (p < np) s += ps * hw;
   }
   return s;
 }
 
-__device__ double block_reduce(double v, double* red) {
-  red[threadIdx.x] = v;
+// integral over [va, vb] of dens (0 number, 1 energy) with the panel nodes spread over the workgroup;
+// the sums by kSumThreads threads
+__device__ double integrate_block(const TrapTab& T, const GL16& gl, double a, double va, double vb, int which,
+                                  double* red, double* node) {
+  int nn = 0;
+  if (vb > va) {
+    const int np = (int)fmin(ceil((vb - va) / kPanel), (double)(kRowNodes / 16));
+    const double w = (vb - va) / np, hw = 0.5 * w;
+    nn = np * 16;
+    for (int n = threadIdx.x; n < nn; n += blockDim.x) {
+      const int p = n >> 4, q = n & 15;
+      const double v = va + (p + 0.5) * w + hw * gl.x[q];
+      node[n] = gl.w[q] * hw * (which ? dens_energy(T, a, v) : dens_number(T, a, v));
+    }
+  }
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
+  if (threadIdx.x < kSumThreads) {
+    double s = 0.0;
+    for (int n = threadIdx.x; n < nn; n += kSumThreads) s += node[n];
+    red[threadIdx.x] = s;
+  }
+  __syncthreads();
+  for (int s = kSumThreads / 2; s > 0; s >>= 1) {
     if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
     __syncthreads();
   }
@@ -109,29 +187,16 @@ __device__ double block_reduce(double v, double* red) {
   return r;
 }
 
-// the same integral with the panel nodes spread over the workgroup
-__device__ double integrate_block(const GL16& gl, double a, double va, double vb, int which, double* red) {
-  double s = 0.0;
-  if (vb > va) {
-    const int np = (int)fmin(ceil((vb - va) / kPanel), 2048.0);
-    const double w = (vb - va) / np, hw = 0.5 * w;
-    for (int n = threadIdx.x; n < np * 16; n += blockDim.x) {
-      const int p = n >> 4, q = n & 15;
-      const double v = va + (p + 0.5) * w + hw * gl.x[q];
-      s += gl.w[q] * hw * (which ? dens_energy(a, v) : dens_number(a, v));
-    }
-  }
-  return block_reduce(s, red);
-}
-
 // Row i of h, g and P_chi.  Steps: total energy of the spectrum (and g from it); v_c of the 1e-9 energy cut
 // (Newton on the cumulative energy); log-spaced chi grid from chi_min to eta/2; number
 // integral of each segment; prefix sums normalised by h = the total number integral.
 __global__ __launch_bounds__(kRowThreads) void k_build_eta_rows(qed_table_params p, GL16 gl, double* h,
                                                                   double* lnchi_min, double* dlnchi, double* P,
                                                                   double* g) {
-  __shared__ double red[kRowThreads];
+  __shared__ double red[kSumThreads];
   __shared__ double seg[1024];
+  __shared__ double node[kRowNodes];
+  __shared__ TrapTab T;
   __shared__ double sh_vc;
   const int i = blockIdx.x;
   const double le0 = log(p.eta_min), le1 = log(p.eta_max);
@@ -139,29 +204,48 @@ __global__ __launch_bounds__(kRowThreads) void k_build_eta_rows(qed_table_params
   const double a = 1.5 * eta;
   const double stop = log(0.5 * eta);
   const double vmax = log(745.0);
+  trap_table(T);
+  __syncthreads();
 
   // total energy (tail below kV0 ~ y^{4/3}: (3/4) of the density there)
-  const double e_tail = 0.75 * dens_energy(a, kV0);
-  const double e_tot = e_tail + integrate_block(gl, a, kV0, vmax, 1, red);
+  const double e_tail = 0.75 * dens_energy(T, a, kV0);
+  const double e_tot = e_tail + integrate_block(T, gl, a, kV0, vmax, 1, red, node);
   const double target = p.cutoff_energy_frac * e_tot;
   // g = 3 sqrt3 / (2 pi eta^2) int_0^{eta/2} F dchi, and the energy density is in units of eta/2
   if (threadIdx.x == 0) g[i] = 3.0 * sqrt(3.0) / (4.0 * kPi * eta) * e_tot;
 
   // starting point: at small y the cumulative energy is (3/4) of the density (power law)
-  if (threadIdx.x == 0) {
+  // (bisection, 80 halvings; lane m of the first wave holds point m of the next levels, as a heap:
+  // its halves left or right by the bits of m below the leading one)
+  if (threadIdx.x < 64) {
     double lo = kV0, hi = vmax;
-    for (int it = 0; it < 80; ++it) {
-      const double mid = 0.5 * (lo + hi);
-      if (0.75 * dens_energy(a, mid) > target) hi = mid; else lo = mid;
+    const int m = threadIdx.x ? threadIdx.x : 1, depth = 31 - __clz(m);
+    for (int done = 0; done < 80;) {
+      double l = lo, u = hi, mid = 0.5 * (l + u);
+      for (int b = depth - 1; b >= 0; --b) {
+        if ((m >> b) & 1) l = mid; else u = mid;
+        mid = 0.5 * (l + u);
+      }
+      const unsigned long long above = __ballot(0.75 * dens_energy(T, a, mid) > target);
+      for (int at = 1; at < 64 && done < 80; ++done) {
+        mid = 0.5 * (lo + hi);
+        if ((above >> at) & 1) {
+          hi = mid;
+          at = 2 * at;
+        } else {
+          lo = mid;
+          at = 2 * at + 1;
+        }
+      }
     }
-    sh_vc = 0.5 * (lo + hi);
+    if (threadIdx.x == 0) sh_vc = 0.5 * (lo + hi);
   }
   __syncthreads();
   double vc = sh_vc;
   // Newton on E(v) = tail + int_{v0}^{v} dens_energy = target
   for (int it = 0; it < 30; ++it) {
-    const double E = e_tail + integrate_block(gl, a, kV0, vc, 1, red);
-    const double d = (E - target) / dens_energy(a, vc);
+    const double E = e_tail + integrate_block(T, gl, a, kV0, vc, 1, red, node);
+    const double d = (E - target) / dens_energy(T, a, vc);
     vc = fmin(fmax(vc - d, kV0), vmax);  // stay inside the integration range
     if (!(fabs(d) >= 1e-15 * fabs(vc))) break;
   }
@@ -178,9 +262,12 @@ __global__ __launch_bounds__(kRowThreads) void k_build_eta_rows(qed_table_params
     const double v = d - log(a) - log(-expm1(d));
     return v < vmax ? v : vmax;
   };
-  const double below = 3.0 * dens_number(a, kV0) + integrate_block(gl, a, kV0, vc, 0, red);
-  for (int j = 1 + threadIdx.x; j < n; j += blockDim.x) {
-    seg[j] = integrate_serial(gl, a, v_of(j - 1), v_of(j), 0);
+  const double below = 3.0 * dens_number(T, a, kV0) + integrate_block(T, gl, a, kV0, vc, 0, red, node);
+  for (int j0 = 1; j0 < n; j0 += kRowThreads / 16) {  // a segment per 16 lanes
+    const int j = j0 + (threadIdx.x >> 4);
+    const double va = j < n ? v_of(j - 1) : 0.0, vb = j < n ? v_of(j) : 0.0;
+    const double v = integrate_group(T, gl, a, va, vb);
+    if (j < n && (threadIdx.x & 15) == 0) seg[j] = v;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -201,13 +288,13 @@ __global__ __launch_bounds__(kRowThreads) void k_build_eta_rows(qed_table_params
 
 // unnormalised pair split density times df/dtheta, at f = sin^2 theta:
 // (2 + g)/g K_{2/3}(1/(3 chi g)) sin(2 theta), g = f(1 - f) = sin^2 theta cos^2 theta
-__device__ double pair_integrand(double chi, double theta) {
+__device__ double pair_integrand(const TrapTab& T, double chi, double theta) {
   double s, c;
   sincos(theta, &s, &c);
   const double g = s * s * c * c;
   if (!(g > 0.0)) return 0.0;
   double k23;
-  bessel_trap(1.0 / (3.0 * chi * g), 2.0 / 3.0, 0.0, false, &k23, nullptr);
+  bessel_tab(T, 1.0 / (3.0 * chi * g), false, &k23, nullptr);
   return (2.0 + g) / g * k23 * (2.0 * s * c);
 }
 
@@ -216,7 +303,10 @@ __device__ double pair_integrand(double chi, double theta) {
 __global__ __launch_bounds__(kRowThreads) void k_build_pair_rows(qed_table_params p, GL16 gl, double* T,
                                                                    double* fgrid, double* Pf, double* knorm) {
   __shared__ double seg[1024];
+  __shared__ TrapTab T32;
   const int k = blockIdx.x;
+  trap_table(T32);
+  __syncthreads();
   const double lc0 = log(p.chi_pair_min), lc1 = log(p.chi_pair_max);
   const double chi = exp(lc0 + k * ((lc1 - lc0) / (p.n_chi_pair - 1)));
   const int n = p.n_f;
@@ -226,16 +316,18 @@ __global__ __launch_bounds__(kRowThreads) void k_build_pair_rows(qed_table_param
     bessel_trap(2.0 / (3.0 * chi), 1.0 / 3.0, 0.0, false, &k13, nullptr);
     T[k] = 0.16 * k13 * k13 / chi;
   }
-  for (int l = 1 + threadIdx.x; l < n; l += blockDim.x) {
+  for (int l0 = 1; l0 < n; l0 += kRowThreads / 16) {  // a segment per 16 lanes, each half in order
+    const int l = l0 + (threadIdx.x >> 4), q = threadIdx.x & 15, base = threadIdx.x & 48;
     const double ta = (l - 1) * dth;
     double s = 0.0;
     for (int half = 0; half < 2; ++half) {
       const double c = ta + (half + 0.5) * 0.5 * dth, hw = 0.25 * dth;
+      const double f = l < n ? gl.w[q] * pair_integrand(T32, chi, c + hw * gl.x[q]) : 0.0;
       double ps = 0.0;
-      for (int q = 0; q < 16; ++q) ps += gl.w[q] * pair_integrand(chi, c + hw * gl.x[q]);
+      for (int r = 0; r < 16; ++r) ps += __shfl(f, base + r);
       s += ps * hw;
     }
-    seg[l] = s;
+    if (l < n && q == 0) seg[l] = s;
   }
   __syncthreads();
   if (threadIdx.x == 0) {

@@ -264,7 +264,9 @@ qed_status qed_sort_static(qed_workspace* ws, const qed_step_params* params, qed
  * a pair again (the paper deletes photons that cannot matter for pair creation, Sec. 3.1); their
  * energy goes to the ledger's retired_energy and each is counted in its instance's photon
  * spectrum.  Then it puts the photons whose window is over in front of the others (the photon
- * sweep starts after them) and rebuilds the live masks of the groups of 64 photon slots.
+ * sweep starts after them) and rebuilds the live masks of the groups of 64 photon slots.  After a
+ * sort it makes the windows again first; before the first step after a qed_bind no photon has a
+ * window, and only converted photons are removed.
  * Call it periodically (e.g. every 100 steps).  Async; graph-capturable. */
 qed_status qed_compact(qed_workspace* ws, qed_stream stream);
 

@@ -156,6 +156,7 @@ struct qed_workspace {
   uint64_t* d_lmask = nullptr;  // live masks of the photon slot groups (kWinGroup slots each), at acc.lmask_off
   size_t lmask_len = 0;
   bool win_valid = false;
+  bool win_made = false;        // windows were made since the bind, with the constants below
   bool win_front = false;       // a front that sorts left is valid for the constants below
   double win_t0 = 0.0, win_dt = 0.0, win_cp_min = 0.0;
   int block[2] = {256, 256}, ppt[2] = {4, 4};  // launch shapes: [0] lepton sweep, [1] photon sweep
@@ -521,22 +522,24 @@ qed_status enqueue_multi(const qed_tables* tb, qed_workspace* ws, const qed_step
   return QED_OK;
 }
 
-// (Re)computes the photons' pair windows when the step constants or tables differ from those
-// they were made with.  Enqueued on `s` outside any graph capture.
+// (Re)computes the photons' pair windows.  Enqueued on `s` outside any graph capture.
+qed_status make_windows(qed_workspace* ws, double t0, double dt, double cp_min, hipStream_t s) {
+  const bool same = ws->win_made && ws->win_t0 == t0 && ws->win_dt == dt && ws->win_cp_min == cp_min;
+  launch_photon_windows(ws->field_kind, ws->d_inst, ws->n_inst, ws->d_acc, ws->d_glob, ws->d_win, ws->d_rec, ws->d_lmask,
+                        t0, dt, cp_min, ws->prec == QED_FP32_MIXED, ws->win_front && same, s);
+  HIP_TRY(hipGetLastError());
+  ws->win_front = false;
+  ws->win_valid = ws->win_made = true;
+  ws->win_t0 = t0;
+  ws->win_dt = dt;
+  ws->win_cp_min = cp_min;
+  return QED_OK;
+}
+// the same when the step constants or tables differ from those the windows were made with
 qed_status ensure_windows(const qed_tables* tb, qed_workspace* ws, const qed_step_params* p, hipStream_t s) {
   const double cp_min = device_tabs(tb).cp_min;
   if (ws->win_valid && ws->win_t0 == p->t0 && ws->win_dt == p->dt && ws->win_cp_min == cp_min) return QED_OK;
-  launch_photon_windows(ws->field_kind, ws->d_inst, ws->n_inst, ws->d_acc, ws->d_glob, ws->d_win, ws->d_rec, ws->d_lmask,
-                        p->t0, p->dt, cp_min,
-                        ws->prec == QED_FP32_MIXED,
-                        ws->win_front && ws->win_t0 == p->t0 && ws->win_dt == p->dt && ws->win_cp_min == cp_min, s);
-  HIP_TRY(hipGetLastError());
-  ws->win_front = false;
-  ws->win_valid = true;
-  ws->win_t0 = p->t0;
-  ws->win_dt = p->dt;
-  ws->win_cp_min = cp_min;
-  return QED_OK;
+  return make_windows(ws, p->t0, p->dt, cp_min, s);
 }
 
 static bool grid_kind(int kind) { return kind == QED_FIELD_GRID_CP_STANDING || kind == QED_FIELD_GRID_FDTD; }
@@ -885,7 +888,7 @@ qed_status qed_bind(qed_workspace* ws, const qed_instance* inst, int32_t n_inst,
     ws->win_len = movers ? movers : 1;
     ws->rec_bytes = rec_bytes;
   }
-  ws->win_valid = false;  // computed by the first step, which knows t0, dt and the tables
+  ws->win_valid = ws->win_made = false;  // made by the first step, which knows t0, dt and the tables
   ws->win_front = false;
   if (ws->retire.spec) HIP_TRY(hipMemset(ws->retire.spec, 0, ws->spec_len * sizeof(unsigned long long)));
   // emission queue: the wave segments of the lepton sweep (a lepton emits at most once per step)
@@ -1113,12 +1116,17 @@ qed_status qed_profile_read(qed_workspace* ws, double* ms, int64_t* launches) {
 qed_status qed_compact(qed_workspace* ws, qed_stream stream) {
   if (!ws) return fail(QED_ERR_ARG, "workspace is NULL");
   if (!ws->bound) return fail(QED_ERR_STATE, "no instances bound");
+  // After a sort the windows are not those of the photons in their slots: they are made again (and
+  // the next step need not) before photons are retired or partitioned by them.  Before the first
+  // step after a bind there are none: the compaction then only removes converted photons.
+  if (ws->win_made && !ws->win_valid) {
+    const qed_status st = make_windows(ws, ws->win_t0, ws->win_dt, ws->win_cp_min, (hipStream_t)stream);
+    if (st) return st;
+  }
   launch_compact(ws->field_kind, ws->d_inst, ws->n_inst, ws->d_acc, ws->d_glob, ws->d_movers, ws->d_win, ws->d_rec,
-                 ws->d_lmask, ws->prec == QED_FP32_MIXED, ws->retire, (hipStream_t)stream);
+                 ws->d_lmask, ws->prec == QED_FP32_MIXED, ws->win_made ? ws->retire : RetireSpec(), ws->win_made,
+                 (hipStream_t)stream);
   HIP_TRY(hipGetLastError());
-  // after a sort the windows are not yet those of the photons in their slots: a front made from
-  // them does not outlive the next step's rebuild
-  if (!ws->win_valid) ws->win_front = false;
   return QED_OK;
 }
 

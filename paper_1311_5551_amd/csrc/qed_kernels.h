@@ -100,7 +100,8 @@ void launch_multi(int fk, MultiArgs m, bool mixed, hipStream_t s);
 void launch_init_tau(const qed_instance* inst, int n_inst, hipStream_t s);
 void launch_ledger(const qed_instance* inst, int n_inst, InstAcc* acc, bool mixed, hipStream_t s);
 void launch_compact(int fk, const qed_instance* inst, int n_inst, InstAcc* acc, const Glob* glob, int64_t* movers,
-                    uint32_t* win, void* rec, uint64_t* lmask, bool mixed, const RetireSpec& rs, hipStream_t s);
+                    uint32_t* win, void* rec, uint64_t* lmask, bool mixed, const RetireSpec& rs, bool partition,
+                    hipStream_t s);
 void launch_photon_windows(int fk, const qed_instance* inst, int n_inst, InstAcc* acc, const Glob* glob, uint32_t* win,
                            void* rec, uint64_t* lmask, double t0, double dt, double cp_min, bool mixed, bool keep_front,
                            hipStream_t s);

@@ -1749,7 +1749,8 @@ void launch_photon_windows(int fk, const qed_instance* inst, int n_inst, InstAcc
 }
 
 void launch_compact(int fk, const qed_instance* inst, int n_inst, InstAcc* acc, const Glob* glob, int64_t* movers,
-                    uint32_t* win, void* rec, uint64_t* lmask, bool mixed, const RetireSpec& rs, hipStream_t s) {
+                    uint32_t* win, void* rec, uint64_t* lmask, bool mixed, const RetireSpec& rs, bool partition,
+                    hipStream_t s) {
   const int rw = photon_rec_bytes(mixed, fk) / 8;
   RetireArgs r{};
   r.on = rs.on;
@@ -1769,6 +1770,7 @@ void launch_compact(int fk, const qed_instance* inst, int n_inst, InstAcc* acc, 
   if (mixed) hipLaunchKernelGGL(k_compact_fill<true>, g, dim3(256), 0, s, inst, acc, glob, movers, win, rec, rw, r);
   else hipLaunchKernelGGL(k_compact_fill<false>, g, dim3(256), 0, s, inst, acc, glob, movers, win, rec, rw, r);
   hipLaunchKernelGGL(k_compact_finish, dim3(1), dim3(256), 0, s, inst, n_inst, acc);
+  if (!partition) return;
   hipLaunchKernelGGL(k_part_prep, dim3(1), dim3(256), 0, s, inst, n_inst, acc);
   hipLaunchKernelGGL(k_part_count, g, dim3(256), 0, s, acc, glob, win);
   hipLaunchKernelGGL(k_part_movers, g, dim3(256), 0, s, acc, glob, win, movers);

@@ -230,9 +230,14 @@ struct Glob {
 struct MultiCtl {
   int64_t s0;                    // its first step
   int64_t n_lep, n_ph;           // chunk-list lengths of the round
+  int64_t n_left;                // its leptons
   int32_t lep_chunk, ph_chunk;   // slots per chunk
   unsigned long long ph_ticket;  // next photon chunk to take
   unsigned long long lep_ticket; // next lepton chunk to take, after each block's first
+  // k_multi_tail
+  unsigned long long pub;        // phase << 32 | blocks that may take part << 16 | blocks taking part
+  unsigned long long pair_ticket;  // next share of the pair events
+  uint32_t joined, arrived;      // blocks that have started; that have ended the phase
 };
 
 // largest idx with base[idx] <= c (lands on a non-empty entry; see the chunk-list layout)

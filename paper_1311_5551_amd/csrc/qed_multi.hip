@@ -14,11 +14,13 @@
 //   k_multi_mid     the photon chunk list: the photons present before and those just emitted
 //   k_multi_photon  every photon inside its window to the end of the run, or to its conversion
 //   k_multi_pairs   the pairs of the converted photons (appended with their first step)
-// and the same again for the new leptons, their photons, and so on: kRounds rounds of grid-wide
-// launches, then k_multi_finish, one block that repeats the rounds until no particle is left.
-// Generations shrink fast (a photon that converts is one of hundreds), and each starts at a later
-// step than the one before, so the rounds end.  Without pair creation one round of the first two
-// kernels is the whole run.
+// and the same again for the new leptons, their photons, and so on: kRounds rounds of launches,
+// then k_multi_tail, whose blocks go on with the rounds until no particle is left.  In a beam that
+// crosses a pulse a generation is some hundred times smaller than the one before, and the tail has
+// nothing or a few leptons to do; in a cascade (standing waves of a0 near 1000) most particles are of
+// later generations, and the tail fills the chip as the launches before it do.  Each generation
+// starts at a later step than the one before, so the rounds end.  Without pair creation one round of
+// the first two kernels is the whole run.
 //
 // Measured against single steps replayed from graphs: a beam of 1e5 electrons through a 10 fs pulse
 // (1200 steps) 97.8 -> 15.2 ms, 1e6 through 30 fs (3800 steps) 726 -> 222 ms, 48 batched beams
@@ -26,6 +28,7 @@
 // instructions most of the time (the photon kernel all of it); small runs are the latency of one
 // lane's steps.
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stdint.h>
 
 #include <algorithm>
@@ -39,8 +42,9 @@
 namespace qedk {
 
 constexpr int kMultiBlock = 256, kMultiWaves = kMultiBlock / 64;
-constexpr int kRounds = 3;       // grid-wide rounds before k_multi_finish
+constexpr int kRounds = 3;       // rounds of launches before k_multi_tail
 constexpr int kLepChunkMin = 16; // fewest leptons a block takes
+constexpr int kPairBlocks = 256; // blocks of k_multi_pairs
 constexpr int kRefillLep = 8, kRefillPh = 8;  // idle lanes at which a wave takes new particles
 constexpr int kPhInner = 4;      // photon steps between two looks at the idle lanes
 constexpr int kRing = 128;       // per-wave ring of photon slots waiting for a lane
@@ -89,8 +93,9 @@ __device__ __forceinline__ int64_t clamp_count(const qed_species& S) {
   return r;
 }
 
-// Lepton slots of the round and their chunk list; one block.  Returns the number of leptons.
-__device__ inline int64_t multi_begin(const MultiArgs& m, int round, MultiShared& sh, int grid) {
+// Lepton slots of the round and their chunk list; one block.  `dealt`: chunks that the blocks take
+// without a ticket (their first ones).
+__device__ inline void multi_begin(const MultiArgs& m, int round, MultiShared& sh, int grid, int dealt) {
   const qed_instance* inst = m.s.inst;
   InstAcc* acc = m.s.acc;
   const int per = (m.n_inst + kMultiBlock - 1) / kMultiBlock;
@@ -144,16 +149,18 @@ __device__ inline int64_t multi_begin(const MultiArgs& m, int round, MultiShared
     }
   if (threadIdx.x == 0) {
     m.mc->n_lep = n_ch;
+    m.mc->n_left = total;
     m.mc->lep_chunk = (int32_t)chunk;
-    m.mc->lep_ticket = (unsigned long long)grid;
+    m.mc->lep_ticket = (unsigned long long)dealt;
     if (round == 0) {
+      m.mc->pub = 0;
+      m.mc->joined = m.mc->arrived = 0;
       // the clock moves on now: the run's kernels take its first step from the control words
       m.mc->s0 = m.glob->step_next;
       m.glob->step_cur = m.glob->step_next + m.k - 1;
       m.glob->step_next += m.k;
     }
   }
-  return total;
 }
 
 // Photon slots of the round, in chunks of whole groups; one block.
@@ -352,6 +359,7 @@ struct PhotonStage {
   }
 };
 
+// `bid`: the block's first chunk; it takes others by tickets where there are more than `nblk`.
 template <int FK, bool MIXED>
 __device__ __forceinline__ void multi_lepton(const MultiArgs& m, int round, MultiShared& sh, double* tab,
                                              double* pools, int bid, int nblk) {
@@ -819,7 +827,7 @@ __device__ __forceinline__ void multi_pairs(const MultiArgs& m, int bid, int nbl
 
 __global__ __launch_bounds__(kMultiBlock) void k_multi_begin(MultiArgs m) {
   __shared__ MultiShared sh;
-  multi_begin(m, m.round, sh, m.lep_grid);
+  multi_begin(m, m.round, sh, m.lep_grid, m.round < kRounds ? m.lep_grid : 0);
 }
 __global__ __launch_bounds__(kMultiBlock) void k_multi_mid(MultiArgs m) {
   __shared__ MultiShared sh;
@@ -841,27 +849,110 @@ template <int FK, bool MIXED>
 __global__ __launch_bounds__(kMultiBlock) void k_multi_pairs(MultiArgs m) {
   multi_pairs<FK, MIXED>(m, blockIdx.x, gridDim.x);
 }
-// The last generations: the same five passes in one block until no new lepton is left.  Each
-// generation starts at a later step than its parents', so at most k + 1 of them run.
+// The rounds that are left, until no new lepton is: the same passes as phases of one launch, over
+// as many blocks as are running.
+//
+// Blocks join as they start, and those that have joined by the start of a phase take part in it:
+// they take its work by tickets, and the last of them to end it prepares the next one (the chunk
+// lists, alone) and publishes it with the number of blocks that have joined by then.  A block waits
+// only for blocks that have joined, which are running, and every phase's work is finite: no block
+// waits for one that has not started, whatever else the GPU runs.  The first block to join opens the
+// first round, and the one that finds no lepton left closes the tail; with none from the start
+// (k_multi_begin ran before) the blocks leave at once.  As in the launches before, a block gets at
+// least kLepChunkMin leptons: as many blocks stay as that allows for the first round, so a few
+// leptons are one block's work, without waits for others.  (A later round may be larger.  A block
+// that starts with 16 leptons and ends with some thousands takes no longer than the single steps'
+// launches would.)
+//
+// One block alone did all these rounds before.  199 steps of electrons at rest in a standing wave of
+// a0 = 1000, dt = lambda/200c: 1e4 electrons took 65.8 ms and take 7.3 (single steps: 17.8 ms), 1e5
+// 631 and 27.4 (45.7).  Where the third round leaves nothing the launch is 4.6 us, and the
+// k_multi_begin before it 5.8 (8.6 before, together): runs of 100 steps of a beam in a pulse, of
+// 1.2 ms, take what they took.
+constexpr uint32_t kTailClosed = ~0u;
+
 template <int FK, bool MIXED>
-__global__ __launch_bounds__(kMultiBlock) void k_multi_finish(MultiArgs m) {
+__global__ __launch_bounds__(kMultiBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_multi_tail(MultiArgs m) {
   extern __shared__ __attribute__((aligned(16))) double tab[];
   __shared__ MultiShared sh;
-  auto sync = [] {
+  __shared__ unsigned long long s_pub;
+  __shared__ uint32_t s_id;
+  __shared__ int s_last;
+  MultiCtl* const mc = m.mc;
+  auto ticket = [&](unsigned long long* t) {
+    __syncthreads();
+    if (threadIdx.x == 0) sh.chunk = (long long)atomicAdd(t, 1ull);
+    __syncthreads();
+    return sh.chunk;
+  };
+  auto joined = [&] { return __hip_atomic_load(&mc->joined, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  if (uni64(mc->n_left) == 0) return;
+  if (threadIdx.x == 0) s_id = atomicAdd(&mc->joined, 1u);
+  __syncthreads();
+  const uint32_t id = s_id;
+  uint32_t phase = 0, may = gridDim.x;
+  bool last = id == 0;  // phase 0: the first block alone, without work
+  for (;;) {
+    if (last) {  // block-uniform: prepare the phase after this one and publish it
+      __threadfence();
+      uint32_t next = phase + 1;
+      if (phase == 0) {
+        may = (uint32_t)min((int64_t)may, (mc->n_left + kLepChunkMin - 1) / kLepChunkMin);
+        // the blocks of a free GPU start within some microseconds: not without them, but not longer
+        if (threadIdx.x == 0)
+          for (int i = 0; i < 64 && joined() < may; ++i) __builtin_amdgcn_s_sleep(16);
+      } else if (phase % 3 == 0) {
+        multi_begin(m, kRounds, sh, (int)may, 0);
+        __syncthreads();
+        // (a generation per three phases, and at most k + 1 generations)
+        if (mc->n_left == 0 || phase > 3u * (uint32_t)m.k) next = kTailClosed;
+      } else if (phase % 3 == 1) {
+        multi_mid(m, sh, (int)may);
+      } else if (threadIdx.x == 0) {
+        mc->pair_ticket = 0;
+      }
+      __threadfence();
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        __hip_atomic_store(&mc->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&mc->pub, (unsigned long long)next << 32 | may << 16 | min(joined(), may), __ATOMIC_RELEASE,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    // the next phase that this block takes part in, or the end
+    if (threadIdx.x == 0) {
+      unsigned long long p;
+      for (;;) {
+        p = __hip_atomic_load(&mc->pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t ph = (uint32_t)(p >> 32);
+        if (ph != phase && ph != 0 && (ph == kTailClosed || id < (p & 0xFFFFu) || id >= ((p >> 16) & 0xFFFFu))) break;
+        __builtin_amdgcn_s_sleep(16);
+      }
+      s_pub = p;
+    }
+    __syncthreads();
+    __threadfence();
+    const unsigned long long p = s_pub;
+    phase = (uint32_t)(p >> 32);
+    may = (uint32_t)(p >> 16) & 0xFFFFu;
+    const uint32_t active = (uint32_t)p & 0xFFFFu;
+    if (phase == kTailClosed || id >= may) return;  // block-uniform
+    if (phase % 3 == 1) {
+      const int first = (int)min(ticket(&mc->lep_ticket), (long long)INT_MAX);
+      multi_lepton<FK, MIXED>(m, kRounds, sh, tab, tab + m.n_tab, first, 0);
+    } else if (phase % 3 == 2) {
+      multi_photon<FK, MIXED>(m, sh, tab);
+    } else {
+      // shares of the events, as many as would be blocks of k_multi_pairs, fewer for few events
+      const int64_t cnt = m.evc->count;
+      const int shares = m.evc->overflow ? kPairBlocks : (int)min((int64_t)kPairBlocks, (cnt + kMultiBlock - 1) / kMultiBlock);
+      for (long long v; (v = ticket(&mc->pair_ticket)) < shares;) multi_pairs<FK, MIXED>(m, (int)v, shares);
+    }
     __threadfence();
     __syncthreads();
-  };
-  for (int g = 0; g <= m.k; ++g) {
-    if (multi_begin(m, kRounds, sh, 1) == 0) break;  // block-uniform
-    sync();
-    multi_lepton<FK, MIXED>(m, kRounds, sh, tab, tab + m.n_tab, 0, 1);
-    sync();
-    multi_mid(m, sh, 1);
-    sync();
-    multi_photon<FK, MIXED>(m, sh, tab);
-    sync();
-    multi_pairs<FK, MIXED>(m, 0, 1);
-    sync();
+    if (threadIdx.x == 0) s_last = atomicAdd(&mc->arrived, 1u) + 1u == active;
+    __syncthreads();
+    last = s_last != 0;
   }
 }
 
@@ -909,9 +1000,10 @@ static void launch_multi_fk(MultiArgs m, hipStream_t s) {
     if (!pairs) return;
     hipLaunchKernelGGL(k_multi_mid, dim3(1), b, 0, s, m);
     hipLaunchKernelGGL((k_multi_photon<FK, MIXED>), dim3(m.ph_grid), b, shp, s, m);
-    hipLaunchKernelGGL((k_multi_pairs<FK, MIXED>), dim3(256), b, 0, s, m);
+    hipLaunchKernelGGL((k_multi_pairs<FK, MIXED>), dim3(kPairBlocks), b, 0, s, m);
   }
-  hipLaunchKernelGGL((k_multi_finish<FK, MIXED>), dim3(1), b, shl, s, m);
+  hipLaunchKernelGGL(k_multi_begin, dim3(1), b, 0, s, m);
+  hipLaunchKernelGGL((k_multi_tail<FK, MIXED>), dim3(std::min(m.lep_grid, 0xFFFF)), b, shl, s, m);
 }
 void launch_multi(int fk, MultiArgs m, bool mixed, hipStream_t s) {
 #define QED_MULTI(K)                               \

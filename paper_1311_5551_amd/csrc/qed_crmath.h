@@ -10,14 +10,16 @@
 //   exp: x = k ln2 + r, |r| <= ln2/2 (ln2 in three parts, the first with 42 bits so k*L1
 //        is exact), e^r by a degree-25 Taylor polynomial in Horner form, times 2^k.
 //   log: x = m 2^e, m in [1/sqrt2, sqrt2); one Newton step y1 = y0 + m e^{-y0} - 1 from the
-//        library value y0 = log(m), with e^{-y0} in double-double; plus e ln2.
+//        library value y0 = log(m), with e^{-y0} in double-double; plus e ln2.  Next to x = 1 the
+//        series of log(1 + r).
 //   sin/cos: x = k pi/2 + r, |r| <= pi/4 (pi/2 in three parts, the first with 33 bits),
 //        Taylor polynomials in r^2 to degree 29, quadrant from k mod 4.
 // These full double-double evaluations (*_dd) are the slow paths.  The entry points cr_exp,
-// cr_log, cr_sin, cr_cos and cr_sincos first evaluate a shorter series whose unrounded error is
-// below 2^-68 and return its rounding when an interval of 2^-66 around it rounds to a single
-// double (Ziv's test), which is then the correctly rounded result; about one call in 5000 falls
-// through to the slow path.  Same results, a tenth of the work and of the dependent latency.
+// cr_log, cr_sin, cr_cos and cr_sincos first evaluate a short series from a table of nodes, and
+// return its rounding when an interval of 2^-66 of it on either side rounds to a single double
+// (Ziv's test), which is then the correctly rounded result; about one call in 5000 falls through
+// to the slow path.  The short forms' unrounded error is below 2^-67 of the result (sine and cosine:
+// 2^-67.9 the largest of 3e6 arguments; exponential and logarithm: derived where they stand).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -105,6 +107,19 @@ __device__ __noinline__ double cr_log_dd(double x) {
   if (m < 0.70710678118654752) {
     m *= 2.0;
     e -= 1;
+  }
+  if (e == 0 && fabs(m - 1.0) < 0x1p-7) {
+    // next to 1 the Newton step's error, 2^-100 of 1, is large against the logarithm: its series
+    // r (1 - r/2 + r^2/3 - ...) to r^15, 1/n = (n - 1)! / n!
+    const double r = m - 1.0;  // exact
+    double f = 87178291200.0;  // 14!
+    dd p = dd_mul_d(c_inv_fact[15], f);
+    for (int n = 14; n >= 1; --n) {
+      f /= n;  // (n - 1)!, exact
+      p = dd_add(dd_mul_d(c_inv_fact[n], f), dd_mul_d(p, -r));
+    }
+    p = dd_mul_d(p, r);
+    return p.hi + p.lo;
   }
   const double y0 = log(m);
   // Newton step on e^y = m: y1 = y0 + m e^{-y0} - 1

@@ -58,6 +58,38 @@ def test_batched_cascades(precision, tables):
 
 
 @pytest.mark.parametrize("precision", PRECISIONS)
+@pytest.mark.parametrize("size", [(2, 2, 2, 3), (1024, 40, 1024, 40)])
+def test_smallest_and_largest_rate_tables(size, precision):
+    tb = Tables.build(**dict(zip(("n_eta", "n_chi", "n_chi_pair", "n_f"), size)))
+    w = _at_rest(300, 1500.0, 120)
+    ra, rb = Run(w, tb, precision=precision), Run(w, tb, precision=precision)
+    _single(ra, 120)
+    rb.run(120)
+    _same(ra, rb)
+
+
+def test_cascades_on_two_streams(tables):
+    # two tails share the GPU: each advances with the blocks that it has running
+    ws = [_at_rest(3000, a0, 150, seed=s) for a0, s in ((1000.0, 3), (1200.0, 8))]
+    alone, both = [Run(w, tables) for w in ws], [Run(w, tables) for w in ws]
+    for r in alone:
+        r.run(150)
+        r.synchronize()
+    assert both[0].stream.cuda_stream != both[1].stream.cuda_stream
+    for _ in range(3):
+        for r in both:
+            r.run(50)
+    for a, b in zip(alone, both):
+        b.synchronize()
+        for name in ("electron", "positron", "photon"):
+            x, y = a.species(0, name), b.species(0, name)
+            i, j = np.argsort(x["uid"]), np.argsort(y["uid"])
+            assert len(i) == len(j) > 1000 * (name != "positron")
+            for k in x:
+                np.testing.assert_array_equal(x[k][i], y[k][j], err_msg="%s.%s" % (name, k))
+
+
+@pytest.mark.parametrize("precision", PRECISIONS)
 def test_cascade_is_no_slower_than_single_steps(precision, tables):
     # with the later generations in one block the run took 3.7 times as long as the single steps
     def best(advance):

@@ -17,8 +17,12 @@ photon inside its pair window: the steps in which its pair rate can be non-zero)
 outside their window, whose position is the closed form of their birth record, are not counted;
 their count is reported apart (`photon_slot_steps`).
 
-Also on the same JSON line: the roofline of the dominant kernel (algorithmic bytes per launch /
-its mean HIP-event duration over the same window, against 8 TB/s), and the FP64 oracle timed on
+The timed steps of the collision, batched and uniform forms are `qed_run` calls of one compaction
+period, which advance each particle by all of their steps at once; the grid forms take single steps.
+
+Also on the same JSON line: the roofline of the dominant kernel of single steps over the same window
+(algorithmic bytes per launch / its mean HIP-event duration, against 8 TB/s; the runs launch other
+kernels), and the FP64 oracle timed on
 the host cores over a bounded sample of the same workload.  `detail` holds the other forms
 (FP32-mixed, batched instances, the 2-D grid workload, the uniform-field workload) and the
 value of the whole 20000-step schedule.
@@ -262,7 +266,8 @@ def run_form(form, args, tables, tuned):
     from paper_1311_5551_amd import autotune, capi, workloads as W
     from paper_1311_5551_amd.sim import Run
 
-    graphs = form not in ("grid", "feedback") and not args.no_graphs
+    runs = form not in ("grid", "feedback") and not args.no_graphs
+    how = "%d-step runs" if runs else "single steps, periods of %d"
     if form == "feedback":
         w = W.feedback_config(n=args.grid_electrons)
         total = size_grid(w, tables, args)
@@ -287,8 +292,7 @@ def run_form(form, args, tables, tuned):
         total = w.n_steps
         ws, pre, s0, steps = [w], 0, 0, total
         workload = ("uniform_b_1e4: 10000 electrons gamma0=1000 perpendicular to a uniform B (eta0=1), dt=0.01 "
-                    "gyro-periods, steps 0..%d, photons recorded (not propagated), FP64, hipGraph replay of "
-                    "100-step graphs" % total)
+                    "gyro-periods, steps 0..%d, photons recorded (not propagated), FP64, %s" % (total, how % args.compact_every))
     elif form == "batched":
         ws = W.batched_config5(n_steps=SCHEDULE, n_scale=args.batched_scale)
         pre, s0 = window(SCHEDULE, args.batched_warmup, args.batched_window, MEET)
@@ -297,10 +301,10 @@ def run_form(form, args, tables, tuned):
         total = s0 + steps
         workload = ("batched_collisions: 256 instances, N_i=floor(%s10^U(3,6)) (total %d electrons), a0~U(50,500), "
                     "gamma0 log-U[500,5000], FP32-mixed, dt=lambda/200c, steps %d..%d of %d (window centred on the "
-                    "collisions at step %d; %d untimed steps before), hipGraph replay of %d-step graphs, "
+                    "collisions at step %d; %d untimed steps before), %s, "
                     "compaction every %d%s"
                     % ("" if args.batched_scale == 1.0 else "%g*" % args.batched_scale, sum(w.n for w in ws), s0,
-                       s0 + steps, SCHEDULE, MEET, s0, args.compact_every, args.compact_every,
+                       s0 + steps, SCHEDULE, MEET, s0, how % args.compact_every, args.compact_every,
                        " retiring the photons whose pair window is over" if args.batched_retire else ""))
     else:
         w = W.collision_config2(n=args.electrons, n_steps=SCHEDULE)
@@ -324,12 +328,12 @@ def run_form(form, args, tables, tuned):
             r.set_retire(RETIRE_BINS, RETIRE_EMIN, RETIRE_EMAX)
         return r
 
-    def advance(run, step, k, graph):
-        """k steps from `step`: graph replay of whole compaction periods, compaction between them."""
+    def advance(run, step, k, in_runs):
+        """k steps from `step`: a run per compaction period (`in_runs`) or single steps, compaction between them."""
         done = 0
         while done < k:
             n = min(args.compact_every - step % args.compact_every, k - done)
-            if graph:
+            if in_runs:
                 run.run(n, graph_steps=n if n == args.compact_every else 0)
             else:
                 for i in range(n):
@@ -352,7 +356,7 @@ def run_form(form, args, tables, tuned):
         led0 = _aggregate(run.ledger())
         run.synchronize()
         t0 = time.perf_counter()
-        advance(run, 0, SCHEDULE, graphs)
+        advance(run, 0, SCHEDULE, runs)
         run.synchronize()
         t1 = time.perf_counter()
         led1 = _aggregate(run.ledger())
@@ -368,15 +372,15 @@ def run_form(form, args, tables, tuned):
     run = make_run()
     if pre:
         log("%s: %d untimed steps to the window" % (form, pre))
-    step = advance(run, 0, pre, graphs)
+    step = advance(run, 0, pre, runs)
     warm = s0 - pre
     log("%s: %d warmup steps" % (form, warm))
-    step = advance(run, step, warm, graphs)
+    step = advance(run, step, warm, runs)
     led0 = run.ledger()
     run.synchronize()
     log("%s: timing steps %d..%d" % (form, s0, s0 + steps))
     t0 = time.perf_counter()
-    step = advance(run, step, steps, graphs)
+    step = advance(run, step, steps, runs)
     run.synchronize()
     t1 = time.perf_counter()
     led1 = run.ledger()
@@ -384,11 +388,11 @@ def run_form(form, args, tables, tuned):
     del run
     torch.cuda.empty_cache()
     # kernel times: HIP events around every kernel class on the run's stream, over the same
-    # steps replayed eagerly from the same initial state (graph replay records no per-kernel
-    # events, and the event records would add launch gaps to the timed run)
-    log("%s: kernel timing pass (HIP events, steps %d..%d, eager)" % (form, s0, s0 + steps))
+    # steps taken one by one from the same initial state (the timed runs advance each particle by
+    # many steps at once, in other kernels)
+    log("%s: kernel timing pass (HIP events, steps %d..%d, single steps)" % (form, s0, s0 + steps))
     run = make_run()
-    step = advance(run, 0, s0, graphs)
+    step = advance(run, 0, s0, runs)
     lk0 = _aggregate(run.ledger())
     run.profile(True)
     step = advance(run, step, steps, False)
@@ -422,9 +426,11 @@ def run_form(form, args, tables, tuned):
                            for i, l in enumerate(led1) if l["n_dropped"] > 0][:16],
                photons_retired=int(sum(l["n_retired"] for l in led1)),
                launch={k: (tuned.get(k) if tuned else None) for k in ("lepton", "photon")},
-               kernel_timing="HIP events per kernel class on the run's stream over the same steps replayed eagerly "
-                             "from the same initial state" + (" (the timed run replays captured HIP graphs)"
-                                                               if graphs else ""))
+               timed_path="runs of %d steps, each particle advanced by all of a run's steps at once" % args.compact_every
+                          if runs else "single steps",
+               kernel_timing="HIP events per kernel class on the run's stream over the same steps taken one by one "
+                             "from the same initial state" + ("; kernel_ms, launches, launch and the roofline are "
+                                                               "those of these single steps" if runs else ""))
     # the kernel that takes the most time in the window bounds the step
     kind = "photon" if ms[2] >= ms[1] else "lepton"
     byts = kernel_bytes("fp64" if prec == capi.QED_FP64 else "fp32", kind, lk0, lk1, grid=form in ("grid", "feedback"),
@@ -436,7 +442,7 @@ def run_form(form, args, tables, tuned):
     res["roofline"] = {"kernel": "k_%s (%s)" % (kind, form), "bound": "hbm",
                        "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                        "traffic": traffic, "algorithmic_bytes_per_launch": byts / max(n_l, 1),
-                       "mean_launch_us": avg_s * 1e6}
+                       "mean_launch_us": avg_s * 1e6, "taken_over": "single steps"}
     if form == "feedback" and launches[5]:
         # the Yee solver's three passes per step (B half, E, B half): 9 + 15 + 9 planes of nx x ny
         # FP64 words read or written; one fused pass would need 15 (read E, B, J; write E, B, J)
@@ -519,7 +525,7 @@ def main():
     ap.add_argument("--grid-electrons", type=int, default=16_000_000)
     ap.add_argument("--grid-sort-every", type=int, default=10, help="grid form: steps between spatial sorts")
     ap.add_argument("--no-graphs", action="store_true",
-                    help="time eager launches instead of graph replay")
+                    help="time single steps instead of runs of --compact-every steps")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="only run plain device copies of 1 GiB (reference for HBM byte counters)")
@@ -571,7 +577,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": main_r["workload"], "form": main_r["form"], "instances": main_r["n_inst"],
                    "counted": "evaluated particle-steps: lepton steps + photon steps inside the photon's pair window",
-                   # the shapes the run used: tuned (cache or replica) per sweep, else the command line
+                   # the single-step sweeps' shapes: tuned (cache or replica) per sweep, else the command line
                    "launch": ({k: {"block": v["block"], "particles_per_thread": v["ppt"]}
                                for k, v in main_r["launch"].items() if v}
                               if any(main_r["launch"].values()) else

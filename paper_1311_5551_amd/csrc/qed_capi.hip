@@ -1,7 +1,7 @@
 // C ABI of libqed (declared in include/qed.h): argument checking, device memory that the
 // library owns (tables, workspace), kernel launch sequencing, HIP-graph replay and the
 // energy ledger.  No call here computes physics on the host; every step of the method
-// runs in the kernels of qed_tables.hip, qed_step.hip and qed_mixed.h.
+// runs in the kernels of qed_tables.hip, qed_step.hip, qed_multi.hip, qed_sort.hip and qed_fdtd.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

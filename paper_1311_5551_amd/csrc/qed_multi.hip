@@ -24,9 +24,9 @@
 //
 // Measured against single steps replayed from graphs: a beam of 1e5 electrons through a 10 fs pulse
 // (1200 steps) 97.8 -> 15.2 ms, 1e6 through 30 fs (3800 steps) 726 -> 222 ms, 48 batched beams
-// 485 -> 99 ms, 1e4 electrons in a uniform field (1000 steps) 41.8 -> 7.0 ms.  The sweeps issue vector
-// instructions most of the time (the photon kernel all of it); small runs are the latency of one
-// lane's steps.
+// 485 -> 98 ms, 1e4 electrons in a uniform field (1000 steps) 41.8 -> 6.9 ms.  At the peak of the
+// collision of 1e6 the photon kernel issues vector instructions 99% of the time and the lepton
+// kernel 55% (at four cycles each); small runs are the latency of one lane's steps.
 #include <hip/hip_runtime.h>
 #include <limits.h>
 #include <stdint.h>

@@ -201,7 +201,8 @@ class Run:
         capi.qed_set_event_queue(self.ws, capacity)
 
     def step(self, n: int = 1):
-        """n steps: one by qed_step, more by qed_run (the same results)."""
+        """n steps: one by qed_step, more by qed_run (the same results; where a full buffer drops
+        children, which ones may differ)."""
         if n == 1:
             capi.qed_step(self.tables.handle, self.ws, self.params, self._s())
         elif n > 1:

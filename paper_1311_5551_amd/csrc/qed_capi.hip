@@ -103,10 +103,10 @@ struct qed_tables {
 };
 
 constexpr int64_t kDefaultEventQueue = int64_t(1) << 20;
-// Steps of a multi-step run.  Its 16 launches and the serial steps of late pair children cost as
+// Steps of a multi-step run.  Its 17 launches and the serial steps of late pair children cost as
 // much as three single steps: 3 steps take 276 us one by one and 318 us as a run with 1.3e5 electrons
-// in a collision (FP32-mixed; 258 and 256 us with 1e5 in FP64), 4 take 369 and 334 us (344 and 265 us);
-// with 1e6 electrons 1862 and 721 us, with 1e4 in a uniform field 148 and 50 us.  At most 256 steps,
+// in a collision (FP32-mixed; 258 and 256 us with 1e5 in FP64), 4 take 371 and 335 us (345 and 262 us);
+// with 1e6 electrons 1870 and 725 us, with 1e4 in a uniform field 148 and 50 us.  At most 256 steps,
 // which bounds a lane's counters and the time of one launch.
 constexpr int64_t kMultiMin = 4, kMultiMax = 256;
 

@@ -8,7 +8,7 @@ import pytest
 
 from paper_1311_5551_amd import capi, workloads as W
 from paper_1311_5551_amd.sim import Run, Tables
-from test_gpu_multi import FULL, _same, _single
+from test_gpu_multi import FULL, _make, _same, _same_particles, _single
 
 pytestmark = pytest.mark.gpu
 
@@ -80,13 +80,8 @@ def test_cascades_on_two_streams(tables):
         for r in both:
             r.run(50)
     for a, b in zip(alone, both):
-        b.synchronize()
-        for name in ("electron", "positron", "photon"):
-            x, y = a.species(0, name), b.species(0, name)
-            i, j = np.argsort(x["uid"]), np.argsort(y["uid"])
-            assert len(i) == len(j) > 1000 * (name != "positron")
-            for k in x:
-                np.testing.assert_array_equal(x[k][i], y[k][j], err_msg="%s.%s" % (name, k))
+        _same_particles(a, b)
+        assert b.count(0, "positron") > 1000
 
 
 @pytest.mark.parametrize("precision", PRECISIONS)
@@ -107,3 +102,27 @@ def test_cascade_is_no_slower_than_single_steps(precision, tables):
     single, run = best(_single), best(lambda r, k: r.run(k))
     print("single steps %.2f ms, run %.2f ms" % (1e3 * single, 1e3 * run))
     assert run < 1.25 * single
+
+
+@pytest.mark.parametrize("kind", ["cascade", "pulse"])
+def test_run_in_a_captured_graph(kind, tables):
+    # a program's own graph of a run and a compaction, replayed with eager work between the replays
+    w = _at_rest(500, 1200.0, 121) if kind == "cascade" else _make("pulse", 1500, 121)
+    ra, rb = Run(w, tables), Run(w, tables)
+    for r in (ra, rb):
+        r.step(1)
+        r.synchronize()
+    torch = rb.torch
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=rb.stream):
+        rb.run(30)
+        rb.compact()
+    for _ in range(4):
+        ra.run(30)
+        ra.compact()
+        with torch.cuda.stream(rb.stream):
+            g.replay()
+        assert rb.ledger()[0]["n_emit"] == ra.ledger()[0]["n_emit"]
+        torch.ones(100, device=rb.dev).sum().item()
+    _same_particles(ra, rb)
+    assert ra.ledger()[0]["n_pair"] == rb.ledger()[0]["n_pair"] > 0

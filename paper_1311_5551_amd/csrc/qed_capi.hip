@@ -522,6 +522,12 @@ qed_status enqueue_multi(const qed_tables* tb, qed_workspace* ws, const qed_step
   return QED_OK;
 }
 
+// whether work enqueued on `s` is recorded into a caller's graph (the null stream cannot be)
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  return s && hipStreamIsCapturing(s, &c) == hipSuccess && c == hipStreamCaptureStatusActive;
+}
+
 // (Re)computes the photons' pair windows.  Enqueued on `s` outside any graph capture.
 qed_status make_windows(qed_workspace* ws, double t0, double dt, double cp_min, hipStream_t s) {
   const bool same = ws->win_made && ws->win_t0 == t0 && ws->win_dt == dt && ws->win_cp_min == cp_min;
@@ -1119,7 +1125,8 @@ qed_status qed_compact(qed_workspace* ws, qed_stream stream) {
   // After a sort the windows are not those of the photons in their slots: they are made again (and
   // the next step need not) before photons are retired or partitioned by them.  Before the first
   // step after a bind there are none: the compaction then only removes converted photons.
-  if (ws->win_made && !ws->win_valid) {
+  const bool remake = ws->win_made && !ws->win_valid, front = ws->win_front;
+  if (remake) {
     const qed_status st = make_windows(ws, ws->win_t0, ws->win_dt, ws->win_cp_min, (hipStream_t)stream);
     if (st) return st;
   }
@@ -1127,6 +1134,10 @@ qed_status qed_compact(qed_workspace* ws, qed_stream stream) {
                  ws->d_lmask, ws->prec == QED_FP32_MIXED, ws->win_made ? ws->retire : RetireSpec(), ws->win_made,
                  (hipStream_t)stream);
   HIP_TRY(hipGetLastError());
+  if (remake && capturing((hipStream_t)stream)) {  // recorded, not run: the windows are as they were
+    ws->win_valid = false;
+    ws->win_front = front;
+  }
   return QED_OK;
 }
 

@@ -74,3 +74,30 @@ def test_compaction_before_the_first_step(retire, tables):
         r.compact()
     la = _same(ra, rb)
     assert la["n_pair"] > 0 and (la["n_retired"] > 0) == bool(retire)
+
+
+def test_a_captured_compaction_leaves_the_windows_to_the_next_step(tables):
+    # recorded after a sort and not replayed: the next step still makes the windows again
+    def make():
+        w = W.grid_config3(n=3000, nx=250, ny=61, a0=700.0, n_steps=120, seed=4)
+        w.capacity = dict(electron=30 * w.n, positron=30 * w.n, photon=100 * w.n)
+        return Run(w, tables)
+    ra, rb = make(), make()
+    for r in (ra, rb):
+        for _ in range(60):
+            r.step(1)
+    rb.sort()
+    rb.synchronize()
+    g = rb.torch.cuda.CUDAGraph()
+    with rb.torch.cuda.graph(g, stream=rb.stream):
+        rb.compact()
+    for i in range(60):
+        for r in (ra, rb):
+            r.step(1)
+        if i == 30:
+            rb.sort()
+            with rb.torch.cuda.stream(rb.stream):
+                g.replay()
+    for r in (ra, rb):
+        r.compact()
+    assert _same(ra, rb)["n_pair"] > 0

@@ -142,8 +142,8 @@ TUNED_CACHE = os.path.join(ROOT, "paper_1311_5551_amd", "tuned_launch.json")
 
 def tuned_launch(form, args, tables):
     """Cached tuned shapes for (device, form, collision workload size, kernel sources), else a
-    fresh tuning whose result is written to gpurun_out/tuned_launch.json (the tuner's output
-    file; the package's cache holds its entries)."""
+    fresh tuning whose result is written to the tuner's output file (the package's cache holds its
+    entries)."""
     import torch
     from paper_1311_5551_amd import autotune, capi
     prec = capi.QED_FP64 if form == "fp64" else capi.QED_FP32_MIXED
